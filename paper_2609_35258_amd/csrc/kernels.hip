@@ -1998,6 +1998,22 @@ static inline int grid_for(int n, int per = MAXW) {
     return b < NXCD ? NXCD : (b > 1048576 ? 1048576 : b);
 }
 
+// The cross-level faces are few, long items beside the same-level face stages:
+// FP64 takes two waves per SIMD (at four, 450 registers spill: cylinder 95 x 45,
+// 236 faces, 0.212 ms, 0.126 at two); FP32 is no slower at four (cylinder 256 x
+// 128, 566 faces, 0.223 and 0.213 ms alone, and the step 1% faster at four).
+#define MLVS_LAUNCH_X(prec, W32_, W64_, M_, ...)                                                 \
+    do {                                                                                        \
+        if ((prec) == 32) hipLaunchKernelGGL((k_xface<float, W32_, M_>), __VA_ARGS__);           \
+        else hipLaunchKernelGGL((k_xface<double, W64_, M_>), __VA_ARGS__);                       \
+    } while (0)
+#define MLVS_DISPATCH_X(prec, var, mk, ...)                                                      \
+    do {                                                                                        \
+        if (mk) MLVS_LAUNCH_X(prec, 4, 2, 1, __VA_ARGS__);                                       \
+        else if ((var) == 2) MLVS_LAUNCH_X(prec, 2, 1, 0, __VA_ARGS__);                          \
+        else MLVS_LAUNCH_X(prec, 4, 2, 0, __VA_ARGS__);                                          \
+    } while (0)
+
 // Tunable kernels are instantiated for several (points per lane per chunk U,
 // minimum waves per SIMD) pairs; the variant index selects one at launch.
 // (1, 2) gives the FP64 fused kernels 256 VGPRs, where (1, 4) spills.
@@ -2033,11 +2049,31 @@ constexpr int N_VARIANTS = 5;
         default: MLVS_LAUNCH_UWC(prec, KERNEL, 2, 4, C_, __VA_ARGS__); break;                    \
         }                                                                                       \
     } while (0)
-// ... and for the kernels instantiated per compatibility order (4 or 8 moments)
+// ... and for the kernels instantiated per compatibility order.  The 64 sums of
+// eight moments need 256 registers: at four waves per SIMD (128) every variant
+// spilled 480 to 690 of them (cylinder 95 x 45, 61^2, FP64: update 0.68 ms,
+// 0.15 ms at two waves).
 #define MLVS_DISPATCH_VC(prec, var, cm, KERNEL, ...)                                             \
     do {                                                                                        \
-        if ((cm) == 8) MLVS_DISPATCH_VC1(prec, var, 8, KERNEL, __VA_ARGS__);                     \
+        if ((cm) == 8) MLVS_LAUNCH_UWC(prec, KERNEL, 1, 2, 8, __VA_ARGS__);                      \
         else MLVS_DISPATCH_VC1(prec, var, 4, KERNEL, __VA_ARGS__);                               \
+    } while (0)
+// ... the update with the next cell stage: its scalar chain spills at four
+// waves per SIMD (cavity 64 x 64, 28^2, FP64: 0.116 ms, 0.105 ms at two)
+#define MLVS_DISPATCH_VU1(prec, var, C_, KERNEL, ...)                                            \
+    do {                                                                                        \
+        switch (var) {                                                                          \
+        case 0: MLVS_LAUNCH_UWC(prec, KERNEL, 1, 2, C_, __VA_ARGS__); break;                     \
+        case 2: MLVS_LAUNCH_UWC(prec, KERNEL, 4, 2, C_, __VA_ARGS__); break;                     \
+        case 3: MLVS_LAUNCH_UWC(prec, KERNEL, 2, 3, C_, __VA_ARGS__); break;                     \
+        case 4: MLVS_LAUNCH_UWC(prec, KERNEL, 4, 1, C_, __VA_ARGS__); break;                     \
+        default: MLVS_LAUNCH_UWC(prec, KERNEL, 2, 2, C_, __VA_ARGS__); break;                    \
+        }                                                                                       \
+    } while (0)
+#define MLVS_DISPATCH_VU(prec, var, cm, KERNEL, ...)                                             \
+    do {                                                                                        \
+        if ((cm) == 8) MLVS_DISPATCH_VU1(prec, var, 8, KERNEL, __VA_ARGS__);                     \
+        else MLVS_DISPATCH_VU1(prec, var, 4, KERNEL, __VA_ARGS__);                               \
     } while (0)
 
 // ... and per mesh kind (unstructured meshes: the (1, 4) pair for every
@@ -2082,7 +2118,8 @@ constexpr int N_VARIANTS = 5;
     } while (0)
 #define MLVS_DISPATCH_VCM(prec, var, cm, mk, KERNEL, ...)                                        \
     do {                                                                                        \
-        if ((cm) == 8) MLVS_DISPATCH_VCM1(prec, var, 8, mk, KERNEL, __VA_ARGS__);                \
+        if ((cm) == 8 && (mk)) MLVS_LAUNCH_UWCM(prec, KERNEL, 1, 2, 8, 1, __VA_ARGS__);          \
+        else if ((cm) == 8) MLVS_LAUNCH_UWCM(prec, KERNEL, 1, 2, 8, 0, __VA_ARGS__);             \
         else MLVS_DISPATCH_VCM1(prec, var, 4, mk, KERNEL, __VA_ARGS__);                          \
     } while (0)
 
@@ -2160,7 +2197,7 @@ hipError_t launch_update_cell(int prec, hipStream_t st, const LevelDesc* lv, con
                               const int* cell_frow, const FaceItem* items, const double* fpar, double* params,
                               Phys ph, double* cmom, int var) {
     if (n_cells <= 0) return hipSuccess;
-    MLVS_DISPATCH_VC(prec, var, ph.compat, k_update_cell, dim3(grid_for(n_cells)), dim3(BS), 0, st, lv, cell_lev,
+    MLVS_DISPATCH_VU(prec, var, ph.compat, k_update_cell, dim3(grid_for(n_cells)), dim3(BS), 0, st, lv, cell_lev,
                      cell_slot, order, n_cells, geom, cell_frow, items, fpar, params, ph, cmom);
     return hipGetLastError();
 }
@@ -2225,7 +2262,7 @@ __device__ __forceinline__ void side_refined(const SD& sd, const LevelDesc& Ln, 
     sy[1] = sy[1] + dq * sy[0];
 }
 
-template <typename S, int U, int MK>
+template <typename S, int MK>
 __device__ __forceinline__ void xface_items(const LevelDesc* __restrict__ lvs, const XFaceItem* __restrict__ items,
                                             int n, const int* __restrict__ cell_slot,
                                             const int* __restrict__ cell_nbr, const CellGeom* __restrict__ geom,
@@ -2388,12 +2425,12 @@ __device__ __forceinline__ void xface_items(const LevelDesc* __restrict__ lvs, c
     }
 }
 
-template <typename S, int U, int MINW, int MK>
+template <typename S, int MINW, int MK>
 __global__ __launch_bounds__(BS, MINW) void k_xface(const LevelDesc* __restrict__ lvs, const XFaceItem* __restrict__ items,
                                               int n, const int* __restrict__ cell_slot,
                                               const int* __restrict__ cell_nbr, const CellGeom* __restrict__ geom,
                                               const double* __restrict__ params, Phys ph, unsigned long long* neg) {
-    xface_items<S, U, MK>(lvs, items, n, cell_slot, cell_nbr, geom, params, ph, neg, item0(), istride());
+    xface_items<S, MK>(lvs, items, n, cell_slot, cell_nbr, geom, params, ph, neg, item0(), istride());
 }
 
 // ---------------------------------------------------------------------------
@@ -2938,7 +2975,7 @@ __global__ __launch_bounds__(BS, MINW) void k_step_persistent(const StepArgs* __
     ghost_items<S>(A->lvs, A->ghosts, A->n_ghosts, A->cell_lev, A->cell_slot, A->params, ph, A->neg, first, stride);
     grid_barrier(A->sync, phase);
     const int nx = A->n_xfaces;
-    xface_items<S, U, MK>(A->lvs, A->xfaces, nx, A->cell_slot, A->cell_nbr, A->geom, A->params, ph, A->neg, first,
+    xface_items<S, MK>(A->lvs, A->xfaces, nx, A->cell_slot, A->cell_nbr, A->geom, A->params, ph, A->neg, first,
                           stride);
     const int fstart = ((first - nx) % stride + stride) % stride;
     face_full_items<S, U, CM, MK>(A->lvs, A->faces, A->n_faces, A->cell_slot, A->cell_nbr, A->geom, A->params,
@@ -3003,7 +3040,7 @@ hipError_t launch_xface(int prec, hipStream_t st, const LevelDesc* lv, const XFa
                         const int* cell_slot, const int* cell_nbr, const CellGeom* geom, const double* params,
                         Phys ph, unsigned long long* neg, int var) {
     if (n <= 0) return hipSuccess;
-    MLVS_DISPATCH_VM(prec, var, ph.mesh_kind, k_xface, dim3(grid_for(n)), dim3(BS), 0, st, lv, items, n, cell_slot,
+    MLVS_DISPATCH_X(prec, var, ph.mesh_kind, dim3(grid_for(n)), dim3(BS), 0, st, lv, items, n, cell_slot,
                      cell_nbr, geom, params, ph, neg);
     return hipGetLastError();
 }
