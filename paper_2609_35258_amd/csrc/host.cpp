@@ -1135,6 +1135,11 @@ struct mlvs_ctx_s {
     bool prep_valid = false;           // phi_bar+ rows and parameters match the stored state
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
+    // STEP_BATCH steps as one graph, captured once a level set has been replayed
+    // for a while (see do_steps)
+    hipGraph_t graph_n = nullptr;
+    hipGraphExec_t gexec_n = nullptr;
+    int replays = 0;                   // single-step replays of the current graph
     // cross-level faces run on a second stream (default priority) beside the
     // same-level face stages, forked after the ghost rows and joined before the
     // update
@@ -1198,8 +1203,11 @@ void alloc_state(mlvs_ctx c, Level& L) {
 void drop_graph(mlvs_ctx c) {
     if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
     if (c->graph) (void)hipGraphDestroy(c->graph);
-    c->gexec = nullptr;
-    c->graph = nullptr;
+    if (c->gexec_n) (void)hipGraphExecDestroy(c->gexec_n);
+    if (c->graph_n) (void)hipGraphDestroy(c->graph_n);
+    c->gexec = c->gexec_n = nullptr;
+    c->graph = c->graph_n = nullptr;
+    c->replays = 0;
 }
 
 void free_items(mlvs_ctx c) {
@@ -1802,7 +1810,7 @@ void retile_rows(mlvs_ctx c) {
     c->prep_valid = prep && keep_mom;
 }
 
-void do_step(mlvs_ctx c);
+int do_steps(mlvs_ctx c, int left);
 // The cell stage reads the raw moments of the stored state from d_cmom; the
 // update keeps them current.  After any other write of the state they are
 // recomputed once, outside the step (and outside a captured step graph).
@@ -2950,9 +2958,9 @@ mlvs_status mlvs_step(mlvs_ctx c, int n_steps) {
             ensure_moments(c);
             strict_check(c, -1);
         }
-        for (int k = 0; k < n_steps; ++k) {
-            do_step(c);
-            if (c->strict & 1) strict_check(c, k);
+        for (int k = 0; k < n_steps;) {
+            k += do_steps(c, c->strict & 1 ? 1 : n_steps - k);
+            if (c->strict & 1) strict_check(c, k - 1);
         }
         if (c->strict & 2) {
             unsigned long long neg1[3] = {0, 0, 0};
@@ -3434,9 +3442,31 @@ mlvs_status mlvs_criterion(mlvs_ctx c, uint8_t* out) {
 
 namespace {
 
-void do_step(mlvs_ctx c) {
-    const int n = c->mesh.n_cells;
-    if (c->adaptive && c->ap.interval > 0 && c->step_count % c->ap.interval == 0) {
+// Capture `steps` steps' launches as a graph.
+void capture_steps(mlvs_ctx c, int steps, hipGraph_t& graph, hipGraphExec_t& exec) {
+    hip_check(hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal), "begin capture");
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < steps && e == hipSuccess; ++k) e = launch_step_kernels(c);
+    hipGraph_t g = nullptr;
+    hipError_t e2 = hipStreamEndCapture(c->st, &g);
+    graph = g;
+    hip_check(e, "captured launch");
+    hip_check(e2, "end capture");
+    hip_check(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0), "graph instantiate");
+    ++c->n_captures;
+}
+
+// One step of a call with `left` steps to go, or STEP_BATCH of them; returns how
+// many.  Between two graph launches the GPU idles for several microseconds, a
+// fifth of a small problem's step (1-D, 200 cells, FP64: 29.7 us a step
+// replayed singly, 23.4 by eights; cavity 64 x 64, 28^2: 264 and 255): level
+// sets of small levels (fused steps) replay STEP_BATCH steps as one graph,
+// captured after BATCH_AFTER single replays, so that a short run or a level set
+// that is soon replaced does not pay for the longer capture.
+constexpr int STEP_BATCH = 8, BATCH_AFTER = 64;
+int do_steps(mlvs_ctx c, int left) {
+    const int64_t at = c->adaptive && c->ap.interval > 0 ? c->step_count % c->ap.interval : -1;
+    if (at == 0) {
         if (mlvs_adapt(c, nullptr) != MLVS_OK) throw Fail{MLVS_E_STATE, g_last_error};
     }
     ensure_moments(c);
@@ -3446,27 +3476,26 @@ void do_step(mlvs_ctx c) {
         hip_check(launch_stage(c, 0), "cell stage launch");
         c->prep_valid = true;
     }
+    int steps = 1;
     if (c->use_graph) {
-        if (!c->gexec) {
-            hip_check(hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal), "begin capture");
-            hipError_t e = launch_step_kernels(c);
-            hipGraph_t g = nullptr;
-            hipError_t e2 = hipStreamEndCapture(c->st, &g);
-            hip_check(e, "captured launch");
-            hip_check(e2, "end capture");
-            c->graph = g;
-            hip_check(hipGraphInstantiate(&c->gexec, c->graph, nullptr, nullptr, 0), "graph instantiate");
-            ++c->n_captures;
+        if (!c->gexec) capture_steps(c, 1, c->graph, c->gexec);
+        if (c->fused && !c->persistent && left >= STEP_BATCH && c->replays >= BATCH_AFTER &&
+            (at < 0 || at + STEP_BATCH <= c->ap.interval)) {
+            if (!c->gexec_n) capture_steps(c, STEP_BATCH, c->graph_n, c->gexec_n);
+            steps = STEP_BATCH;
+        } else {
+            ++c->replays;
         }
-        hip_check(hipGraphLaunch(c->gexec, c->st), "graph launch");
+        hip_check(hipGraphLaunch(steps > 1 ? c->gexec_n : c->gexec, c->st), "graph launch");
         ++c->n_graph_launches;
     } else {
         hip_check(launch_step_kernels(c), "step launch");
     }
     c->prep_valid = c->fused || c->persistent;
-    ++c->step_count;
-    c->cnt_updates += c->step_points;
-    c->cnt_iface += c->step_iface_points;
+    c->step_count += steps;
+    c->cnt_updates += steps * c->step_points;
+    c->cnt_iface += steps * c->step_iface_points;
+    return steps;
 }
 
 // The stages one step launches, in order.
