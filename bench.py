@@ -397,9 +397,9 @@ def cell_areas(p):
 VARIANTS = {0: (1, 4), 1: (2, 4), 2: (4, 2), 3: (4, 4), 4: (1, 2)}
 # kernels instantiated per compatibility order carry it as a template argument,
 # and the face kernels the mesh kind (0 structured, 1 unstructured) after it
-STAGE_CM = ("cell", "face_target", "face", "update_cell")
-STAGE_MK = ("face_rec", "face", "xface")
-STAGE_KERNEL = {"face": "k_face_full", "update_cell": "k_update_cell",
+STAGE_CM = ("cell", "face_target", "update_cell")
+STAGE_MK = ("face_rec", "xface")
+STAGE_KERNEL = {"update_cell": "k_update_cell",
                 "cell": "k_cell_prep", "face_rec": "k_face_rec", "face_target": "k_face_target",
                 "update": "k_update", "xface": "k_xface"}
 

@@ -346,8 +346,8 @@ mlvs_status mlvs_counters(mlvs_ctx ctx, int64_t* steps, double* cell_updates, do
  * faces: face state, corrected target, recovery weights), 4 cross-level
  * faces, 5 update (fluxes and new state; the state is saved before and put
  * back after the timed launches), 6 criterion, and the fused forms of the
- * step whose levels have at most 1024 points: 7 face reconstruction and target
- * in one launch, 8 update followed by the next step's cell stage (state, rows
+ * step whose levels have at most 1024 points: 7 face reconstruction, then
+ * target, 8 update followed by the next step's cell stage (state, rows
  * and parameters saved and put back as for 5; MLVS_E_STATE when the step is
  * not fused), 9 the persistent step (state saved and put back as for 8;
  * MLVS_E_STATE when it is off).  Needs a step taken since the last level

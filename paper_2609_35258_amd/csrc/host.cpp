@@ -283,6 +283,7 @@ struct Level {
     bool geo_in_arena = false;             // device geometry lives in a build's staging block
     // device
     double *d_x = nullptr, *d_y = nullptr, *d_w = nullptr;
+    int* d_ang = nullptr;                  // angle bounds of every 64 points (see angle_bounds)
     float* d_xy = nullptr;                 // (xi_x, xi_y) pairs in float, for FP32 storage
     int* d_pt_of_base = nullptr;
     int stride = 0;
@@ -859,6 +860,7 @@ void build_mesh(MeshH& M, const mlvs_mesh& in, int dim) {
                 const bool isL = (F.L == c) && (k == 1 || k == 3);
                 const double dx = isL ? F.dLx : F.dRx, dy = isL ? F.dLy : F.dRy;
                 cenx[k] = M.xc[c] + dx; ceny[k] = M.yc[c] + dy;
+                g.fox[k] = dx; g.foy[k] = dy;
                 have[k] = true;
                 // neighbour offset: x_n - x_c = (x_f - x_c) - (x_f - x_n)
                 const double ox = isL ? (F.dLx - F.dRx) : (F.dRx - F.dLx);
@@ -867,6 +869,7 @@ void build_mesh(MeshH& M, const mlvs_mesh& in, int dim) {
                 g.dist[k] = std::hypot(ox, oy);
             } else if (b >= 0) {
                 cenx[k] = M.bfaces[b].cx; ceny[k] = M.bfaces[b].cy;
+                g.fox[k] = M.bfaces[b].dLx; g.foy[k] = M.bfaces[b].dLy;
                 have[k] = true;
             }
         }
@@ -885,6 +888,24 @@ void build_mesh(MeshH& M, const mlvs_mesh& in, int dim) {
         for (int k = 0; k < 4; ++k)
             if (have[k]) M.hmin = std::min(M.hmin, 2.0 * std::hypot(cenx[k] - M.xc[c], ceny[k] - M.yc[c]));
     }
+}
+
+// Angle of a direction in units of 2^-31 half turns.
+int angle_units(double x, double y) {
+    const double a = std::atan2(y, x) / 3.14159265358979323846 * 2147483648.0;
+    return (int)std::max(-2147483648.0, std::min(2147483647.0, std::nearbyint(a)));
+}
+
+// CellGeom::ang of every mesh: the outward normal of each slot's face.
+void normal_angles(MeshH& M) {
+    for (int c = 0; c < M.n_cells; ++c)
+        for (int k = 0; k < 4; ++k) {
+            const int f = M.face_of_cell[4 * c + k], b = M.bface_of_cell[4 * c + k];
+            if (f < 0 && b < 0) continue;
+            const FaceH& F = f >= 0 ? M.faces[f] : M.bfaces[b];
+            const double s = f >= 0 && !(F.L == c && (M.unstructured || k == 1 || k == 3)) ? -1.0 : 1.0;
+            M.geom[c].ang[k] = angle_units(s * F.nx, s * F.ny);
+        }
 }
 
 // Unstructured mesh (triangles and quadrilaterals).  Slot k of a cell is its
@@ -1074,7 +1095,7 @@ struct mlvs_ctx_s {
     uint8_t* stage_install = nullptr;
     size_t stage_install_cap = 0;
     void* levels_block = nullptr;      // device block with the current levels' geometry
-    double* d_fmom = nullptr;          // [chunks][faces + boundary faces][NFMOM] face moments
+    double* d_fmom = nullptr;          // [chunks][faces + boundary faces][2][NFMOM] face moments
     int chunk = 1024;                  // velocity points per chunk (multiple of 64), set per level set
     int chunk_env = 0;                 // MLVS_CHUNK: a fixed chunk instead of the chosen one
     int nch = 1;                       // chunks of the largest level
@@ -1167,28 +1188,54 @@ namespace {
 
 // (xi_x, xi_y) pairs rounded to float: the FP32 form's reconstruction and
 // phi_bar+ rows read one 8-byte pair per point instead of two doubles.
+// Padded to whole rows of 64 points: lanes read several points at once.
 std::vector<float> xy_pairs(const Level& L) {
-    std::vector<float> v(2 * (size_t)L.N);
+    std::vector<float> v(2 * ((size_t)(L.N + 63) / 64 * 64), 0.0f);
     for (int i = 0; i < L.N; ++i) { v[2 * i] = (float)L.xi_x[i]; v[2 * i + 1] = (float)L.xi_y[i]; }
+    return v;
+}
+
+// First and last angle of every 64 points (LevelDesc::ang); a run that holds
+// the point at rest, which has no angle, gets the whole turn.
+std::vector<int> angle_bounds(const Level& L) {
+    std::vector<int> v(2 * ((size_t)(L.N + 63) / 64));
+    for (int b = 0; b < L.N; b += 64) {
+        const int e = std::min(L.N, b + 64);
+        int lo = angle_units(L.xi_x[b], L.xi_y[b]), hi = angle_units(L.xi_x[e - 1], L.xi_y[e - 1]);
+        for (int i = b; i < e; ++i)
+            if (L.xi_x[i] == 0.0 && L.xi_y[i] == 0.0) { lo = INT_MIN; hi = INT_MAX; }
+        v[2 * (b / 64)] = lo;
+        v[2 * (b / 64) + 1] = hi;
+    }
+    return v;
+}
+
+// Per-point values for the device, zero past the last point up to a whole row
+// of 64 (waves read whole rows).
+std::vector<double> padded(const std::vector<double>& a) {
+    std::vector<double> v(a);
+    v.resize((a.size() + 63) / 64 * 64, 0.0);
     return v;
 }
 
 void upload_level_geometry(mlvs_ctx c, Level& L) {
     L.d_xy = upload(c->dm, xy_pairs(L), c->st);
-    L.d_x = upload(c->dm, L.xi_x, c->st);
-    L.d_y = upload(c->dm, L.xi_y, c->st);
-    L.d_w = upload(c->dm, L.w, c->st);
+    L.d_ang = upload(c->dm, angle_bounds(L), c->st);
+    L.d_x = upload(c->dm, padded(L.xi_x), c->st);
+    L.d_y = upload(c->dm, padded(L.xi_y), c->st);
+    L.d_w = upload(c->dm, padded(L.w), c->st);
     L.d_pt_of_base = upload(c->dm, L.pt_of_base, c->st);
     L.stride = (L.N + 63) / 64 * 64;
 }
 
 void free_level(mlvs_ctx c, Level& L) {
     if (!L.geo_in_arena)
-        for (void* p : {(void*)L.d_x, (void*)L.d_y, (void*)L.d_w, (void*)L.d_xy, (void*)L.d_pt_of_base})
+        for (void* p : {(void*)L.d_x, (void*)L.d_y, (void*)L.d_w, (void*)L.d_xy, (void*)L.d_ang, (void*)L.d_pt_of_base})
             c->dm.release(p);
     for (void* p : {L.g, L.h, L.fg, L.fh, L.Fg, L.Fh}) c->dm.release(p);
     L.d_x = L.d_y = L.d_w = nullptr;
     L.d_xy = nullptr;
+    L.d_ang = nullptr;
     L.d_pt_of_base = nullptr;
     L.g = L.h = L.fg = L.fh = L.Fg = L.Fh = nullptr;
 }
@@ -1329,6 +1376,7 @@ void update_step_args(mlvs_ctx c) {
     A.params = c->d_params;
     A.cmom = c->d_cmom;
     A.fpar = c->d_fpar;
+    A.fmom = c->d_fmom;
     A.neg = c->d_neg;
     A.sync = c->d_sync;
     A.n_ghosts = c->n_ghosts;
@@ -1615,14 +1663,14 @@ void build_items(mlvs_ctx c) {
         L.Fg = c->dm.alloc(nr); L.Fh = c->dm.alloc(nr);
         L.fg = c->dm.alloc(nf); L.fh = c->dm.alloc(nf);
     }
-    struct GeoOff { size_t x, y, w, ptb, xy; };
+    struct GeoOff { size_t x, y, w, ptb, xy, ang; };
     std::vector<GeoOff> igeo;
     for (auto& Lp : c->ifaces) {
         Level& L = *Lp;
         const size_t nr = (size_t)std::max(L.n_rows, 1) * L.stride * c->elt();
         L.Fg = c->dm.alloc(nr); L.Fh = c->dm.alloc(nr);
-        igeo.push_back({stg.put(L.xi_x), stg.put(L.xi_y), stg.put(L.w), stg.put(L.pt_of_base),
-                        stg.put(xy_pairs(L))});
+        igeo.push_back({stg.put(padded(L.xi_x)), stg.put(padded(L.xi_y)), stg.put(padded(L.w)), stg.put(L.pt_of_base),
+                        stg.put(xy_pairs(L)), stg.put(angle_bounds(L))});
     }
     mk.mark("items: row buffers", c->st);
     c->n_faces = n_same;
@@ -1659,6 +1707,7 @@ void build_items(mlvs_ctx c) {
         L.d_w = reinterpret_cast<double*>(base + igeo[i].w);
         L.d_pt_of_base = reinterpret_cast<int*>(base + igeo[i].ptb);
         L.d_xy = reinterpret_cast<float*>(base + igeo[i].xy);
+        L.d_ang = reinterpret_cast<int*>(base + igeo[i].ang);
         L.geo_in_arena = true;
     }
     for (size_t i = 0; i < gitems.size(); ++i) gitems[i].tab = gtab[i].at(base);
@@ -1676,7 +1725,7 @@ void build_items(mlvs_ctx c) {
         Level& L = level_by_index(c, i);
         LevelDesc d{};
         d.N = L.N; d.stride = L.stride; d.n_rows_state = L.n_cells;
-        d.xi_x = L.d_x; d.xi_y = L.d_y; d.w = L.d_w; d.xy32 = L.d_xy;
+        d.xi_x = L.d_x; d.xi_y = L.d_y; d.w = L.d_w; d.xy32 = L.d_xy; d.ang = L.d_ang;
         d.g = L.g; d.h = L.h; d.fg = L.fg; d.fh = L.fh; d.Fg = L.Fg; d.Fh = L.Fh;
         std::copy(L.Minv, L.Minv + 16, d.Minv);
         std::copy(L.G6inv, L.G6inv + 36, d.G6inv);
@@ -1726,7 +1775,7 @@ void build_items(mlvs_ctx c) {
     c->nch = (nmax + c->chunk - 1) / c->chunk;
     c->fused = c->fuse_allowed && c->nch == 1 && nmax <= FUSE_MAX_POINTS;
     c->d_fmom = static_cast<double*>(
-        c->dm.alloc(sizeof(double) * NFMOM * c->nch * (size_t)std::max(nF_all, 1)));
+        c->dm.alloc(sizeof(double) * 2 * NFMOM * c->nch * (size_t)std::max(nF_all, 1)));
     c->item_allocs.push_back(c->d_fmom);
     c->d_cmom = static_cast<double*>(c->dm.alloc(sizeof(double) * NMOM * c->nch * (size_t)std::max(n, 1)));
     c->item_allocs.push_back(c->d_cmom);
@@ -1851,12 +1900,13 @@ int64_t install_levels(mlvs_ctx c, std::vector<std::unique_ptr<Level>> nl, const
     // one staged block: the new levels' geometry (kept with the level set) and
     // the remap's descriptors, tables and work list
     Stage stg(c->stage_install, c->stage_install_cap);
-    struct GeoOff { size_t x, y, w, ptb, xy; };
+    struct GeoOff { size_t x, y, w, ptb, xy, ang; };
     std::vector<GeoOff> geo;
     for (auto& L : c->levels) {
         L->stride = (L->N + 63) / 64 * 64;
-        geo.push_back({stg.put(L->xi_x), stg.put(L->xi_y), stg.put(L->w), stg.put(L->pt_of_base),
-                       stg.put(xy_pairs(*L))});
+        geo.push_back({stg.put(padded(L->xi_x)), stg.put(padded(L->xi_y)), stg.put(padded(L->w)),
+                       stg.put(L->pt_of_base),
+                       stg.put(xy_pairs(*L)), stg.put(angle_bounds(*L))});
         alloc_state(c, *L);
     }
     mk.mark("install: free items, state", c->st);
@@ -1914,6 +1964,7 @@ int64_t install_levels(mlvs_ctx c, std::vector<std::unique_ptr<Level>> nl, const
         L.d_w = reinterpret_cast<double*>(base + geo[l].w);
         L.d_pt_of_base = reinterpret_cast<int*>(base + geo[l].ptb);
         L.d_xy = reinterpret_cast<float*>(base + geo[l].xy);
+        L.d_ang = reinterpret_cast<int*>(base + geo[l].ang);
         L.geo_in_arena = true;
     }
     for (int cc = 0; cc < n; ++cc)
@@ -1925,6 +1976,7 @@ int64_t install_levels(mlvs_ctx c, std::vector<std::unique_ptr<Level>> nl, const
             LevelDesc x{};
             x.N = Lp->N; x.stride = Lp->stride; x.xi_x = Lp->d_x; x.xi_y = Lp->d_y; x.w = Lp->d_w;
             x.xy32 = Lp->d_xy;
+            x.ang = Lp->d_ang;
             x.g = Lp->g; x.h = Lp->h;
             std::copy(Lp->Minv, Lp->Minv + 16, x.Minv);
             std::copy(Lp->G6inv, Lp->G6inv + 36, x.G6inv);
@@ -2811,6 +2863,7 @@ static mlvs_status create_impl(const mlvs_physics* phys, const mlvs_mesh* mesh, 
         if (adapt) c->ap = *adapt;
         if (umesh) build_umesh(c->mesh, *umesh);
         else build_mesh(c->mesh, *mesh, phys->dim);
+        normal_angles(c->mesh);
         if (mesh) {
             // traversal tiles (MLVS_TILE=WxH overrides; 0 = row-major)
             int tw = 16, th = 8;
@@ -3538,8 +3591,14 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
                                     c->d_params, c->d_cmom, c->chunk, c->variant[0]);
     case 1: return launch_ghost(c->prec, c->st, c->d_lv, c->d_ghosts, c->n_ghosts, c->d_cell_lev, c->d_cell_slot,
                                 c->d_params, c->ph, c->d_neg);
-    case 2: return launch_face_rec(c->prec, c->st, c->d_lv, c->d_faces, nf, c->d_cell_slot, c->d_cell_nbr, c->d_geom,
-                                   c->d_params, c->ph, c->d_fmom, c->chunk, c->nch, c->variant[2]);
+    case 2: case 7: {
+        const hipError_t e = launch_face_rec(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_cell_nbr,
+                                             c->d_cell_frow, c->d_order, n, c->d_faces, nf, c->d_geom, c->d_params,
+                                             c->ph, c->d_fmom, c->chunk, c->nch, c->variant[stage]);
+        if (stage == 2 || e != hipSuccess) return e;
+        return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->d_bcs, c->ph, c->d_fmom, c->d_fpar,
+                                  c->chunk, c->variant[7]);
+    }
     case 3: return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->d_bcs, c->ph, c->d_fmom,
                                       c->d_fpar, c->chunk, c->variant[3]);
     case 4: return launch_xface(c->prec, on ? on : c->st, c->d_lv, c->d_xfaces, c->n_xfaces, c->d_cell_slot, c->d_cell_nbr,
@@ -3547,8 +3606,6 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
     case 5: return launch_update(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->d_geom,
                                  c->d_cell_frow, c->d_faces, c->d_fpar, c->d_params, c->ph, c->d_cmom, c->chunk,
                                  c->nch, c->variant[5]);
-    case 7: return launch_face_full(c->prec, c->st, c->d_lv, c->d_faces, nf, c->d_cell_slot, c->d_cell_nbr,
-                                    c->d_geom, c->d_params, c->d_bcs, c->ph, c->d_fpar, c->variant[7]);
     case 9: return launch_step_persistent(c->prec, c->st, c->d_args, c->d_sync, c->ph, c->variant[9],
                                           &c->persistent_grid);
     case 8: return launch_update_cell(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n,

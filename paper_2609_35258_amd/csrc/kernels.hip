@@ -83,6 +83,47 @@ __device__ __forceinline__ void wave_sum(double (&v)[NV]) {
     }
 }
 
+// Swap the upper 32 lanes of a with the lower 32 lanes of b (both 32-bit halves).
+__device__ __forceinline__ void swap32(double& a, double& b) {
+    const long long p = __double_as_longlong(a), q = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)p, (unsigned)q, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(p >> 32), (unsigned)(q >> 32), false, false);
+    a = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0]));
+    b = __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+// Swap the odd rows of 16 lanes of a with the even rows of b.
+__device__ __forceinline__ void swap16(double& a, double& b) {
+    const long long p = __double_as_longlong(a), q = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)p, (unsigned)q, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(p >> 32), (unsigned)(q >> 32), false, false);
+    a = __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0]));
+    b = __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+// Eleven sums over the wavefront (all lanes active) added to tot[0..10] in LDS,
+// in about 65 instructions instead of wave_sum<11>'s 250: two exchanges that
+// each halve the values a lane holds (sums 2t, 2t + 1 go to the lower and upper
+// 32 lanes, then to even and odd rows of 16), and the four DPP steps inside a
+// row for the three registers that are left.  Row r of register t then holds
+// sum 4t + (0, 2, 1, 3)[r].  The wave alone touches tot.
+__device__ __forceinline__ void add_sums11(double (&v)[11], double* tot) {
+    const int r = (threadIdx.x >> 4) & 3, idx = ((r & 1) << 1) | (r >> 1);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        double a0 = v[4 * t], b0 = v[4 * t + 1], a1 = v[4 * t + 2], b1 = t < 2 ? v[4 * t + 3] : 0.0;
+        swap32(a0, b0);
+        swap32(a1, b1);
+        double a = a0 + b0, b = a1 + b1;
+        swap16(a, b);
+        double x = a + b;
+        x += dpp_mov<0xB1>(x);
+        x += dpp_mov<0x4E>(x);
+        x += dpp_mov<0x141>(x);
+        x += dpp_mov<0x140>(x);
+        if ((threadIdx.x & 15) == 0 && 4 * t + idx < 11) tot[4 * t + idx] += x;
+    }
+}
+
 // Maximum of NV doubles over the wavefront (all lanes active), same exchanges.
 template <int NV>
 __device__ __forceinline__ void wave_max(double (&v)[NV]) {
@@ -941,24 +982,24 @@ __global__ __launch_bounds__(BS) void k_ghost(const LevelDesc* __restrict__ lvs,
 // ---------------------------------------------------------------------------
 // same-level faces
 // ---------------------------------------------------------------------------
-// van Leer's limited slope from two one-sided slopes: 2ab/(a+b) where they
-// agree in sign, else 0.  Written without a branch (the division runs on every
-// lane with a safe denominator) so the stencil loads around it stay batched.
+// Half of van Leer's limited slope from two one-sided slopes: ab/(a+b) where
+// they agree in sign, else 0 (the factor 2 is in the geometry it is multiplied
+// by, exactly).  Written without a branch (the division runs on every lane) so
+// the stencil loads around it stay batched.
 __device__ __forceinline__ double vl_div(double n, double d) { return n / d; }
 __device__ __forceinline__ float vl_div(float n, float d) { return n * __builtin_amdgcn_rcpf(d); }
 template <typename C>
 __device__ __forceinline__ C van_leer(C a, C b) {
     const C p = a * b;
-    const bool pos = p > C(0);
-    const C q = vl_div(C(2) * p, pos ? a + b : C(1));
-    return pos ? q : C(0);
+    const C q = vl_div(p, a + b);
+    return p > C(0) ? q : C(0);
 }
 
 template <typename S>
 struct Side {                       // one cell's reconstruction stencil on its level
     gptr<const S> base[2];          // the level's phi_bar+ buffers (g, h)
     size_t off[5];                  // element offsets of the rows: own, W, E, S, N
-    S G[4], id[4];                  // [t_i; t_j]^-1 and 1/|x_n - x_c|
+    S G[4], id[4];                  // 2 [t_i; t_j]^-1 (see van_leer) and 1/|x_n - x_c|
     S dx, dy;                       // x_f - x_cell
 };
 
@@ -981,21 +1022,8 @@ __device__ __forceinline__ void load_side(Side<S>& sd, const LevelDesc& L, int c
     for (int k = 0; k < 4; ++k) sd.off[k + 1] = nb_off(L, cell_nbr[4 * cell + k], cell_slot, own);
     const CellGeom& gm = geom[cell];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) { sd.G[k] = (S)gm.G[k]; sd.id[k] = (S)gm.inv_dist[k]; }
+    for (int k = 0; k < 4; ++k) { sd.G[k] = S(2) * (S)gm.G[k]; sd.id[k] = (S)gm.inv_dist[k]; }
     sd.dx = (S)dx; sd.dy = (S)dy;
-}
-
-// Per-lane choice between two stencils of the same level (branch-free upwind selection).
-template <typename S>
-__device__ __forceinline__ void select_side(Side<S>& o, const Side<S>& a, const Side<S>& b, bool useA) {
-    o.base[0] = a.base[0];
-    o.base[1] = a.base[1];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) o.off[k] = useA ? a.off[k] : b.off[k];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) { o.G[k] = useA ? a.G[k] : b.G[k]; o.id[k] = useA ? a.id[k] : b.id[k]; }
-    o.dx = useA ? a.dx : b.dx;
-    o.dy = useA ? a.dy : b.dy;
 }
 
 // Limited gradient of phi_bar+ at velocity index i: per index direction a van
@@ -1021,8 +1049,8 @@ __device__ __forceinline__ void side_slope(const Side<S>& sd, int i, S (&f)[2], 
 
 // phi_bar+ of the side's cell extrapolated to the face at velocity index i:
 // phi_bar+ + (x_f - x_c - xi s) . sigma.
-template <typename S>
-__device__ __forceinline__ void side_ext(const Side<S>& sd, int i, S x, S y, S s, S& eg, S& eh) {
+template <typename S, typename SD>
+__device__ __forceinline__ void side_ext(const SD& sd, int i, S x, S y, S s, S& eg, S& eh) {
     S f[2], sx[2], sy[2];
     side_slope<S>(sd, i, f, sx, sy);
     const S ax = sd.dx - x * s, ay = sd.dy - y * s;
@@ -1055,43 +1083,6 @@ __device__ __forceinline__ Eq<double> face_target(const LevelDesc& L, double* m,
     return make_eq(rho, u, v, T, qx, qy, compat ? a : nullptr, ph);
 }
 
-// The five stencil values (own, W, E, S, N) of g and h at one velocity index,
-// from side a or b chosen per lane.
-template <typename S>
-struct Stencil { S v[2][5]; };
-
-template <typename S, typename SD>
-__device__ __forceinline__ void load_stencil(const SD& a, const SD& b, bool useA, int i, Stencil<S>& st) {
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-        const auto B = a.base[comp] + i;
-#pragma unroll
-        for (int k = 0; k < 5; ++k) st.v[comp][k] = B[useA ? a.off[k] : b.off[k]];
-    }
-}
-
-// phi_bar+ + (x_f - x_c - xi s) . sigma from a loaded stencil (Eqs.
-// bar_phi_transport, reconstruction): per index direction a van Leer limited
-// pair of one-sided slopes, mapped through [t_i; t_j]^-1.
-template <typename S>
-__device__ __forceinline__ void stencil_ext(const Side<S>& a, const Side<S>& b, bool useA, const Stencil<S>& st,
-                                            S x, S y, S s, S& eg, S& eh) {
-    S G[4], id[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) { G[k] = useA ? a.G[k] : b.G[k]; id[k] = useA ? a.id[k] : b.id[k]; }
-    const S ax = (useA ? a.dx : b.dx) - x * s, ay = (useA ? a.dy : b.dy) - y * s;
-    S e[2];
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-        const S fv = st.v[comp][0];
-        const S s0 = van_leer<S>((fv - st.v[comp][1]) * id[0], (st.v[comp][2] - fv) * id[1]);
-        const S s1 = van_leer<S>((fv - st.v[comp][3]) * id[2], (st.v[comp][4] - fv) * id[3]);
-        e[comp] = fv + ax * (G[0] * s0 + G[1] * s1) + ay * (G[2] * s0 + G[3] * s1);
-    }
-    eg = e[0];
-    eh = e[1];
-}
-
 // Face state from the raw moments of phi_bar_f (Eq. W_from_bar): W_f, tau_f,
 // q_f = 2 tau_f q_bar/(2 tau_f + s Pr) and the recovery weights c1 = 2 tau_f /
 // (2 tau_f + s), c2 = s/(2 tau_f + s) of Eq. recover_phi (one lane per face).
@@ -1110,32 +1101,6 @@ __device__ __forceinline__ FaceState face_state(const double* mm, double u0, dou
     f.c1 = 2.0 * tau / (2.0 * tau + s);
     f.c2 = s / (2.0 * tau + s);
     return f;
-}
-
-// The same with one side for the whole wavefront (no per-lane choice).
-template <typename S, typename SD>
-__device__ __forceinline__ void load_stencil1(const SD& a, int i, Stencil<S>& st) {
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-        const auto B = a.base[comp] + i;
-#pragma unroll
-        for (int k = 0; k < 5; ++k) st.v[comp][k] = B[a.off[k]];
-    }
-}
-
-template <typename S>
-__device__ __forceinline__ void stencil_ext1(const Side<S>& a, const Stencil<S>& st, S x, S y, S s, S& eg, S& eh) {
-    const S ax = a.dx - x * s, ay = a.dy - y * s;
-    S e[2];
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-        const S fv = st.v[comp][0];
-        const S s0 = van_leer<S>((fv - st.v[comp][1]) * a.id[0], (st.v[comp][2] - fv) * a.id[1]);
-        const S s1 = van_leer<S>((fv - st.v[comp][3]) * a.id[2], (st.v[comp][4] - fv) * a.id[3]);
-        e[comp] = fv + ax * (a.G[0] * s0 + a.G[1] * s1) + ay * (a.G[2] * s0 + a.G[3] * s1);
-    }
-    eg = e[0];
-    eh = e[1];
 }
 
 // ---------------------------------------------------------------------------
@@ -1225,165 +1190,429 @@ __device__ __forceinline__ void side_slope(const USide<S>& sd, int i, S (&f)[2],
     }
 }
 
-template <typename S>
-__device__ __forceinline__ void stencil_ext(const USide<S>& a, const USide<S>& b, bool useA, const Stencil<S>& st,
-                                            S x, S y, S s, S& eg, S& eh) {
-    S lx[4], ly[4], fx[4], fy[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        lx[k] = useA ? a.lx[k] : b.lx[k]; ly[k] = useA ? a.ly[k] : b.ly[k];
-        fx[k] = useA ? a.fx[k] : b.fx[k]; fy[k] = useA ? a.fy[k] : b.fy[k];
-    }
-    const S eps2 = useA ? a.eps2 : b.eps2;
-    const S ax = (useA ? a.dx : b.dx) - x * s, ay = (useA ? a.dy : b.dy) - y * s;
-    S e[2];
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-        S sx, sy;
-        venkat_slope<S>(lx, ly, fx, fy, eps2, st.v[comp], sx, sy);
-        e[comp] = st.v[comp][0] + ax * sx + ay * sy;
-    }
-    eg = e[0];
-    eh = e[1];
-}
-
-template <typename S>
-__device__ __forceinline__ void stencil_ext1(const USide<S>& a, const Stencil<S>& st, S x, S y, S s, S& eg, S& eh) {
-    const S ax = a.dx - x * s, ay = a.dy - y * s;
-    S e[2];
-#pragma unroll
-    for (int comp = 0; comp < 2; ++comp) {
-        S sx, sy;
-        venkat_slope<S>(a.lx, a.ly, a.fx, a.fy, a.eps2, st.v[comp], sx, sy);
-        e[comp] = st.v[comp][0] + ax * sx + ay * sy;
-    }
-    eg = e[0];
-    eh = e[1];
-}
-
 // The side type of a mesh kind (0 structured, 1 unstructured).
 template <typename S, int MK>
 using SideOf = typename std::conditional<MK == 1, USide<S>, Side<S>>::type;
 
-// Face stage, part 1 (reconstruction): for every same-level interior face and
-// every boundary face, the interface value phi_bar_f = phi_bar+_up + (x_f -
-// x_up - xi s) . sigma_up (both sides averaged where xi . n = 0) is written to
-// the face row.  Interior faces also reduce the eleven raw moments of phi_bar_f
-// (about the mean of the two cell velocities); boundary faces reduce the
-// outgoing mass flux.  Per-face results go to fmom[item][NFMOM] (the moments,
-// then the velocity shift they are taken about).
-template <typename S, int U, int MK>
-__device__ __forceinline__ void face_rec_points(const LevelDesc& L, const FaceItem& F, const int* cell_slot,
-                                                const int* cell_nbr, const CellGeom* geom, const double* params,
-                                                const Phys& ph, int beg, int N, double (&m)[11], double& u0,
-                                                double& v0) {
-    const S s = (S)(0.5 * ph.dt);
-    auto rg = rowp<S>(L.Fg, (size_t)F.row * L.stride);
-    auto rh = rowp<S>(L.Fh, (size_t)F.row * L.stride);
-    SideOf<S, MK> sL;
-    load_side<S>(sL, L, F.L, cell_slot, cell_nbr, geom, F.dLx, F.dLy);
-    const bool interior = F.R >= 0;
-    SideOf<S, MK> sR = sL;
-    u0 = 0.0;
-    v0 = 0.0;
-    if (interior) {
-        load_side<S>(sR, L, F.R, cell_slot, cell_nbr, geom, F.dRx, F.dRy);
-        u0 = 0.5 * (params[(size_t)F.L * NPARAM + P_U] + params[(size_t)F.R * NPARAM + P_U]);
-        v0 = 0.5 * (params[(size_t)F.L * NPARAM + P_V] + params[(size_t)F.R * NPARAM + P_V]);
-    }
+// Limited gradient of phi_bar+ from loaded stencil values (own, W, E, S, N).
+template <typename S>
+__device__ __forceinline__ void stencil_slope(const Side<S>& a, const S (&v)[5], S& sx, S& sy) {
+    const S s0 = van_leer<S>((v[0] - v[1]) * a.id[0], (v[2] - v[0]) * a.id[1]);
+    const S s1 = van_leer<S>((v[0] - v[3]) * a.id[2], (v[4] - v[0]) * a.id[3]);
+    sx = a.G[0] * s0 + a.G[1] * s1;
+    sy = a.G[2] * s0 + a.G[3] * s1;
+}
+template <typename S>
+__device__ __forceinline__ void stencil_slope(const USide<S>& a, const S (&v)[5], S& sx, S& sy) {
+    venkat_slope<S>(a.lx, a.ly, a.fx, a.fy, a.eps2, v, sx, sy);
+}
+
+// Values a lane holds of one row: consecutive points, one 8-byte access.
+template <typename S>
+constexpr int VW = 8 / (int)sizeof(S);
+template <typename T, int N>
+using vec = T __attribute__((ext_vector_type(N)));
+
+// N consecutive values at element i (a multiple of N) of a row whose address
+// is uniform: scalar base and one 32-bit byte offset per lane, shared by all
+// rows read at that index.
+template <int N, typename T>
+__device__ __forceinline__ vec<T, N> ldv(gptr<const T> row, int i) {
+    return *(gptr<const vec<T, N>>)((gptr<const char>)row + (unsigned)i * (unsigned)sizeof(T));
+}
+template <int N, typename T>
+__device__ __forceinline__ void stv(gptr<T> row, int i, vec<T, N> x) {
+    __builtin_nontemporal_store(x, (gptr<vec<T, N>>)((gptr<char>)row + (unsigned)i * (unsigned)sizeof(T)));
+}
+
+// Face stage, part 1 (reconstruction): the interface values phi_bar_f =
+// phi_bar+_up + (x_f - x_up - xi s) . sigma_up of the same-level and boundary
+// faces (both sides averaged where xi . n = 0), and the eleven raw moments of
+// phi_bar_f.
+//
+// One wave per (velocity chunk, cell).  At every velocity the cell is upwind
+// of the faces it flows out through, about two of its four, so its limited
+// gradient is formed once per velocity and serves them all; a wave per face
+// forms it once per face, twice the stencil loads and limiters.  Each cell
+// writes the outgoing half of its faces' rows (the neighbour writes the other
+// half) and reduces that half's moments about its own velocity; the target
+// stage shifts and adds the two halves.  Two sets of sums serve the four slots
+// of a structured cell: opposite faces take turns, and a set is flushed to LDS
+// when its pair changes over (five times per row of points sorted by angle),
+// which frees 44 registers for loads in flight.  On unstructured meshes the
+// slots of a set would change over at every chunk of an overlap, so each has
+// its own.  Where xi . n = 0 the flux is zero
+// whatever the row holds: the left cell writes it, and each side adds half its
+// value to its sums.  Points are stored by velocity angle, so a wave's points
+// nearly always all leave or all enter through a face and the face is skipped
+// whole.  Boundary faces: outgoing rows and moments, with double velocities as
+// in the update, so that a diffuse wall's zero net mass flux holds there for
+// either storage precision.
+//
+// The batch after the one in work is on its way to LDS (loads that pass by the
+// registers): a wave's ten stencil rows, velocities and weights take 7 KB, and
+// no register is held for them (loads two batches ahead into registers: 2.85 ms
+// on the cylinder below).
+//
+// Bound by memory traffic with half of the vector issue slots taken.  Time with
+// one wave per face, and so: cylinder 256 x 128, 101^2, FP32 4.02 -> 2.53 ms
+// (4 TB/s); the same with merged levels .64 -> .48; jet 512 x 256 with merged
+// levels, FP32 1.11 -> .73; two-cavity triangles (9504 cells, 101^2) 1.25 ->
+// .97 ms.
+constexpr int REC_ROWS = 14;           // 512-byte pieces of a batch: stencil rows, velocities, weights
+
+// Batch b0 (64 V points) to the wave's LDS area `to`: lanes 0..31 fetch one
+// piece, lanes 32..63 the next, 16 bytes each.  Rows and tables are whole
+// multiples of 64 points long; lanes past that read the last 16 bytes.
+template <typename S>
+__device__ __forceinline__ void rec_fetch(gptr<const char> (&src)[REC_ROWS / 2], int b0, int stride, char* to) {
+    const int in = (lane_id() & 31) * 16;
+    const unsigned off = min(b0 * (int)sizeof(S) + in, stride * (int)sizeof(S) - 16);
 #pragma unroll
-    for (int k = 0; k < 11; ++k) m[k] = 0.0;
-    for (int i0 = beg + lane_id(); i0 < N; i0 += WL * U) {
-        double xv[U], yv[U], wv[U];
-        bool up[U];
-        // points are stored by velocity angle, so a chunk almost always has
-        // one upwind side for the whole wavefront: then that side's stencil
-        // is used with scalar offsets and coefficients
-        bool allL = true, allR = true;
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int i = i0 + q * WL, ic = clampi(i, N);
-            load_xy<S>(L, ic, xv[q], yv[q]);
-            wv[q] = i < N ? gp(L.w)[ic] : 0.0;
-            const double dn = xv[q] * F.nx + yv[q] * F.ny;
-            up[q] = dn >= 0.0;
-            allL = allL && (i >= N || dn > 0.0);
-            allR = allR && (i >= N || dn < 0.0);
-        }
-        const int side = !interior ? 0 : (__all(allL) ? 0 : (__all(allR) ? 1 : 2));
-        S eg[U], eh[U];
-        if (side < 2) {
-            const SideOf<S, MK>& sd = side == 0 ? sL : sR;
-            Stencil<S> st[U];
-#pragma unroll
-            for (int q = 0; q < U; ++q) load_stencil1<S>(sd, clampi(i0 + q * WL, N), st[q]);
-#pragma unroll
-            for (int q = 0; q < U; ++q) stencil_ext1<S>(sd, st[q], (S)xv[q], (S)yv[q], s, eg[q], eh[q]);
-        } else {
-            Stencil<S> st[U];
-#pragma unroll
-            for (int q = 0; q < U; ++q) load_stencil<S>(sL, sR, up[q], clampi(i0 + q * WL, N), st[q]);
-#pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const int ic = clampi(i0 + q * WL, N);
-                const S x = (S)xv[q], y = (S)yv[q];
-                stencil_ext<S>(sL, sR, up[q], st[q], x, y, s, eg[q], eh[q]);
-                const double dn = xv[q] * F.nx + yv[q] * F.ny;
-                if (dn == 0.0) {                    // both sides, averaged
-                    Stencil<S> sb;
-                    load_stencil<S>(sL, sR, false, ic, sb);
-                    S bg, bh;
-                    stencil_ext<S>(sL, sR, false, sb, x, y, s, bg, bh);
-                    eg[q] = S(0.5) * (eg[q] + bg);
-                    eh[q] = S(0.5) * (eh[q] + bh);
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int i = i0 + q * WL;
-            if (i < N) { rg[i] = eg[q]; rh[i] = eh[q]; }
-            if (interior) {
-                acc_raw<S>(m, wv[q], xv[q] - u0, yv[q] - v0, eg[q], eh[q]);
-            } else {
-                // the outgoing mass flux in the update's own arithmetic (double
-                // velocities), so that a diffuse wall's zero net mass flux holds
-                // in the update for either storage precision
-                const int ic = clampi(i0 + q * WL, N);
-                const double dn = gp(L.xi_x)[ic] * F.nx + gp(L.xi_y)[ic] * F.ny;
-                if (dn > 0) m[0] += wv[q] * dn * (double)eg[q];
-            }
-        }
+    for (int t = 0; t < REC_ROWS / 2; ++t) {
+        unsigned o = off;
+        if (VW<S> == 2 && t >= 5) o = min(b0 * 8 + lane_id() * 16, stride * 8 - 16);   // 8 bytes per point
+        __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) void*)(src[t] + o),
+                                         (__attribute__((address_space(3))) void*)(to + 1024 * t), 16, 0, 0);
     }
 }
 
-template <typename S, int U, int MINW, int MK>
+// Read-only tables by uniform index: scalar loads, also past a wait whose asm
+// names memory.
+template <typename T>
+using cptr = __attribute__((address_space(4))) const T*;
+template <typename T>
+__device__ __forceinline__ cptr<T> cp(const T* p) { return (cptr<T>)(unsigned long long)p; }
+
+// What reconstruction and sums need of a cell's face slot (uniform).
+template <typename S>
+struct Slot {
+    int code;                          // cell_frow code, -1: nothing to do here
+    int ang;                           // outward normal's angle
+    bool bnd;                          // boundary face
+    S dx, dy;                          // x_f - x_c
+    gptr<S> rg, rh;                    // face rows
+};
+
+template <typename S, int MK>
+__device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const SideOf<S, MK>& sd,
+                                                const int* cell_frow, const FaceItem* items, const CellGeom& gm,
+                                                const Phys& ph, int beg, int end, double u0, double v0,
+                                                double (*tot)[12], char* lds) {
+    // NS sets of sums; set n serves the PER slots PER n ..
+    constexpr int V = VW<S>, NS = MK == 1 ? 4 : 2, PER = 4 / NS;
+    const S s = uni((S)(0.5 * ph.dt));
+    const int stride = L.stride;
+    gptr<const char> src[REC_ROWS / 2];
+    {
+        const bool hi = lane_id() >= 32;
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            const auto lo = (gptr<const char>)(sd.base[2 * t / 5] + sd.off[2 * t % 5]);
+            const auto up = (gptr<const char>)(sd.base[(2 * t + 1) / 5] + sd.off[(2 * t + 1) % 5]);
+            src[t] = hi ? up : lo;
+        }
+        if constexpr (V == 2) src[5] = (gptr<const char>)gp(L.xy32);
+        else src[5] = hi ? (gptr<const char>)gp(L.xi_y) : (gptr<const char>)gp(L.xi_x);
+        src[6] = (gptr<const char>)gp(L.w);
+    }
+    rec_fetch<S>(src, beg, stride, lds);
+    Slot<S> slot[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int cd = cell_frow[4 * c + k];
+        slot[k].code = cd >= 0 && !(cd & 2) ? cd : -1;
+        slot[k].ang = gm.ang[k];
+        slot[k].bnd = slot[k].code >= 0 && items[cd >> 2].R < 0;
+        slot[k].dx = uni((S)gm.fox[k]);
+        slot[k].dy = uni((S)gm.foy[k]);
+        const size_t row = (size_t)(slot[k].code >= 0 ? items[cd >> 2].row : 0) * stride;
+        slot[k].rg = rowp<S>(L.Fg, row);
+        slot[k].rh = rowp<S>(L.Fh, row);
+    }
+    double acc[NS][11];
+    int own[NS];                       // the slot whose sums set n holds
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+        own[n] = n * PER;
+#pragma unroll
+        for (int j = 0; j < 11; ++j) acc[n][j] = 0.0;
+    }
+    unsigned long long fast[NS], far[NS], slow[NS];
+    int stores = 0;                    // store instructions since the last fetch (-1: not counted)
+    for (int b0 = beg; b0 < end; b0 += WL * V) {
+        const int i = b0 + V * lane_id();
+        // Which slots the batches are upwind of, 64 batches at a time, a lane each:
+        // from the angles of a batch's points, a face whose normal is well within
+        // (outside) a quarter turn of all of them is left (entered) by all.  Per
+        // set: batches where one slot alone is left, by all points of a whole batch
+        // (fast, `far` naming the last slot), and batches that take a look at every
+        // point (slow: also boundary faces).
+        const int nb = (b0 - beg) / (WL * V) & 63;
+        if (nb == 0) {
+            const int lb = b0 + WL * V * lane_id(), le = min(end, lb + WL * V);
+            const bool on = lb < end;
+            const int a0 = gp(L.ang)[on ? 2 * (lb / WL) : 0], a1 = gp(L.ang)[on ? 2 * ((le - 1) / WL) + 1 : 0];
+            const unsigned span = (unsigned)(a1 - a0);
+            constexpr unsigned W = 2u * (ANG_QUARTER - ANG_MARGIN);
+#pragma unroll
+            for (int n = 0; n < NS; ++n) {
+                bool easy[2] = {false, false}, any[2] = {false, false};
+#pragma unroll
+                for (int m = 0; m < PER; ++m) {
+                    const Slot<S>& sl = slot[PER * n + m];
+                    const unsigned t = (unsigned)(a0 - sl.ang) + W / 2;
+                    any[m] = on && sl.code >= 0 && !(span <= W && t + 0x80000000u <= W - span);
+                    easy[m] = any[m] && !sl.bnd && lb + WL * V <= end && span <= W && t <= W - span;
+                }
+                fast[n] = __ballot((easy[0] && !any[1]) || (easy[1] && !any[0]));
+                far[n] = __ballot(any[1]);
+                slow[n] = __ballot(any[0] || any[1]) & ~fast[n];
+            }
+        }
+        // the fetch is done when only the stores after it are left
+        if (stores == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        vec<S, V> st[2][5];
+#pragma unroll
+        for (int r = 0; r < 10; ++r) st[r / 5][r % 5] = *(const vec<S, V>*)(lds + 512 * r + 8 * lane_id());
+        S xs[V], ys[V];
+        vec<double, V> wv;
+        if constexpr (V == 2) {
+            const vec<float, 4> xy = *(const vec<float, 4>*)(lds + 512 * 10 + 16 * lane_id());
+            xs[0] = xy[0]; ys[0] = xy[1]; xs[1] = xy[2]; ys[1] = xy[3];
+            wv = *(const vec<double, V>*)(lds + 512 * 12 + 16 * lane_id());
+        } else {
+            xs[0] = *(const S*)(lds + 512 * 10 + 8 * lane_id());
+            ys[0] = *(const S*)(lds + 512 * 11 + 8 * lane_id());
+            wv = *(const vec<double, V>*)(lds + 512 * 12 + 8 * lane_id());
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the area is read: the next batch may come
+        if (b0 + WL * V < end) rec_fetch<S>(src, b0 + WL * V, stride, lds);
+        asm volatile("" ::: "memory");
+        stores = 0;
+        S f[V][2], sx[V][2], sy[V][2];
+#pragma unroll
+        for (int p = 0; p < V; ++p)
+#pragma unroll
+            for (int comp = 0; comp < 2; ++comp) {
+                S v[5];
+#pragma unroll
+                for (int k = 0; k < 5; ++k) v[k] = st[comp][k][p];
+                f[p][comp] = v[0];
+                stencil_slope<S>(sd, v, sx[p][comp], sy[p][comp]);
+            }
+        auto reach = [&](const Slot<S>& sl, vec<S, V> (&r)[2]) {
+#pragma unroll
+            for (int p = 0; p < V; ++p) {
+                const S ax = sl.dx - xs[p] * s, ay = sl.dy - ys[p] * s;
+#pragma unroll
+                for (int comp = 0; comp < 2; ++comp) r[comp][p] = f[p][comp] + ax * sx[p][comp] + ay * sy[p][comp];
+            }
+        };
+        vec<S, V> e[NS][2];
+        bool act[NS];
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+            act[n] = false;
+            e[n][0] = e[n][1] = vec<S, V>(S(0));
+            if (fast[n] >> nb & 1) {
+                const int s1 = PER > 1 ? (int)(far[n] >> nb & 1) : 0;
+                const Slot<S>& sl = PER > 1 && s1 ? slot[PER * n + PER - 1] : slot[PER * n];
+                // one slot, left by all points of the batch
+                const int k = PER * n + s1 * (PER - 1);
+                reach(sl, e[n]);
+                stv<V>(sl.rg, i, e[n][0]);
+                stv<V>(sl.rh, i, e[n][1]);
+                if (stores >= 0) stores += 2;
+                act[n] = true;
+                if (own[n] != k) {
+                    add_sums11(acc[n], tot[own[n]]);
+                    own[n] = k;
+#pragma unroll
+                    for (int j = 0; j < 11; ++j) acc[n][j] = 0.0;
+                }
+                continue;
+            }
+            if (!(slow[n] >> nb & 1)) continue;
+            stores = -1;
+#pragma unroll 1
+            for (int m = 0; m < PER; ++m) {
+                const int k = PER * n + m;
+                const Slot<S>& q = PER > 1 && m ? slot[PER * n + PER - 1] : slot[PER * n];
+                if (q.code < 0) continue;
+                const auto F = cp(items) + (q.code >> 2);
+                const bool right = q.code & 1, bf = q.bnd;
+                const double nx = right ? -F->nx : F->nx, ny = right ? -F->ny : F->ny;
+                double xd[V], yd[V];
+                bool out[V], store[V], any = false;
+                S half[V];             // 1/2 where xi . n = 0: each side adds half its value
+#pragma unroll
+                for (int p = 0; p < V; ++p) {
+                    xd[p] = (double)xs[p];
+                    yd[p] = (double)ys[p];
+                    if (V == 2 && bf) {
+                        const int id = min(i + p, end - 1);
+                        xd[p] = gp(L.xi_x)[id];
+                        yd[p] = gp(L.xi_y)[id];
+                    }
+                    const double dn = xd[p] * nx + yd[p] * ny;
+                    out[p] = i + p < end && dn >= 0.0;
+                    store[p] = out[p] && !(right && dn == 0.0);
+                    half[p] = dn == 0.0 ? S(0.5) : S(1);
+                    any = any || out[p];
+                }
+                if (!__any(any)) continue;
+                vec<S, V> r[2];
+                reach(q, r);
+#pragma unroll
+                for (int p = 0; p < V; ++p) {
+                    if (store[p]) {
+                        q.rg[(unsigned)(i + p)] = r[0][p];
+                        q.rh[(unsigned)(i + p)] = r[1][p];
+                    }
+                    r[0][p] = out[p] ? half[p] * r[0][p] : S(0);
+                    r[1][p] = out[p] ? half[p] * r[1][p] : S(0);
+                }
+                // the second slot of a set in one batch, or a boundary face (double
+                // velocities) cannot wait for the set: its sums go to LDS at once
+                const bool now = (V == 2 && bf) || act[n];
+                if (now || own[n] != k) {
+                    add_sums11(acc[n], tot[own[n]]);
+#pragma unroll
+                    for (int j = 0; j < 11; ++j) acc[n][j] = 0.0;
+                    if (now) {
+#pragma unroll
+                        for (int p = 0; p < V; ++p)
+                            acc_raw<S>(acc[n], wv[p], xd[p] - u0, yd[p] - v0, r[0][p], r[1][p]);
+                        add_sums11(acc[n], tot[k]);
+#pragma unroll
+                        for (int j = 0; j < 11; ++j) acc[n][j] = 0.0;
+                        continue;
+                    }
+                    own[n] = k;
+                }
+                act[n] = true;
+                e[n][0] = r[0];
+                e[n][1] = r[1];
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < V; ++p) {
+            const double w = wv[p], x = (double)xs[p] - u0, y = (double)ys[p] - v0;
+            const double x2 = x * x + y * y;
+            const double wx = w * x, wy = w * y, wxx = wx * x, wxy = wx * y, wyy = wy * y, wx2 = wx * x2,
+                         wy2 = wy * x2;
+#pragma unroll
+            for (int n = 0; n < NS; ++n)
+                if (act[n]) {
+                    double (&m)[11] = acc[n];
+                    const double g = (double)e[n][0][p], h = (double)e[n][1][p];
+                    m[0] += w * g; m[1] += wx * g; m[2] += wy * g; m[3] += wxx * g; m[4] += wxy * g;
+                    m[5] += wyy * g; m[6] += wx2 * g; m[7] += wy2 * g;
+                    m[8] += w * h; m[9] += wx * h; m[10] += wy * h;
+                }
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NS; ++n) add_sums11(acc[n], tot[own[n]]);
+}
+
+// Pairs (velocity chunk, cell) [first, n) with stride `stride`: the loop of the
+// kernel below, and one stage of the persistent step.
+template <typename S, int MK>
+__device__ __forceinline__ void cell_rec_items(const LevelDesc* __restrict__ lvs, const int* __restrict__ cell_lev,
+                                               const int* __restrict__ cell_slot, const int* __restrict__ cell_nbr,
+                                               const int* __restrict__ cell_frow, const int* __restrict__ order,
+                                               int n_cells, const FaceItem* __restrict__ items, int nF,
+                                               const CellGeom* __restrict__ geom, const double* __restrict__ params,
+                                               Phys ph, double* __restrict__ fmom, int CH, int nch, int first,
+                                               int stride) {
+    __shared__ double sh_tot[MAXW][4][12];         // the slots' sums, a wave each
+    __shared__ __attribute__((aligned(16))) char sh_in[MAXW][REC_ROWS * 512];
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    double (*tot)[12] = sh_tot[w];
+    const int r = lane_id() >> 4, j = lane_id() & 15;
+    const int n = n_cells * nch;
+    for (int it = first; it < n; it += stride) {
+        const int kc = it / n_cells, c = order[it - kc * n_cells];
+        const LevelDesc& L = lvs[cell_lev[c]];
+        const int beg = kc * CH;
+        if (beg >= L.N) continue;
+        const int end = min(L.N, beg + CH);
+        const double u0 = params[(size_t)c * NPARAM + P_U], v0 = params[(size_t)c * NPARAM + P_V];
+        SideOf<S, MK> sd;
+        load_side<S>(sd, L, c, cell_slot, cell_nbr, geom, 0.0, 0.0);
+        if (j < 11) tot[r][j] = 0.0;
+        cell_rec_points<S, MK>(L, c, sd, cell_frow, items, geom[c], ph, beg, end, u0, v0, tot, sh_in[w]);
+        // lane 16 r + j writes moment j of slot r
+        const int cd = cell_frow[4 * c + r];
+        const double val = j == M_U0 ? u0 : j == M_V0 ? v0 : tot[r][j < 11 ? j : 0];
+        if (cd >= 0 && !(cd & 2) && j <= M_V0) fmom[(((size_t)kc * nF + (cd >> 2)) * 2 + (cd & 1)) * NFMOM + j] = val;
+    }
+}
+
+template <typename S, int MINW, int MK>
 __global__ __launch_bounds__(BS, MINW) void k_face_rec(const LevelDesc* __restrict__ lvs,
-                                                       const FaceItem* __restrict__ items, int nF,
+                                                       const int* __restrict__ cell_lev,
                                                        const int* __restrict__ cell_slot,
                                                        const int* __restrict__ cell_nbr,
+                                                       const int* __restrict__ cell_frow,
+                                                       const int* __restrict__ order, int n_cells,
+                                                       const FaceItem* __restrict__ items, int nF,
                                                        const CellGeom* __restrict__ geom,
                                                        const double* __restrict__ params, Phys ph,
                                                        double* __restrict__ fmom, int CH, int nch) {
-    const int n = nF * nch;
-    for (int it = item0(); it < n; it += istride()) {
-        const int kc = it / nF, f = it - kc * nF;
-        const FaceItem F = items[f];
-        const LevelDesc& L = lvs[F.lev];
-        const int beg = kc * CH;
-        if (beg >= L.N) continue;
-        const int N = min(L.N, beg + CH);      // end of this chunk
-        double m[11], u0, v0;
-        face_rec_points<S, U, MK>(L, F, cell_slot, cell_nbr, geom, params, ph, beg, N, m, u0, v0);
-        double* out = fmom + (size_t)it * NFMOM;
-        wave_sum<11>(m);
-        if (lane_id() < 11) {
-#pragma unroll
-            for (int k = 0; k < 11; ++k)
-                if (lane_id() == k) out[k] = m[k];
+    cell_rec_items<S, MK>(lvs, cell_lev, cell_slot, cell_nbr, cell_frow, order, n_cells, items, nF, geom, params, ph,
+                          fmom, CH, nch, item0(), istride());
+}
+
+// Raw moments of phi_bar_f of one face from its two halves (chunk partials
+// added in chunk order), each shifted from its cell's velocity to the mean
+// (M_U0, M_V0) of the two: with d the old shift minus the new one,
+// sum w (x + d)^k .. expands in the sums about the old shift.  Boundary faces:
+// out[0] the outgoing mass flux.
+__device__ __forceinline__ void face_moments(const double* fmom, int f, int nF, const FaceItem& F, int N, int CH,
+                                             double* out) {
+    const bool interior = F.R >= 0;
+    const int nch = (N + CH - 1) / CH;
+    double half[2][13];
+    for (int sd = 0; sd < (interior ? 2 : 1); ++sd) {
+        for (int j = 0; j < 13; ++j) half[sd][j] = 0.0;
+        for (int k = 0; k < nch; ++k) {
+            const double* q = fmom + (((size_t)k * nF + f) * 2 + sd) * NFMOM;
+            for (int j = 0; j < 11; ++j) half[sd][j] += q[j];
         }
-        if (lane_id() == 0) { out[11] = u0; out[12] = v0; }
+        const double* q = fmom + ((size_t)f * 2 + sd) * NFMOM;
+        half[sd][M_U0] = q[M_U0];
+        half[sd][M_V0] = q[M_V0];
     }
+    for (int j = 0; j < 11; ++j) out[j] = 0.0;
+    if (!interior) {
+        const double* m = half[0];
+        out[0] = F.nx * (m[1] + m[M_U0] * m[0]) + F.ny * (m[2] + m[M_V0] * m[0]);
+        out[M_U0] = out[M_V0] = 0.0;
+        return;
+    }
+    const double u0 = 0.5 * (half[0][M_U0] + half[1][M_U0]), v0 = 0.5 * (half[0][M_V0] + half[1][M_V0]);
+    for (int sd = 0; sd < 2; ++sd) {
+        const double* m = half[sd];
+        const double a = m[M_U0] - u0, b = m[M_V0] - v0, d2 = a * a + b * b, tr = m[3] + m[5];
+        const double am = a * m[1] + b * m[2];
+        out[0] += m[0];
+        out[1] += m[1] + a * m[0];
+        out[2] += m[2] + b * m[0];
+        out[3] += m[3] + 2.0 * a * m[1] + a * a * m[0];
+        out[4] += m[4] + a * m[2] + b * m[1] + a * b * m[0];
+        out[5] += m[5] + 2.0 * b * m[2] + b * b * m[0];
+        out[6] += m[6] + 2.0 * (a * m[3] + b * m[4]) + d2 * m[1] + a * (tr + 2.0 * am + d2 * m[0]);
+        out[7] += m[7] + 2.0 * (a * m[4] + b * m[5]) + d2 * m[2] + b * (tr + 2.0 * am + d2 * m[0]);
+        out[8] += m[8];
+        out[9] += m[9] + a * m[8];
+        out[10] += m[10] + b * m[8];
+    }
+    out[M_U0] = u0;
+    out[M_V0] = v0;
 }
 
 // Face stage, part 2 (target), staged as the cell stage, for the same faces:
@@ -1455,7 +1684,7 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
         if (t < GW && g0 + t < n) {
             const FaceItem F = items[g0 + t];
             double mm[NFMOM];
-            sum_chunks(fmom, g0 + t, n, lvs[F.lev].N, CH, mm);
+            face_moments(fmom, g0 + t, n, F, lvs[F.lev].N, CH, mm);
             sh_m[t][0] = mm[0];                       // boundary: the outgoing mass flux
             if (F.R >= 0) {
                 const FaceState fs = face_state(mm, mm[11], mm[12], ph);
@@ -1529,28 +1758,24 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
     }
 }
 
-// Reconstruction and target of one face in one wave: all of the face's points
-// in one pass, then the face state, the corrected target and the record from
-// the wave's own sums (every lane holds them; lane 0 writes).  The form for
-// level sets whose levels fit one velocity chunk, where the reconstruction has
-// no chunk partials to add and the staged target's per-workgroup hand-overs
-// would dominate.  Same arithmetic as k_face_rec + k_face_target.
-template <typename S, int U, int CM, int MK>
-__device__ __forceinline__ void face_full_items(const LevelDesc* __restrict__ lvs, const FaceItem* __restrict__ items,
-                                                int nF, const int* __restrict__ cell_slot,
-                                                const int* __restrict__ cell_nbr, const CellGeom* __restrict__ geom,
-                                                const double* __restrict__ params, const BCDev* __restrict__ bcs,
-                                                Phys ph, double* __restrict__ fpar, int first, int stride) {
+// The target of one face in one wave (every lane holds the sums; lane 0
+// writes the record): a stage of the persistent step.  Same arithmetic as
+// k_face_target.
+template <typename S, int U, int CM>
+__device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ lvs,
+                                                  const FaceItem* __restrict__ items, int nF,
+                                                  const BCDev* __restrict__ bcs, Phys ph,
+                                                  const double* __restrict__ fmom, double* __restrict__ fpar,
+                                                  int first, int stride) {
     for (int f = first; f < nF; f += stride) {
         const FaceItem F = items[f];
         const LevelDesc& L = lvs[F.lev];
-        double m[11], u0, v0;
-        face_rec_points<S, U, MK>(L, F, cell_slot, cell_nbr, geom, params, ph, 0, L.N, m, u0, v0);
-        wave_sum<11>(m);
+        double m[NFMOM];
+        face_moments(fmom, f, nF, F, L.N, L.N, m);
         double kind = 0.0, c1, c2;
         Eq<double> e;
         if (F.R >= 0) {
-            const FaceState fs = face_state(m, u0, v0, ph);
+            const FaceState fs = face_state(m, m[M_U0], m[M_V0], ph);
             e = make_eq(fs.rho, fs.u, fs.v, fs.T, fs.qx, fs.qy, nullptr, ph);
             if (ph.compat && ph.face_compat) {
                 double a[8];
@@ -1579,19 +1804,6 @@ __device__ __forceinline__ void face_full_items(const LevelDesc* __restrict__ lv
         }
         if (lane_id() == 0) write_face_record(fpar + (size_t)f * NFP, kind, F, c1, c2, e);
     }
-}
-
-template <typename S, int U, int MINW, int CM, int MK>
-__global__ __launch_bounds__(BS, MINW) void k_face_full(const LevelDesc* __restrict__ lvs,
-                                                        const FaceItem* __restrict__ items, int nF,
-                                                        const int* __restrict__ cell_slot,
-                                                        const int* __restrict__ cell_nbr,
-                                                        const CellGeom* __restrict__ geom,
-                                                        const double* __restrict__ params,
-                                                        const BCDev* __restrict__ bcs, Phys ph,
-                                                        double* __restrict__ fpar) {
-    face_full_items<S, U, CM, MK>(lvs, items, nF, cell_slot, cell_nbr, geom, params, bcs, ph, fpar, item0(),
-                                  istride());
 }
 
 template <typename S>
@@ -2097,30 +2309,25 @@ constexpr int N_VARIANTS = 5;
             }                                                                                   \
         }                                                                                       \
     } while (0)
-#define MLVS_LAUNCH_UWCM(prec, KERNEL, U_, W_, C_, M_, ...)                                      \
+// ... the reconstruction, per occupancy and mesh kind
+#define MLVS_LAUNCH_REC(prec, W_, M_, ...)                                                       \
     do {                                                                                        \
-        if ((prec) == 32) hipLaunchKernelGGL((KERNEL<float, U_, W_, C_, M_>), __VA_ARGS__);      \
-        else hipLaunchKernelGGL((KERNEL<double, U_, W_, C_, M_>), __VA_ARGS__);                  \
+        if ((prec) == 32) hipLaunchKernelGGL((k_face_rec<float, W_, M_>), __VA_ARGS__);          \
+        else hipLaunchKernelGGL((k_face_rec<double, W_, M_>), __VA_ARGS__);                      \
     } while (0)
-#define MLVS_DISPATCH_VCM1(prec, var, C_, mk, KERNEL, ...)                                       \
+#define MLVS_DISPATCH_REC(prec, var, mk, ...)                                                    \
     do {                                                                                        \
         if (mk) {                                                                               \
-            MLVS_LAUNCH_UWCM(prec, KERNEL, 1, 4, C_, 1, __VA_ARGS__);                            \
+            MLVS_LAUNCH_REC(prec, 2, 1, __VA_ARGS__);                                            \
         } else {                                                                                \
             switch (var) {                                                                      \
-            case 0: MLVS_LAUNCH_UWCM(prec, KERNEL, 1, 4, C_, 0, __VA_ARGS__); break;             \
-            case 2: MLVS_LAUNCH_UWCM(prec, KERNEL, 4, 2, C_, 0, __VA_ARGS__); break;             \
-            case 3: MLVS_LAUNCH_UWCM(prec, KERNEL, 4, 4, C_, 0, __VA_ARGS__); break;             \
-            case 4: MLVS_LAUNCH_UWCM(prec, KERNEL, 1, 2, C_, 0, __VA_ARGS__); break;             \
-            default: MLVS_LAUNCH_UWCM(prec, KERNEL, 2, 4, C_, 0, __VA_ARGS__); break;            \
+            case 0: MLVS_LAUNCH_REC(prec, 2, 0, __VA_ARGS__); break;                             \
+            case 2: MLVS_LAUNCH_REC(prec, 4, 0, __VA_ARGS__); break;                             \
+            case 3: MLVS_LAUNCH_REC(prec, 5, 0, __VA_ARGS__); break;                             \
+            case 4: MLVS_LAUNCH_REC(prec, 1, 0, __VA_ARGS__); break;                             \
+            default: MLVS_LAUNCH_REC(prec, 3, 0, __VA_ARGS__); break;                            \
             }                                                                                   \
         }                                                                                       \
-    } while (0)
-#define MLVS_DISPATCH_VCM(prec, var, cm, mk, KERNEL, ...)                                        \
-    do {                                                                                        \
-        if ((cm) == 8 && (mk)) MLVS_LAUNCH_UWCM(prec, KERNEL, 1, 2, 8, 1, __VA_ARGS__);          \
-        else if ((cm) == 8) MLVS_LAUNCH_UWCM(prec, KERNEL, 1, 2, 8, 0, __VA_ARGS__);             \
-        else MLVS_DISPATCH_VCM1(prec, var, 4, mk, KERNEL, __VA_ARGS__);                          \
     } while (0)
 
 int variant_count() { return N_VARIANTS; }
@@ -2166,12 +2373,14 @@ hipError_t launch_ghost(int prec, hipStream_t st, const LevelDesc* lv, const Gho
     return hipGetLastError();
 }
 
-hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n,
-                           const int* cell_slot, const int* cell_nbr, const CellGeom* geom, const double* params,
-                           Phys ph, double* fmom, int CH, int nch, int var) {
-    if (n <= 0) return hipSuccess;
-    MLVS_DISPATCH_VM(prec, var, ph.mesh_kind, k_face_rec, dim3(grid_for(n * nch)), dim3(BS), 0, st, lv, items, n,
-                     cell_slot, cell_nbr, geom, params, ph, fmom, CH, nch);
+hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev, const int* cell_slot,
+                           const int* cell_nbr, const int* cell_frow, const int* order, int n_cells,
+                           const FaceItem* items, int nF, const CellGeom* geom, const double* params, Phys ph,
+                           double* fmom, int CH, int nch, int var) {
+    if (n_cells <= 0 || nF <= 0) return hipSuccess;
+    MLVS_DISPATCH_REC(prec, var, ph.mesh_kind, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st, lv,
+                      cell_lev, cell_slot, cell_nbr, cell_frow, order, n_cells, items, nF, geom, params, ph, fmom, CH,
+                      nch);
     return hipGetLastError();
 }
 
@@ -2180,15 +2389,6 @@ hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, con
     if (n <= 0) return hipSuccess;
     MLVS_DISPATCH_VC(prec, var, ph.compat, k_face_target, dim3(grid_for(n, GW)), dim3(GBS), 0, st, lv, items, n, bcs,
                      ph, fmom, fpar, CH);
-    return hipGetLastError();
-}
-
-hipError_t launch_face_full(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n,
-                            const int* cell_slot, const int* cell_nbr, const CellGeom* geom, const double* params,
-                            const BCDev* bcs, Phys ph, double* fpar, int var) {
-    if (n <= 0) return hipSuccess;
-    MLVS_DISPATCH_VCM(prec, var, ph.compat, ph.mesh_kind, k_face_full, dim3(grid_for(n)), dim3(BS), 0, st, lv, items,
-                      n, cell_slot, cell_nbr, geom, params, bcs, ph, fpar);
     return hipGetLastError();
 }
 
@@ -2961,8 +3161,8 @@ __device__ __forceinline__ void grid_barrier(unsigned int* sync, unsigned int& p
     __syncthreads();
 }
 
-// The fused step of one time step (neighbour rows; cross-level and
-// same-level faces; update with the next step's cell stage) as one launch
+// The fused step of one time step (neighbour rows; cross-level faces and the
+// reconstruction; face targets; update with the next step's cell stage) as one launch
 // over the work lists of StepArgs, whose pointers and counts are read from
 // device memory: a captured launch stays valid when an adaptation replaces
 // the level set.  Stages are separated by grid barriers.  The cross-level
@@ -2978,8 +3178,10 @@ __global__ __launch_bounds__(BS, MINW) void k_step_persistent(const StepArgs* __
     xface_items<S, MK>(A->lvs, A->xfaces, nx, A->cell_slot, A->cell_nbr, A->geom, A->params, ph, A->neg, first,
                           stride);
     const int fstart = ((first - nx) % stride + stride) % stride;
-    face_full_items<S, U, CM, MK>(A->lvs, A->faces, A->n_faces, A->cell_slot, A->cell_nbr, A->geom, A->params,
-                                  A->bcs, ph, A->fpar, fstart, stride);
+    cell_rec_items<S, MK>(A->lvs, A->cell_lev, A->cell_slot, A->cell_nbr, A->cell_frow, A->order, A->n_cells, A->faces,
+                          A->n_faces, A->geom, A->params, ph, A->fmom, 1 << 30, 1, fstart, stride);
+    grid_barrier(A->sync, phase);
+    face_target_items<S, U, CM>(A->lvs, A->faces, A->n_faces, A->bcs, ph, A->fmom, A->fpar, first, stride);
     grid_barrier(A->sync, phase);
     update_cell_items<S, U, CM>(A->lvs, A->cell_lev, A->cell_slot, A->order, A->n_cells, A->geom, A->cell_frow,
                                 A->faces, A->fpar, A->params, ph, A->cmom, first, stride);

@@ -21,10 +21,10 @@ enum {
 // the cell stage, taken about the velocity shift (M_U0, M_V0).
 enum { M_U0 = 11, M_V0 = 12, NMOM = 16 };
 
-// Per-face raw moments of phi_bar_f written by the reconstruction stage, per
-// (velocity chunk, face): the eleven sums (interior faces; boundary faces: [0]
-// the outgoing mass flux), then the velocity shift (u0, v0) they are taken
-// about -- the layout of the cell moments, so NFMOM = NMOM.
+// Raw moments of phi_bar_f written by the reconstruction stage, per (velocity
+// chunk, face, side: 0 the left cell's outgoing half of the velocities, 1 the
+// right cell's): the eleven sums, then the cell velocity they are taken about -- the layout of the cell
+// moments, so NFMOM = NMOM.
 enum { NFMOM = NMOM };
 
 // Per-face record written by the face-target stage and read by the update
@@ -40,6 +40,11 @@ enum {
     NFP = 26
 };
 
+// Angles as 32-bit integers, a whole turn 2^32.  A quarter turn, and the margin
+// (2.4e-5 rad) by which a decision from angles must be clear of it: far above
+// the rounding of an angle or of a float velocity (about 1e-7).
+constexpr int ANG_QUARTER = 1 << 30, ANG_MARGIN = 1 << 14;
+
 // One velocity space (a representative level or an interface level).
 struct LevelDesc {
     int N;             // points
@@ -50,6 +55,8 @@ struct LevelDesc {
     const double* xi_y;
     const double* w;
     const float* xy32;      // (xi_x, xi_y) pairs rounded to float (FP32 storage reads these)
+    const int* ang;         // first and last point's velocity angle of every 64 points, in units
+                            // of 2^-31 half turns (points are stored by angle)
     void* g;   void* h;     // state g~, h~           [cells][stride]
     void* fg;  void* fh;    // phi_bar+ of the step: [cells][stride] followed by the ghost
                             // rows (neighbours on other levels mapped onto this level)
@@ -77,8 +84,9 @@ struct CellGeom {
     double inv_dist[4];  // 1 / dist
     // unstructured meshes (slot k = the cell's k-th edge):
     double lx[4], ly[4];    // least-squares gradient = sum_k (lx, ly)[k] (phi_k - phi_c) (0: no neighbour)
-    double fox[4], foy[4];  // x_f - x_c of each face (0: no face)
     double eps2;            // Venkatakrishnan's eps^2
+    double fox[4], foy[4];  // x_f - x_c of each face (every mesh; 0: no face)
+    int ang[4];             // angle of each face's outward normal (every mesh; see LevelDesc)
 };
 
 struct FaceItem {      // same-level interior face (R >= 0) or boundary face (R = -1 - bc id)
@@ -131,6 +139,7 @@ struct StepArgs {
     double* params;
     double* cmom;
     double* fpar;
+    double* fmom;
     unsigned long long* neg;
     unsigned int* sync;          // [0] barrier arrivals (cleared before each launch), [1] sticky error flag
     int n_ghosts, n_faces, n_xfaces, n_cells;
@@ -148,9 +157,10 @@ hipError_t launch_raw_moments(int prec, hipStream_t st, const LevelDesc* lv, con
 hipError_t launch_ghost(int prec, hipStream_t st, const LevelDesc* lv, const GhostItem* items, int n,
                         const int* cell_lev, const int* cell_slot, const double* params, Phys ph,
                         unsigned long long* neg);
-hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n,
-                           const int* cell_slot, const int* cell_nbr, const CellGeom* geom,
-                           const double* params, Phys ph, double* fmom, int CH, int nch, int var = 1);
+hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
+                           const int* cell_slot, const int* cell_nbr, const int* cell_frow, const int* order,
+                           int n_cells, const FaceItem* items, int nF, const CellGeom* geom, const double* params,
+                           Phys ph, double* fmom, int CH, int nch, int var = 1);
 hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n,
                               const BCDev* bcs, Phys ph, const double* fmom, double* fpar, int CH, int var = 1);
 hipError_t launch_xface(int prec, hipStream_t st, const LevelDesc* lv, const XFaceItem* items, int n,
@@ -163,12 +173,8 @@ hipError_t launch_xface(int prec, hipStream_t st, const LevelDesc* lv, const XFa
 int persistent_variant_count();
 hipError_t launch_step_persistent(int prec, hipStream_t st, const StepArgs* A, unsigned int* sync, Phys ph, int var,
                                   int* grid_used);
-// Fused forms for level sets that fit one velocity chunk: reconstruction +
-// target in one wave per face; update + the next step's cell stage in one
-// wave per cell.
-hipError_t launch_face_full(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n,
-                            const int* cell_slot, const int* cell_nbr, const CellGeom* geom, const double* params,
-                            const BCDev* bcs, Phys ph, double* fpar, int var = 1);
+// Update and the next step's cell stage in one wave per cell, for level sets
+// that fit one velocity chunk.
 hipError_t launch_update_cell(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                               const int* cell_slot, const int* order, int n_cells, const CellGeom* geom,
                               const int* cell_frow, const FaceItem* items, const double* fpar, double* params,
