@@ -1099,6 +1099,8 @@ struct mlvs_ctx_s {
     int chunk = 1024;                  // velocity points per chunk (multiple of 64), set per level set
     int chunk_env = 0;                 // MLVS_CHUNK: a fixed chunk instead of the chosen one
     int nch = 1;                       // chunks of the largest level
+    bool tensor = false;               // the level set is the base grid alone (see LevelDesc::axes)
+    double* d_cpar = nullptr;          // [n_cells][NFP] cell records (tensor level sets)
     double* d_fpar = nullptr;          // [faces + boundary faces][NFP] face records
     bool mom_valid = false;            // d_cmom matches the stored state
     BCDev* d_bcs = nullptr;
@@ -1271,7 +1273,7 @@ void free_items(mlvs_ctx c) {
     c->item_allocs.clear();
     for (auto& L : c->ifaces) free_level(c, *L);
     c->ifaces.clear();
-    c->d_faces = nullptr; c->d_fmom = nullptr; c->d_fpar = nullptr; c->d_cmom = nullptr; c->d_ghosts = nullptr; c->d_xfaces = nullptr;
+    c->d_faces = nullptr; c->d_fmom = nullptr; c->d_fpar = nullptr; c->d_cpar = nullptr; c->d_cmom = nullptr; c->d_ghosts = nullptr; c->d_xfaces = nullptr;
     c->d_lv = nullptr;
     c->n_faces = c->n_bfaces = c->n_ghosts = c->n_xfaces = 0;
 }
@@ -1719,12 +1721,15 @@ void build_items(mlvs_ctx c) {
         xitems[i].AfromI = (a_first ? T[2] : T[3]).at(base);
         xitems[i].BfromI = (a_first ? T[3] : T[2]).at(base);
     }
+    // one level that merges nothing: the tensor base grid itself
+    c->tensor = K == 1 && c->levels[0]->N == c->base.N;
     // level descriptors: representative levels then interface levels
     std::vector<LevelDesc> descs;
     for (int i = 0; i < K + (int)c->ifaces.size(); ++i) {
         Level& L = level_by_index(c, i);
         LevelDesc d{};
         d.N = L.N; d.stride = L.stride; d.n_rows_state = L.n_cells;
+        if (c->tensor) { d.axes = c->d_axes; d.nx = c->base.nx; d.ny = c->base.ny; }
         d.xi_x = L.d_x; d.xi_y = L.d_y; d.w = L.d_w; d.xy32 = L.d_xy; d.ang = L.d_ang;
         d.g = L.g; d.h = L.h; d.fg = L.fg; d.fh = L.fh; d.Fg = L.Fg; d.Fh = L.Fh;
         std::copy(L.Minv, L.Minv + 16, d.Minv);
@@ -1783,6 +1788,11 @@ void build_items(mlvs_ctx c) {
     c->prep_valid = false;
     c->d_fpar = static_cast<double*>(c->dm.alloc(sizeof(double) * NFP * (size_t)std::max(nF_all, 1)));
     c->item_allocs.push_back(c->d_fpar);
+    c->d_cpar = nullptr;
+    if (c->tensor) {
+        c->d_cpar = static_cast<double*>(c->dm.alloc(sizeof(double) * NFP * (size_t)std::max(n, 1)));
+        c->item_allocs.push_back(c->d_cpar);
+    }
     update_step_args(c);                  // last: every pointer it records is allocated
 }
 
@@ -3588,7 +3598,7 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
     const int nf = c->n_faces + c->n_bfaces;
     switch (stage) {
     case 0: return launch_cell_prep(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->ph,
-                                    c->d_params, c->d_cmom, c->chunk, c->variant[0]);
+                                    c->d_params, c->d_cmom, c->chunk, c->d_cpar, c->variant[0]);
     case 1: return launch_ghost(c->prec, c->st, c->d_lv, c->d_ghosts, c->n_ghosts, c->d_cell_lev, c->d_cell_slot,
                                 c->d_params, c->ph, c->d_neg);
     case 2: case 7: {
@@ -3596,11 +3606,11 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
                                              c->d_cell_frow, c->d_order, n, c->d_faces, nf, c->d_geom, c->d_params,
                                              c->ph, c->d_fmom, c->chunk, c->nch, c->variant[stage]);
         if (stage == 2 || e != hipSuccess) return e;
-        return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->d_bcs, c->ph, c->d_fmom, c->d_fpar,
-                                  c->chunk, c->variant[7]);
+        return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->n_faces, c->d_bcs, c->ph, c->d_fmom,
+                                  c->d_fpar, c->chunk, c->tensor, c->variant[7]);
     }
-    case 3: return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->d_bcs, c->ph, c->d_fmom,
-                                      c->d_fpar, c->chunk, c->variant[3]);
+    case 3: return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->n_faces, c->d_bcs, c->ph, c->d_fmom,
+                                      c->d_fpar, c->chunk, c->tensor, c->variant[3]);
     case 4: return launch_xface(c->prec, on ? on : c->st, c->d_lv, c->d_xfaces, c->n_xfaces, c->d_cell_slot, c->d_cell_nbr,
                                 c->d_geom, c->d_params, c->ph, c->d_neg, c->variant[4]);
     case 5: return launch_update(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->d_geom,

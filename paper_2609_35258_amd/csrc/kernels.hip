@@ -389,6 +389,109 @@ __device__ __forceinline__ void compat_solve(const LevelDesc& L, const Eq<S>& eu
     for (int k = 0; k < 4; ++k) a_out[k] = uni(a_out[k]);
 }
 
+// The four-moment correction on the tensor base grid (LevelDesc::axes): the
+// target is a Gaussian times polynomials of c = xi - u, so every velocity sum
+// factors into sums over the two axes, A_k = sum w e^{-c_x^2/2RT} c_x^k and B_l
+// likewise, k, l <= 7: n_x + n_y exponentials per item instead of n_x n_y (202
+// instead of 10201 on 101^2; summed over all points, the face targets of the
+// cylinder 256 x 128, 101^2, FP32 took 1.09 ms, so .128).  Sixteen lanes per item: lane lg of the group
+// takes every sixteenth node, a fixed tree adds the lanes, and every lane
+// holds the result, whatever the launch puts beside the group.  The sums are
+// of the rounded parameters the step evaluates the target with (S).  Solved in
+// the basis [1, c_x, c_y, c^2] (the same span and constraints, taken about the
+// velocity), returned as coefficients of [1, xi_x, xi_y, E_xi].
+constexpr int AXG = 16;
+
+__device__ __forceinline__ void axis_sums(const double* x, const double* w, int n, double u, double i2RT, bool f32,
+                                          int lg, double (&A)[8]) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) A[k] = 0.0;
+    constexpr int U = 4;               // nodes in flight: their loads and exponentials overlap
+    for (int i0 = lg; i0 < n; i0 += AXG * U) {
+        double c[U], t[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int i = i0 + AXG * q, ic = clampi(i, n);
+            const double xi = gp(x)[ic];
+            c[q] = (f32 ? (double)(float)xi : xi) - u;
+            t[q] = i < n ? gp(w)[ic] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) t[q] *= exp(-(c[q] * c[q]) * i2RT);
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                A[k] += t[q];
+                t[q] *= c[q];
+            }
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        double v = A[k];
+        v += dpp_mov<0xB1>(v);
+        v += dpp_mov<0x4E>(v);
+        v += dpp_mov<0x141>(v);
+        v += dpp_mov<0x140>(v);
+        A[k] = v;
+    }
+}
+
+template <typename S>
+__device__ __forceinline__ void compat_axes(const LevelDesc& L, const Eq<double>& e, double rho, double u, double v,
+                                            double T, const Phys& ph, int lg, double* a_out) {
+    constexpr bool F32 = sizeof(S) == 4;
+    auto r = [](double q) { return F32 ? (double)(float)q : q; };
+    const double ue = r(e.ux), ve = r(e.uy), i2RT = r(e.i2RT), iRT = r(e.iRT);
+    double A[8], B[8];
+    axis_sums(L.axes, L.axes + L.nx, L.nx, ue, i2RT, F32, lg, A);
+    axis_sums(L.axes + 2 * L.nx, L.axes + 2 * L.nx + L.ny, L.ny, ve, i2RT, F32, lg, B);
+    // sum w E c_x^a c_y^b (c^2)^m of the Gaussian E
+    auto Q = [&](int a, int b, int m) {
+        if (m == 0) return A[a] * B[b];
+        if (m == 1) return A[a + 2] * B[b] + A[a] * B[b + 2];
+        if (m == 2) return A[a + 4] * B[b] + 2.0 * (A[a + 2] * B[b + 2]) + A[a] * B[b + 4];
+        return A[a + 6] * B[b] + 3.0 * (A[a + 4] * B[b + 2] + A[a + 2] * B[b + 4]) + A[a] * B[b + 6];
+    };
+    const double qx = r(e.Xqx), qy = r(e.Xqy), rn = r(e.rn), rRT = rn * r(e.RT);
+    auto G = [&](int a, int b, int m) {            // sum w g c_x^a c_y^b (c^2)^m
+        const double q1 = qx * Q(a + 1, b, m) + qy * Q(a, b + 1, m);
+        const double q3 = qx * Q(a + 1, b, m + 1) + qy * Q(a, b + 1, m + 1);
+        return rn * (Q(a, b, m) + (iRT * q3 - e.Dp2 * q1));
+    };
+    auto H = [&](int a, int b, int m) {            // sum w h c_x^a c_y^b (c^2)^m
+        const double q1 = qx * Q(a + 1, b, m) + qy * Q(a, b + 1, m);
+        const double q3 = qx * Q(a + 1, b, m + 1) + qy * Q(a, b + 1, m + 1);
+        return rRT * (e.cK * Q(a, b, m) + (e.cK * iRT * q3 - (e.Dd * e.cK + e.K2) * q1));
+    };
+    const double g0 = G(0, 0, 0), gx = G(1, 0, 0), gc = G(0, 0, 1), gxc = G(1, 0, 1);
+    const double h0 = H(0, 0, 0), hx = H(1, 0, 0);
+    const double du = u - ue, dv = v - ve;
+    const double en = 0.5 * (3.0 + ph.K) * rho * ph.R * T + 0.5 * rho * (du * du + dv * dv);
+    const double e3 = 0.5 * (gc + h0), e33 = 0.5 * (G(0, 0, 2) + H(0, 0, 1));
+    double d[4];
+    if (ph.D == 2) {
+        const double gy = G(0, 1, 0), gxy = G(1, 1, 0), gyc = G(0, 1, 1);
+        double M[4][4] = {{g0, gx, gy, gc},
+                          {gx, G(2, 0, 0), gxy, gxc},
+                          {gy, gxy, G(0, 2, 0), gyc},
+                          {e3, 0.5 * (gxc + hx), 0.5 * (gyc + H(0, 1, 0)), e33}};
+        double b[4] = {rho - g0, rho * du - gx, rho * dv - gy, en - e3};
+        solve_fixed<4>(M, b);
+        d[0] = b[0]; d[1] = b[1]; d[2] = b[2]; d[3] = b[3];
+    } else {
+        double M[3][3] = {{g0, gx, gc}, {gx, G(2, 0, 0), gxc}, {e3, 0.5 * (gxc + hx), e33}};
+        double b[3] = {rho - g0, rho * du - gx, en - e3};
+        solve_fixed<3>(M, b);
+        d[0] = b[0]; d[1] = b[1]; d[2] = 0.0; d[3] = b[2];
+    }
+    const double E0 = 0.5 * (3.0 - ph.D + ph.K) * ph.R * T;
+    a_out[3] = 2.0 * d[3];
+    a_out[1] = d[1] - a_out[3] * ue;
+    a_out[2] = ph.D == 2 ? d[2] - a_out[3] * ve : 0.0;
+    a_out[0] = d[0] - a_out[1] * ue - a_out[2] * ve - a_out[3] * (E0 + 0.5 * (ue * ue + ve * ve));
+}
+
 // Eight-moment compatibility correction (Sec. 3.3.1, Eqs. eq_eight_basis,
 // E_c_definition, eq_eight_moment_constraint; D = 2): basis phi = [1, xi_x,
 // xi_y, E_xi, E_c c_x, E_c c_y, c_x^2 - c_y^2, c_x c_y], constraint rows
@@ -583,6 +686,8 @@ __device__ __forceinline__ void cell_target_wave(const LevelDesc& L, const CellS
         double A[64];
         compat_sums8<S, U>(L, eq_cast<S>(e), cs.u, cs.v, cs.T, ph, A);
         compat_from_sums8(A, cs.rho, cs.u, cs.v, cs.T, (1.0 - ph.Pr) * cs.qx, (1.0 - ph.Pr) * cs.qy, ph, a);
+    } else if (L.axes) {
+        compat_axes<S>(L, e, cs.rho, cs.u, cs.v, cs.T, ph, lane_id() & (AXG - 1), a);
     } else {
         double sm[13];
         compat_sums<S, U>(L, eq_cast<S>(e), sm);
@@ -666,6 +771,70 @@ __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __rest
             phibar_points<S, U>(L, (size_t)cell_slot[c] * L.stride, sh_e[j], sh_c[j].alpha, sh_c[j].beta);
         }
         __syncthreads();
+    }
+}
+
+// The record of an equation and two weights (layout FP_*): a face's target, or
+// a cell's.
+__device__ __forceinline__ void write_eq_record(double* o, double c1, double c2, const Eq<double>& e) {
+    o[FP_C1] = c1; o[FP_C2] = c2;
+    o[FP_RN] = e.rn; o[FP_UX] = e.ux; o[FP_UY] = e.uy; o[FP_I2RT] = e.i2RT; o[FP_RT] = e.RT;
+    o[FP_IRT] = e.iRT; o[FP_XQX] = e.Xqx; o[FP_XQY] = e.Xqy;
+    o[FP_B0] = e.b0; o[FP_B1] = e.b1; o[FP_B2] = e.b2; o[FP_B3] = e.b3;
+    o[FP_CORR] = e.corr ? 1.0 : 0.0;
+    o[FP_E4] = e.e4; o[FP_E5] = e.e5; o[FP_E6] = e.e6; o[FP_E7] = e.e7; o[FP_CKRT] = e.cKRT;
+    o[FP_C8] = e.c8 ? 1.0 : 0.0;
+}
+
+template <typename T>
+__device__ __forceinline__ Eq<double> read_eq_record(const T* fp, const Phys& ph) {
+    Eq<double> d;
+    d.rn = fp[FP_RN]; d.ux = fp[FP_UX]; d.uy = fp[FP_UY]; d.i2RT = fp[FP_I2RT]; d.RT = fp[FP_RT];
+    d.iRT = fp[FP_IRT]; d.Xqx = fp[FP_XQX]; d.Xqy = fp[FP_XQY];
+    d.b0 = fp[FP_B0]; d.b1 = fp[FP_B1]; d.b2 = fp[FP_B2]; d.b3 = fp[FP_B3];
+    d.cK = ph.K + 3.0 - ph.D; d.Dp2 = ph.D + 2.0; d.Dd = ph.D; d.K2 = 2.0 * ph.K;
+    d.corr = fp[FP_CORR] != 0.0;
+    d.e4 = fp[FP_E4]; d.e5 = fp[FP_E5]; d.e6 = fp[FP_E6]; d.e7 = fp[FP_E7]; d.cKRT = fp[FP_CKRT];
+    d.c8 = fp[FP_C8] != 0.0;
+    return d;
+}
+
+// Cell stage on the tensor base grid, where the correction costs axis sums
+// only: state, correction and parameters by sixteen lanes per cell (records to
+// cpar), then the rows as a plain stream, at the rate of a copy.  Cylinder
+// 256 x 128, 101^2, FP32: 1.85 ms with sums over all points in the row pass,
+// 1.15 so; 1-D with 200 cells 28.0 -> 27.5 us a step.
+template <typename S>
+__global__ __launch_bounds__(BS) void k_cell_target_axes(const LevelDesc* __restrict__ lvs,
+                                                         const int* __restrict__ cell_lev, int n_cells, Phys ph,
+                                                         double* __restrict__ params,
+                                                         const double* __restrict__ cmom, int CH,
+                                                         double* __restrict__ cpar) {
+    const int lg = threadIdx.x & (AXG - 1);
+    for (int c = (blockIdx.x * BS + threadIdx.x) / AXG; c < n_cells; c += gridDim.x * (BS / AXG)) {
+        const LevelDesc& L = lvs[cell_lev[c]];
+        double cm[NMOM], a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        sum_chunks(cmom, c, n_cells, L.N, CH, cm);
+        const CellState cs = cell_state(cm, ph);
+        Eq<double> e = make_eq(cs.rho, cs.u, cs.v, cs.T, cs.qx, cs.qy, nullptr, ph);
+        compat_axes<S>(L, e, cs.rho, cs.u, cs.v, cs.T, ph, lg, a);
+        e = make_eq(cs.rho, cs.u, cs.v, cs.T, cs.qx, cs.qy, a, ph);
+        if (lg == 0) {
+            write_params(params + (size_t)c * NPARAM, cs, a);
+            write_eq_record(cpar + (size_t)c * NFP, cs.alpha, cs.beta, e);
+        }
+    }
+}
+
+template <typename S, int U, int MINW>
+__global__ __launch_bounds__(BS, MINW) void k_phibar(const LevelDesc* __restrict__ lvs, const int* __restrict__ cell_lev,
+                                                     const int* __restrict__ cell_slot, const int* __restrict__ order,
+                                                     int n_cells, Phys ph, const double* __restrict__ cpar) {
+    for (int it = item0(); it < n_cells; it += istride()) {
+        const int c = order[it];
+        const LevelDesc& L = lvs[cell_lev[c]];
+        const double* fp = cpar + (size_t)c * NFP;
+        phibar_points<S, U>(L, (size_t)cell_slot[c] * L.stride, read_eq_record(fp, ph), fp[FP_C1], fp[FP_C2]);
     }
 }
 
@@ -1576,41 +1745,47 @@ __device__ __forceinline__ void face_moments(const double* fmom, int f, int nF, 
                                              double* out) {
     const bool interior = F.R >= 0;
     const int nch = (N + CH - 1) / CH;
-    double half[2][13];
-    for (int sd = 0; sd < (interior ? 2 : 1); ++sd) {
-        for (int j = 0; j < 13; ++j) half[sd][j] = 0.0;
-        for (int k = 0; k < nch; ++k) {
-            const double* q = fmom + (((size_t)k * nF + f) * 2 + sd) * NFMOM;
-            for (int j = 0; j < 11; ++j) half[sd][j] += q[j];
-        }
+    auto side = [&](int sd, double (&m)[13]) {
         const double* q = fmom + ((size_t)f * 2 + sd) * NFMOM;
-        half[sd][M_U0] = q[M_U0];
-        half[sd][M_V0] = q[M_V0];
-    }
-    for (int j = 0; j < 11; ++j) out[j] = 0.0;
+#pragma unroll
+        for (int j = 0; j < 13; ++j) m[j] = q[j];
+        for (int k = 1; k < nch; ++k) {
+            q += (size_t)nF * 2 * NFMOM;
+#pragma unroll
+            for (int j = 0; j < 11; ++j) m[j] += q[j];
+        }
+    };
+    double l[13], r[13];
+    side(0, l);
     if (!interior) {
-        const double* m = half[0];
-        out[0] = F.nx * (m[1] + m[M_U0] * m[0]) + F.ny * (m[2] + m[M_V0] * m[0]);
+#pragma unroll
+        for (int j = 0; j < 11; ++j) out[j] = l[j];
+        out[0] = F.nx * (l[1] + l[M_U0] * l[0]) + F.ny * (l[2] + l[M_V0] * l[0]);
         out[M_U0] = out[M_V0] = 0.0;
         return;
     }
-    const double u0 = 0.5 * (half[0][M_U0] + half[1][M_U0]), v0 = 0.5 * (half[0][M_V0] + half[1][M_V0]);
-    for (int sd = 0; sd < 2; ++sd) {
-        const double* m = half[sd];
+    side(1, r);
+    const double u0 = 0.5 * (l[M_U0] + r[M_U0]), v0 = 0.5 * (l[M_V0] + r[M_V0]);
+    auto shift = [&](const double (&m)[13], double (&o)[11]) {
         const double a = m[M_U0] - u0, b = m[M_V0] - v0, d2 = a * a + b * b, tr = m[3] + m[5];
         const double am = a * m[1] + b * m[2];
-        out[0] += m[0];
-        out[1] += m[1] + a * m[0];
-        out[2] += m[2] + b * m[0];
-        out[3] += m[3] + 2.0 * a * m[1] + a * a * m[0];
-        out[4] += m[4] + a * m[2] + b * m[1] + a * b * m[0];
-        out[5] += m[5] + 2.0 * b * m[2] + b * b * m[0];
-        out[6] += m[6] + 2.0 * (a * m[3] + b * m[4]) + d2 * m[1] + a * (tr + 2.0 * am + d2 * m[0]);
-        out[7] += m[7] + 2.0 * (a * m[4] + b * m[5]) + d2 * m[2] + b * (tr + 2.0 * am + d2 * m[0]);
-        out[8] += m[8];
-        out[9] += m[9] + a * m[8];
-        out[10] += m[10] + b * m[8];
-    }
+        o[0] = m[0];
+        o[1] = m[1] + a * m[0];
+        o[2] = m[2] + b * m[0];
+        o[3] = m[3] + 2.0 * a * m[1] + a * a * m[0];
+        o[4] = m[4] + a * m[2] + b * m[1] + a * b * m[0];
+        o[5] = m[5] + 2.0 * b * m[2] + b * b * m[0];
+        o[6] = m[6] + 2.0 * (a * m[3] + b * m[4]) + d2 * m[1] + a * (tr + 2.0 * am + d2 * m[0]);
+        o[7] = m[7] + 2.0 * (a * m[4] + b * m[5]) + d2 * m[2] + b * (tr + 2.0 * am + d2 * m[0]);
+        o[8] = m[8];
+        o[9] = m[9] + a * m[8];
+        o[10] = m[10] + b * m[8];
+    };
+    double p[11], q[11];
+    shift(l, p);
+    shift(r, q);
+#pragma unroll
+    for (int j = 0; j < 11; ++j) out[j] = p[j] + q[j];
     out[M_U0] = u0;
     out[M_V0] = v0;
 }
@@ -1658,13 +1833,7 @@ __device__ __forceinline__ double wall_inflow(const LevelDesc& L, const FaceItem
 __device__ __forceinline__ void write_face_record(double* o, double kind, const FaceItem& F, double c1, double c2,
                                                   const Eq<double>& e) {
     o[FP_KIND] = kind; o[FP_ROW] = (double)F.row; o[FP_NX] = F.nx; o[FP_NY] = F.ny;
-    o[FP_C1] = c1; o[FP_C2] = c2;
-    o[FP_RN] = e.rn; o[FP_UX] = e.ux; o[FP_UY] = e.uy; o[FP_I2RT] = e.i2RT; o[FP_RT] = e.RT;
-    o[FP_IRT] = e.iRT; o[FP_XQX] = e.Xqx; o[FP_XQY] = e.Xqy;
-    o[FP_B0] = e.b0; o[FP_B1] = e.b1; o[FP_B2] = e.b2; o[FP_B3] = e.b3;
-    o[FP_CORR] = e.corr ? 1.0 : 0.0;
-    o[FP_E4] = e.e4; o[FP_E5] = e.e5; o[FP_E6] = e.e6; o[FP_E7] = e.e7; o[FP_CKRT] = e.cKRT;
-    o[FP_C8] = e.c8 ? 1.0 : 0.0;
+    write_eq_record(o, c1, c2, e);
 }
 
 template <typename S, int U, int MINW, int CM>
@@ -1759,19 +1928,19 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
 }
 
 // The target of one face in one wave (every lane holds the sums; lane 0
-// writes the record): a stage of the persistent step.  Same arithmetic as
-// k_face_target.
+// writes the record): a stage of the persistent step, and the boundary faces
+// of k_face_target_axes.  Same arithmetic as k_face_target.
 template <typename S, int U, int CM>
 __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ lvs,
                                                   const FaceItem* __restrict__ items, int nF,
                                                   const BCDev* __restrict__ bcs, Phys ph,
-                                                  const double* __restrict__ fmom, double* __restrict__ fpar,
+                                                  const double* __restrict__ fmom, double* __restrict__ fpar, int CH,
                                                   int first, int stride) {
     for (int f = first; f < nF; f += stride) {
         const FaceItem F = items[f];
         const LevelDesc& L = lvs[F.lev];
         double m[NFMOM];
-        face_moments(fmom, f, nF, F, L.N, L.N, m);
+        face_moments(fmom, f, nF, F, L.N, CH, m);
         double kind = 0.0, c1, c2;
         Eq<double> e;
         if (F.R >= 0) {
@@ -1784,6 +1953,8 @@ __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ 
                     compat_sums8<S, U>(L, eq_cast<S>(e), fs.u, fs.v, fs.T, ph, A);
                     compat_from_sums8(A, fs.rho, fs.u, fs.v, fs.T, (1.0 - ph.Pr) * fs.qx, (1.0 - ph.Pr) * fs.qy,
                                       ph, a);
+                } else if (L.axes) {
+                    compat_axes<S>(L, e, fs.rho, fs.u, fs.v, fs.T, ph, lane_id() & (AXG - 1), a);
                 } else {
                     double sm[13];
                     compat_sums<S, U>(L, eq_cast<S>(e), sm);
@@ -1806,17 +1977,41 @@ __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ 
     }
 }
 
+// Face targets on the tensor base grid: sixteen lanes per interior face (faces
+// [0, n_in), the first n_wg workgroups), so the scalar chain (state, solve,
+// record) runs for four faces at once and the correction costs axis sums; then
+// a wave per boundary face.
+template <typename S>
+__global__ __launch_bounds__(BS) void k_face_target_axes(const LevelDesc* __restrict__ lvs,
+                                                         const FaceItem* __restrict__ items, int n_in, int nF,
+                                                         const BCDev* __restrict__ bcs, Phys ph,
+                                                         const double* __restrict__ fmom,
+                                                         double* __restrict__ fpar, int CH, int n_wg) {
+    if ((int)blockIdx.x >= n_wg) {
+        const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        face_target_items<S, 1, 4>(lvs, items, nF, bcs, ph, fmom, fpar, CH,
+                                   n_in + ((int)blockIdx.x - n_wg) * MAXW + w, ((int)gridDim.x - n_wg) * MAXW);
+        return;
+    }
+    const int lg = threadIdx.x & (AXG - 1);
+    for (int f = (blockIdx.x * BS + threadIdx.x) / AXG; f < n_in; f += n_wg * (BS / AXG)) {
+        const FaceItem F = items[f];
+        const LevelDesc& L = lvs[F.lev];
+        double m[NFMOM], a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        face_moments(fmom, f, nF, F, L.N, CH, m);
+        const FaceState fs = face_state(m, m[M_U0], m[M_V0], ph);
+        Eq<double> e = make_eq(fs.rho, fs.u, fs.v, fs.T, fs.qx, fs.qy, nullptr, ph);
+        if (ph.compat && ph.face_compat) {
+            compat_axes<S>(L, e, fs.rho, fs.u, fs.v, fs.T, ph, lg, a);
+            e = make_eq(fs.rho, fs.u, fs.v, fs.T, fs.qx, fs.qy, a, ph);
+        }
+        if (lg == 0) write_face_record(fpar + (size_t)f * NFP, 0.0, F, fs.c1 * F.area, fs.c2 * F.area, e);
+    }
+}
+
 template <typename S>
 __device__ __forceinline__ Eq<S> load_face_eq(const double* fp, const Phys& ph) {
-    Eq<double> d;
-    d.rn = fp[FP_RN]; d.ux = fp[FP_UX]; d.uy = fp[FP_UY]; d.i2RT = fp[FP_I2RT]; d.RT = fp[FP_RT];
-    d.iRT = fp[FP_IRT]; d.Xqx = fp[FP_XQX]; d.Xqy = fp[FP_XQY];
-    d.b0 = fp[FP_B0]; d.b1 = fp[FP_B1]; d.b2 = fp[FP_B2]; d.b3 = fp[FP_B3];
-    d.cK = ph.K + 3.0 - ph.D; d.Dp2 = ph.D + 2.0; d.Dd = ph.D; d.K2 = 2.0 * ph.K;
-    d.corr = fp[FP_CORR] != 0.0;
-    d.e4 = fp[FP_E4]; d.e5 = fp[FP_E5]; d.e6 = fp[FP_E6]; d.e7 = fp[FP_E7]; d.cKRT = fp[FP_CKRT];
-    d.c8 = fp[FP_C8] != 0.0;
-    return eq_cast<S>(d);
+    return eq_cast<S>(read_eq_record(fp, ph));
 }
 
 // ---------------------------------------------------------------------------
@@ -2210,22 +2405,6 @@ static inline int grid_for(int n, int per = MAXW) {
     return b < NXCD ? NXCD : (b > 1048576 ? 1048576 : b);
 }
 
-// The cross-level faces are few, long items beside the same-level face stages:
-// FP64 takes two waves per SIMD (at four, 450 registers spill: cylinder 95 x 45,
-// 236 faces, 0.212 ms, 0.126 at two); FP32 is no slower at four (cylinder 256 x
-// 128, 566 faces, 0.223 and 0.213 ms alone, and the step 1% faster at four).
-#define MLVS_LAUNCH_X(prec, W32_, W64_, M_, ...)                                                 \
-    do {                                                                                        \
-        if ((prec) == 32) hipLaunchKernelGGL((k_xface<float, W32_, M_>), __VA_ARGS__);           \
-        else hipLaunchKernelGGL((k_xface<double, W64_, M_>), __VA_ARGS__);                       \
-    } while (0)
-#define MLVS_DISPATCH_X(prec, var, mk, ...)                                                      \
-    do {                                                                                        \
-        if (mk) MLVS_LAUNCH_X(prec, 4, 2, 1, __VA_ARGS__);                                       \
-        else if ((var) == 2) MLVS_LAUNCH_X(prec, 2, 1, 0, __VA_ARGS__);                          \
-        else MLVS_LAUNCH_X(prec, 4, 2, 0, __VA_ARGS__);                                          \
-    } while (0)
-
 // Tunable kernels are instantiated for several (points per lane per chunk U,
 // minimum waves per SIMD) pairs; the variant index selects one at launch.
 // (1, 2) gives the FP64 fused kernels 256 VGPRs, where (1, 4) spills.
@@ -2288,27 +2467,22 @@ constexpr int N_VARIANTS = 5;
         else MLVS_DISPATCH_VU1(prec, var, 4, KERNEL, __VA_ARGS__);                               \
     } while (0)
 
-// ... and per mesh kind (unstructured meshes: the (1, 4) pair for every
-// variant; with two points per lane the larger limiter stencil spills)
-#define MLVS_LAUNCH_UWM(prec, KERNEL, U_, W_, M_, ...)                                           \
+// The cross-level faces are few, long items beside the same-level face stages:
+// FP64 takes two waves per SIMD (at four, 450 registers spill: cylinder 95 x 45,
+// 236 faces, 0.212 ms, 0.126 at two); FP32 is no slower at four (cylinder 256 x
+// 128, 566 faces, 0.223 and 0.213 ms alone, and the step 1% faster at four).
+#define MLVS_LAUNCH_X(prec, W32_, W64_, M_, ...)                                                 \
     do {                                                                                        \
-        if ((prec) == 32) hipLaunchKernelGGL((KERNEL<float, U_, W_, M_>), __VA_ARGS__);          \
-        else hipLaunchKernelGGL((KERNEL<double, U_, W_, M_>), __VA_ARGS__);                      \
+        if ((prec) == 32) hipLaunchKernelGGL((k_xface<float, W32_, M_>), __VA_ARGS__);           \
+        else hipLaunchKernelGGL((k_xface<double, W64_, M_>), __VA_ARGS__);                       \
     } while (0)
-#define MLVS_DISPATCH_VM(prec, var, mk, KERNEL, ...)                                             \
+#define MLVS_DISPATCH_X(prec, var, mk, ...)                                                      \
     do {                                                                                        \
-        if (mk) {                                                                               \
-            MLVS_LAUNCH_UWM(prec, KERNEL, 1, 4, 1, __VA_ARGS__);                                 \
-        } else {                                                                                \
-            switch (var) {                                                                      \
-            case 0: MLVS_LAUNCH_UWM(prec, KERNEL, 1, 4, 0, __VA_ARGS__); break;                  \
-            case 2: MLVS_LAUNCH_UWM(prec, KERNEL, 4, 2, 0, __VA_ARGS__); break;                  \
-            case 3: MLVS_LAUNCH_UWM(prec, KERNEL, 4, 4, 0, __VA_ARGS__); break;                  \
-            case 4: MLVS_LAUNCH_UWM(prec, KERNEL, 1, 2, 0, __VA_ARGS__); break;                  \
-            default: MLVS_LAUNCH_UWM(prec, KERNEL, 2, 4, 0, __VA_ARGS__); break;                 \
-            }                                                                                   \
-        }                                                                                       \
+        if (mk) MLVS_LAUNCH_X(prec, 4, 2, 1, __VA_ARGS__);                                       \
+        else if ((var) == 2) MLVS_LAUNCH_X(prec, 2, 1, 0, __VA_ARGS__);                          \
+        else MLVS_LAUNCH_X(prec, 4, 2, 0, __VA_ARGS__);                                          \
     } while (0)
+
 // ... the reconstruction, per occupancy and mesh kind
 #define MLVS_LAUNCH_REC(prec, W_, M_, ...)                                                       \
     do {                                                                                        \
@@ -2338,10 +2512,23 @@ int variant_count() { return N_VARIANTS; }
         else hipLaunchKernelGGL(KERNEL<double>, __VA_ARGS__);                                    \
     } while (0)
 
+// Workgroups for n items of AXG lanes.
+static inline int axes_grid(int n) {
+    const int b = (n + BS / AXG - 1) / (BS / AXG);
+    return b > 1048576 ? 1048576 : b;
+}
+
 hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev, const int* cell_slot,
                             const int* order, int n_cells, Phys ph, double* params, const double* cmom, int CH,
-                            int var) {
+                            double* cpar, int var) {
     if (n_cells <= 0) return hipSuccess;
+    if (cpar && ph.compat != 8) {
+        MLVS_DISPATCH(prec, k_cell_target_axes, dim3(axes_grid(n_cells)), dim3(BS), 0, st, lv, cell_lev, n_cells, ph,
+                      params, cmom, CH, cpar);
+        MLVS_DISPATCH_V(prec, var, k_phibar, dim3(grid_for(n_cells)), dim3(BS), 0, st, lv, cell_lev, cell_slot, order,
+                        n_cells, ph, cpar);
+        return hipGetLastError();
+    }
     MLVS_DISPATCH_VC(prec, var, ph.compat, k_cell_prep, dim3(grid_for(n_cells, GW)), dim3(GBS), 0, st, lv, cell_lev,
                      cell_slot, order, n_cells, ph, params, cmom, CH);
     return hipGetLastError();
@@ -2384,9 +2571,16 @@ hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const 
     return hipGetLastError();
 }
 
-hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n,
-                              const BCDev* bcs, Phys ph, const double* fmom, double* fpar, int CH, int var) {
+hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n, int n_in,
+                              const BCDev* bcs, Phys ph, const double* fmom, double* fpar, int CH, bool axes,
+                              int var) {
     if (n <= 0) return hipSuccess;
+    if (axes && ph.compat != 8) {
+        const int n_wg = n_in > 0 ? axes_grid(n_in) : 0, n_b = (n - n_in + MAXW - 1) / MAXW;
+        MLVS_DISPATCH(prec, k_face_target_axes, dim3(n_wg + n_b), dim3(BS), 0, st, lv, items, n_in, n, bcs, ph, fmom,
+                      fpar, CH, n_wg);
+        return hipGetLastError();
+    }
     MLVS_DISPATCH_VC(prec, var, ph.compat, k_face_target, dim3(grid_for(n, GW)), dim3(GBS), 0, st, lv, items, n, bcs,
                      ph, fmom, fpar, CH);
     return hipGetLastError();
@@ -3181,7 +3375,8 @@ __global__ __launch_bounds__(BS, MINW) void k_step_persistent(const StepArgs* __
     cell_rec_items<S, MK>(A->lvs, A->cell_lev, A->cell_slot, A->cell_nbr, A->cell_frow, A->order, A->n_cells, A->faces,
                           A->n_faces, A->geom, A->params, ph, A->fmom, 1 << 30, 1, fstart, stride);
     grid_barrier(A->sync, phase);
-    face_target_items<S, U, CM>(A->lvs, A->faces, A->n_faces, A->bcs, ph, A->fmom, A->fpar, first, stride);
+    face_target_items<S, U, CM>(A->lvs, A->faces, A->n_faces, A->bcs, ph, A->fmom, A->fpar, 1 << 30, first,
+                                stride);
     grid_barrier(A->sync, phase);
     update_cell_items<S, U, CM>(A->lvs, A->cell_lev, A->cell_slot, A->order, A->n_cells, A->geom, A->cell_frow,
                                 A->faces, A->fpar, A->params, ph, A->cmom, first, stride);

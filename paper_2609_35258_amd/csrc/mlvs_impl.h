@@ -50,7 +50,8 @@ struct LevelDesc {
     int N;             // points
     int stride;        // row stride in elements (multiple of 64)
     int n_rows_state;  // cells on this level
-    int pad;
+    int nx, ny;        // axes' nodes
+    const double* axes;     // the tensor base grid's x [nx], wx [nx], y [ny], wy [ny]; null on coarser levels
     const double* xi_x;
     const double* xi_y;
     const double* w;
@@ -147,10 +148,11 @@ struct StepArgs {
 
 // Launch wrappers (kernels.hip).  `S` selects float (32) or double (64) storage.
 int variant_count();
-// order: the cells in traversal order (a permutation of 0..n_cells-1)
+// order: the cells in traversal order (a permutation of 0..n_cells-1).  cpar:
+// room for n_cells records (NFP) when every level is the tensor base grid, else null.
 hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                             const int* cell_slot, const int* order, int n_cells, Phys ph, double* params,
-                            const double* cmom, int CH, int var = 1);
+                            const double* cmom, int CH, double* cpar, int var = 1);
 hipError_t launch_raw_moments(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                               const int* cell_slot, int n_cells, const double* params, double* cmom, int CH,
                               int nch);
@@ -161,8 +163,10 @@ hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const 
                            const int* cell_slot, const int* cell_nbr, const int* cell_frow, const int* order,
                            int n_cells, const FaceItem* items, int nF, const CellGeom* geom, const double* params,
                            Phys ph, double* fmom, int CH, int nch, int var = 1);
-hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n,
-                              const BCDev* bcs, Phys ph, const double* fmom, double* fpar, int CH, int var = 1);
+// items: n_in interior faces, then boundary faces, n in all; axes: every level is the tensor base grid
+hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n, int n_in,
+                              const BCDev* bcs, Phys ph, const double* fmom, double* fpar, int CH, bool axes,
+                              int var = 1);
 hipError_t launch_xface(int prec, hipStream_t st, const LevelDesc* lv, const XFaceItem* items, int n,
                         const int* cell_slot, const int* cell_nbr, const CellGeom* geom,
                         const double* params, Phys ph, unsigned long long* neg, int var = 1);
