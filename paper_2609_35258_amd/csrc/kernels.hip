@@ -817,8 +817,10 @@ __global__ __launch_bounds__(BS) void k_cell_target_axes(const LevelDesc* __rest
         sum_chunks(cmom, c, n_cells, L.N, CH, cm);
         const CellState cs = cell_state(cm, ph);
         Eq<double> e = make_eq(cs.rho, cs.u, cs.v, cs.T, cs.qx, cs.qy, nullptr, ph);
-        compat_axes<S>(L, e, cs.rho, cs.u, cs.v, cs.T, ph, lg, a);
-        e = make_eq(cs.rho, cs.u, cs.v, cs.T, cs.qx, cs.qy, a, ph);
+        if (ph.compat) {
+            compat_axes<S>(L, e, cs.rho, cs.u, cs.v, cs.T, ph, lg, a);
+            e = make_eq(cs.rho, cs.u, cs.v, cs.T, cs.qx, cs.qy, a, ph);
+        }
         if (lg == 0) {
             write_params(params + (size_t)c * NPARAM, cs, a);
             write_eq_record(cpar + (size_t)c * NFP, cs.alpha, cs.beta, e);

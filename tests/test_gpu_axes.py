@@ -52,6 +52,27 @@ def test_axis_sums_match_the_oracle(case, precision, face_compat):
     g.close()
 
 
+@pytest.mark.parametrize("chunk", ["64", None])
+@pytest.mark.parametrize("case", ["sod_5", "sod_101", "gh_8", "nc_16"])
+def test_correction_off(case, chunk, monkeypatch):
+    # five nodes hold the Maxwellian's moments so badly that a correction shows
+    import paper_2609_35258_amd as m
+    if chunk:
+        monkeypatch.setenv("MLVS_CHUNK", chunk)
+    else:
+        monkeypatch.delenv("MLVS_CHUNK", raising=False)
+    p = _shifted(case)
+    print("case off", case, chunk, flush=True)
+    o = Oracle(p, compat=0)
+    g = m.Solver.from_problem(p, precision=64, compat=0)
+    for k in range(2):
+        o.step()
+        g.step(1)
+        e = state_error(g.get_state(), o.g, o.h)
+        assert max(e) < 1e-12, (k, e)
+    g.close()
+
+
 @pytest.mark.parametrize("precision", [64, 32])
 @pytest.mark.parametrize("case", ["gh_8", "gh_28", "nc_16"])
 def test_axis_sums_match_the_general_path(case, precision):
