@@ -1100,7 +1100,7 @@ struct mlvs_ctx_s {
     int chunk_env = 0;                 // MLVS_CHUNK: a fixed chunk instead of the chosen one
     int nch = 1;                       // chunks of the largest level
     bool tensor = false;               // the level set is the base grid alone (see LevelDesc::axes)
-    double* d_cpar = nullptr;          // [n_cells][NFP] cell records (tensor level sets)
+    double* d_cpar = nullptr;          // [n_cells][NFP] cell records
     double* d_fpar = nullptr;          // [faces + boundary faces][NFP] face records
     bool mom_valid = false;            // d_cmom matches the stored state
     BCDev* d_bcs = nullptr;
@@ -1788,11 +1788,8 @@ void build_items(mlvs_ctx c) {
     c->prep_valid = false;
     c->d_fpar = static_cast<double*>(c->dm.alloc(sizeof(double) * NFP * (size_t)std::max(nF_all, 1)));
     c->item_allocs.push_back(c->d_fpar);
-    c->d_cpar = nullptr;
-    if (c->tensor) {
-        c->d_cpar = static_cast<double*>(c->dm.alloc(sizeof(double) * NFP * (size_t)std::max(n, 1)));
-        c->item_allocs.push_back(c->d_cpar);
-    }
+    c->d_cpar = static_cast<double*>(c->dm.alloc(sizeof(double) * NFP * (size_t)std::max(n, 1)));
+    c->item_allocs.push_back(c->d_cpar);
     update_step_args(c);                  // last: every pointer it records is allocated
 }
 
@@ -3598,7 +3595,7 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
     const int nf = c->n_faces + c->n_bfaces;
     switch (stage) {
     case 0: return launch_cell_prep(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->ph,
-                                    c->d_params, c->d_cmom, c->chunk, c->d_cpar, c->variant[0]);
+                                    c->d_params, c->d_cmom, c->chunk, c->d_cpar, c->tensor, c->variant[0]);
     case 1: return launch_ghost(c->prec, c->st, c->d_lv, c->d_ghosts, c->n_ghosts, c->d_cell_lev, c->d_cell_slot,
                                 c->d_params, c->ph, c->d_neg);
     case 2: case 7: {
@@ -3614,8 +3611,8 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
     case 4: return launch_xface(c->prec, on ? on : c->st, c->d_lv, c->d_xfaces, c->n_xfaces, c->d_cell_slot, c->d_cell_nbr,
                                 c->d_geom, c->d_params, c->ph, c->d_neg, c->variant[4]);
     case 5: return launch_update(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->d_geom,
-                                 c->d_cell_frow, c->d_faces, c->d_fpar, c->d_params, c->ph, c->d_cmom, c->chunk,
-                                 c->nch, c->variant[5]);
+                                 c->d_cell_frow, c->d_faces, c->d_fpar, c->d_cpar, c->d_params, c->ph, c->d_cmom,
+                                 c->chunk, c->nch, c->variant[5]);
     case 9: return launch_step_persistent(c->prec, c->st, c->d_args, c->d_sync, c->ph, c->variant[9],
                                           &c->persistent_grid);
     case 8: return launch_update_cell(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n,

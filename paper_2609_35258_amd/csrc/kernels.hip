@@ -164,6 +164,33 @@ __device__ __forceinline__ void load_xy(const LevelDesc& L, int i, double& x, do
     }
 }
 
+// Values a lane holds of one row: consecutive points, one 8-byte access.
+template <typename S>
+constexpr int VW = 8 / (int)sizeof(S);
+template <typename T, int N>
+using vec = T __attribute__((ext_vector_type(N)));
+
+// N consecutive values at element i (a multiple of N) of a row whose address
+// is uniform: scalar base and one 32-bit byte offset per lane, shared by all
+// rows read at that index.
+template <int N, typename T>
+__device__ __forceinline__ vec<T, N> ldv(gptr<const T> row, int i) {
+    return *(gptr<const vec<T, N>>)((gptr<const char>)row + (unsigned)i * (unsigned)sizeof(T));
+}
+template <int N, typename T>
+__device__ __forceinline__ void stv(gptr<T> row, int i, vec<T, N> x) {
+    *(gptr<vec<T, N>>)((gptr<char>)row + (unsigned)i * (unsigned)sizeof(T)) = x;
+}
+// ... streamed past the caches, where nothing reads the row again soon.
+template <int N, typename T>
+__device__ __forceinline__ vec<T, N> ldv_nt(gptr<const T> row, int i) {
+    return __builtin_nontemporal_load((gptr<const vec<T, N>>)((gptr<const char>)row + (unsigned)i * (unsigned)sizeof(T)));
+}
+template <int N, typename T>
+__device__ __forceinline__ void stv_nt(gptr<T> row, int i, vec<T, N> x) {
+    __builtin_nontemporal_store(x, (gptr<vec<T, N>>)((gptr<char>)row + (unsigned)i * (unsigned)sizeof(T)));
+}
+
 // Gaussian elimination with partial pivoting on a register-resident N x N
 // system (all indices compile-time: no scratch).  The pivot search keeps the
 // first largest entry, as LAPACK does.  A singular system yields a = 0.
@@ -314,6 +341,94 @@ __device__ __forceinline__ void eq_eval(const Eq<C>& e, C x, C y, C& g, C& h) {
     }
 }
 
+// The target as the velocity passes of a step evaluate it: Eq with the constants
+// of the exponential and the two polynomials folded, the weight it enters with
+// taken into rn, and the correction factor applied once, to the Maxwellian: 22
+// instructions a point in FP32 where eq_eval takes 33.  It is also the record
+// that a face's or cell's target stage leaves for those passes, in the storage
+// precision, so that they load scalars ready for use.  kind: see the face
+// records; c1: the weight of the row value beside the target.  The products and
+// sums are spelled out, so that every pass rounds alike.
+template <typename C>
+struct StepEq {
+    C rn, ux, uy, k, iRT, RT, Xqx, Xqy, hiRT, hD, cK, Dp2;
+    C b0, b1, b2, b3;
+    C e4, e5, e6, e7, cKRT;
+    C c1;
+    int kind, corr, c8, pad;
+};
+
+constexpr double LOG2E = 1.4426950408889634074;
+
+// k: FP32 storage uses the hardware base-2 exponential, FP64 exp().  One item
+// per lane.
+template <typename C>
+__device__ __forceinline__ StepEq<C> step_eq_lane(const Eq<double>& d, double c1, double scale, int kind) {
+    StepEq<C> e;
+    e.rn = (C)(scale * d.rn); e.ux = (C)d.ux; e.uy = (C)d.uy;
+    e.k = (C)(sizeof(C) == 4 ? -d.i2RT * LOG2E : -d.i2RT);
+    e.iRT = (C)d.iRT; e.RT = (C)d.RT; e.Xqx = (C)d.Xqx; e.Xqy = (C)d.Xqy;
+    e.hiRT = (C)(d.cK * d.iRT); e.hD = (C)(d.Dd * d.cK + d.K2); e.cK = (C)d.cK; e.Dp2 = (C)d.Dp2;
+    e.b0 = (C)d.b0; e.b1 = (C)d.b1; e.b2 = (C)d.b2; e.b3 = (C)d.b3;
+    e.e4 = (C)d.e4; e.e5 = (C)d.e5; e.e6 = (C)d.e6; e.e7 = (C)d.e7; e.cKRT = (C)d.cKRT;
+    e.c1 = (C)c1;
+    e.kind = kind;
+    e.corr = d.corr;
+    e.c8 = d.c8;
+    e.pad = 0;
+    return e;
+}
+// ... one item per wave.
+template <typename C>
+__device__ __forceinline__ StepEq<C> uni_eq(StepEq<C> e) {
+    e.rn = uni(e.rn); e.ux = uni(e.ux); e.uy = uni(e.uy); e.k = uni(e.k); e.iRT = uni(e.iRT); e.RT = uni(e.RT);
+    e.Xqx = uni(e.Xqx); e.Xqy = uni(e.Xqy); e.hiRT = uni(e.hiRT); e.hD = uni(e.hD); e.cK = uni(e.cK);
+    e.Dp2 = uni(e.Dp2); e.b0 = uni(e.b0); e.b1 = uni(e.b1); e.b2 = uni(e.b2); e.b3 = uni(e.b3);
+    e.e4 = uni(e.e4); e.e5 = uni(e.e5); e.e6 = uni(e.e6); e.e7 = uni(e.e7); e.cKRT = uni(e.cKRT); e.c1 = uni(e.c1);
+    e.kind = __builtin_amdgcn_readfirstlane(e.kind);
+    e.corr = __builtin_amdgcn_readfirstlane(e.corr);
+    e.c8 = __builtin_amdgcn_readfirstlane(e.c8);
+    return e;
+}
+template <typename C>
+__device__ __forceinline__ StepEq<C> step_eq(const Eq<double>& d, double c1 = 0.0, double scale = 1.0) {
+    return uni_eq(step_eq_lane<C>(d, c1, scale, 0));
+}
+
+__device__ __forceinline__ float kexp(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ double kexp(double x) { return exp(x); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// g and h of the target at (x, y); x2 = x^2 + y^2.
+template <typename C>
+__device__ __forceinline__ void step_eval(const StepEq<C>& e, C x, C y, C x2, C& g, C& h) {
+    const C cx = x - e.ux, cy = y - e.uy;
+    const C c2 = fma_(cx, cx, cy * cy);
+    C ge = e.rn * kexp(c2 * e.k);
+    const C Xc = fma_(cx, e.Xqx, cy * e.Xqy);
+    if (e.corr) {
+        C f = fma_(e.b1, x, fma_(e.b2, y, fma_(e.b3, x2, e.b0)));
+        if (e.c8) {
+            f = fma_(fma_(e.e4, cx, e.e5 * cy), e.cKRT + c2, f);
+            f = fma_(e.e6, fma_(cx, cx, -(cy * cy)), f);
+            f = fma_(e.e7, cx * cy, f);
+        }
+        ge *= f;
+    }
+    g = ge * fma_(Xc, fma_(c2, e.iRT, -e.Dp2), C(1));
+    h = ge * e.RT * fma_(Xc, fma_(c2, e.hiRT, -e.hD), e.cK);
+}
+
+// Either form by name of its parameters: the velocity sums of a correction use
+// the evaluation that the corrected target will be evaluated with.
+template <typename C>
+__device__ __forceinline__ void target_eval(const Eq<C>& e, C x, C y, C& g, C& h) { eq_eval<C>(e, x, y, g, h); }
+template <typename C>
+__device__ __forceinline__ void target_eval(const StepEq<C>& e, C x, C y, C& g, C& h) {
+    step_eval<C>(e, x, y, fma_(x, x, y * y), g, h);
+}
+
 // Velocity points of one item are visited in chunks of U points per lane:
 // every load of a chunk is issued before any of its arithmetic, so U loads
 // per lane are in flight.  Indices past the end are clamped to the last point
@@ -323,8 +438,8 @@ __device__ __forceinline__ int clampi(int i, int N) { return i < N ? i : N - 1; 
 // Compatibility correction (Sec. 3.3.1), part 1: the thirteen velocity sums of
 // the uncorrected target over the level that the 4x4 system needs (wave per
 // item; every lane receives the totals).
-template <typename S, int U>
-__device__ __forceinline__ void compat_sums(const LevelDesc& L, const Eq<S>& eu, double (&s)[13]) {
+template <typename S, int U, typename E>
+__device__ __forceinline__ void compat_sums(const LevelDesc& L, const E& eu, double (&s)[13]) {
 #pragma unroll
     for (int k = 0; k < 13; ++k) s[k] = 0.0;
     const int N = L.N;
@@ -340,7 +455,7 @@ __device__ __forceinline__ void compat_sums(const LevelDesc& L, const Eq<S>& eu,
         for (int q = 0; q < U; ++q) {
             const double x = xv[q], y = yv[q];
             S g, h;
-            eq_eval<S>(eu, (S)x, (S)y, g, h);
+            target_eval<S>(eu, (S)x, (S)y, g, h);
             const double wg = wv[q] * (double)g, wh = wv[q] * (double)h;
             const double x2 = x * x + y * y;
             s[0] += wg; s[1] += wg * x; s[2] += wg * y; s[3] += wg * x * x; s[4] += wg * x * y;
@@ -442,7 +557,8 @@ __device__ __forceinline__ void compat_axes(const LevelDesc& L, const Eq<double>
                                             double T, const Phys& ph, int lg, double* a_out) {
     constexpr bool F32 = sizeof(S) == 4;
     auto r = [](double q) { return F32 ? (double)(float)q : q; };
-    const double ue = r(e.ux), ve = r(e.uy), i2RT = r(e.i2RT), iRT = r(e.iRT);
+    const double ue = r(e.ux), ve = r(e.uy), iRT = r(e.iRT);
+    const double i2RT = F32 ? -r(-e.i2RT * LOG2E) / LOG2E : e.i2RT;     // as StepEq rounds it
     double A[8], B[8];
     axis_sums(L.axes, L.axes + L.nx, L.nx, ue, i2RT, F32, lg, A);
     axis_sums(L.axes + 2 * L.nx, L.axes + 2 * L.nx + L.ny, L.ny, ve, i2RT, F32, lg, B);
@@ -500,8 +616,8 @@ __device__ __forceinline__ void compat_axes(const LevelDesc& L, const Eq<double>
 // energy, the heat flux and a zero deviatoric stress.  Part 1 (wave per item):
 // A[k][m] = sum w (psi_g,k g_S + psi_h,k h_S) phi_m, row-major; column 0 holds
 // the target's own moments (phi_0 = 1).
-template <typename S, int U>
-__device__ __forceinline__ void compat_sums8(const LevelDesc& L, const Eq<S>& eu, double u, double v, double T,
+template <typename S, int U, typename E>
+__device__ __forceinline__ void compat_sums8(const LevelDesc& L, const E& eu, double u, double v, double T,
                                              const Phys& ph, double (&A)[64]) {
 #pragma unroll
     for (int k = 0; k < 64; ++k) A[k] = 0.0;
@@ -519,7 +635,7 @@ __device__ __forceinline__ void compat_sums8(const LevelDesc& L, const Eq<S>& eu
         for (int q = 0; q < U; ++q) {
             const double x = xv[q], y = yv[q];
             S g, h;
-            eq_eval<S>(eu, (S)x, (S)y, g, h);
+            target_eval<S>(eu, (S)x, (S)y, g, h);
             const double wg = wv[q] * (double)g, wh = wv[q] * (double)h;
             const double cx = x - u, cy = y - v, c2 = cx * cx + cy * cy, x2 = x * x + y * y;
             const double Ec = 0.5 * (cKRT + c2);
@@ -631,6 +747,9 @@ __device__ __forceinline__ CellState cell_state(const double* cm, const Phys& ph
     return c;
 }
 
+template <typename S>
+constexpr bool UPDATE_RE = false;
+
 // Cell stage: W, q, tau, compatibility coefficients (written to params) and
 // the rows phi_bar+ = alpha phi~ + beta phi_S* (Eq. g_h_eq_Pr with the
 // correction of Sec. 3.3.1).  The raw moments of g~, h~ come from cmom (the
@@ -638,37 +757,56 @@ __device__ __forceinline__ CellState cell_state(const double* cm, const Phys& ph
 // The phi_bar+ row of one cell (Eq. bar_phi_transport): phi_bar+ = alpha
 // phi~ + beta phi_S* at every point of its level, phi_S* the (corrected)
 // target e.
-template <typename S, int U>
-__device__ __forceinline__ void phibar_points(const LevelDesc& L, size_t row, const Eq<double>& ed, double alpha,
-                                              double beta) {
-    const int N = L.N;
+// The target in a face's or cell's record (layout FP_*).
+template <typename S>
+__device__ __forceinline__ void write_eq_record(double* o, const StepEq<S>& e) {
+    *reinterpret_cast<StepEq<S>*>(o + FP_EQ) = e;
+}
+template <typename S>
+__device__ __forceinline__ StepEq<S> read_eq_record(const double* o) {
+    return uni_eq(*reinterpret_cast<const StepEq<S>*>(o + FP_EQ));
+}
+
+// ST: rows too large for the caches, streamed past them.
+template <typename S, int U, bool ST>
+__device__ __forceinline__ void phibar_points(const LevelDesc& L, size_t row, const StepEq<S>& e) {
+    constexpr int V = VW<S>;
+    const int N = L.N, last = L.stride - V;
     auto g = rowp<S>(L.g, row);
     auto h = rowp<S>(L.h, row);
     auto fg = rowp<S>(L.fg, row);
     auto fh = rowp<S>(L.fh, row);
-    const Eq<S> e = eq_cast<S>(ed);
-    const S al = uni((S)alpha), be = uni((S)beta);
-    for (int i0 = lane_id(); i0 < N; i0 += WL * U) {
-        S gv[U], hv[U], xv[U], yv[U];
+    for (int b0 = 0; b0 < N; b0 += WL * V * U) {
+        vec<S, V> gv[U], hv[U], xv[U], yv[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int ic = clampi(i0 + q * WL, N);
-            gv[q] = g[ic]; hv[q] = h[ic];
-            double xd, yd;
-            load_xy<S>(L, ic, xd, yd);
-            xv[q] = (S)xd; yv[q] = (S)yd;
+            const int ic = min(b0 + V * (lane_id() + q * WL), last);
+            gv[q] = ST ? ldv_nt<V, S>(g, ic) : ldv<V, S>(g, ic);
+            hv[q] = ST ? ldv_nt<V, S>(h, ic) : ldv<V, S>(h, ic);
+            if constexpr (V == 2) {
+                const vec<float, 4> p = ldv<4, float>(gp(L.xy32), 2 * ic);
+                xv[q] = vec<S, V>{p[0], p[2]};
+                yv[q] = vec<S, V>{p[1], p[3]};
+            } else {
+                xv[q] = ldv<V, S>(gp((const S*)L.xi_x), ic);
+                yv[q] = ldv<V, S>(gp((const S*)L.xi_y), ic);
+            }
         }
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            S gs, hs;
-            eq_eval<S>(e, xv[q], yv[q], gs, hs);
-            gv[q] = al * gv[q] + be * gs;
-            hv[q] = al * hv[q] + be * hs;
-        }
+        for (int q = 0; q < U; ++q)
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                S gs, hs;
+                step_eval<S>(e, xv[q][v], yv[q][v], fma_(xv[q][v], xv[q][v], yv[q][v] * yv[q][v]), gs, hs);
+                gv[q][v] = fma_(e.c1, gv[q][v], gs);
+                hv[q][v] = fma_(e.c1, hv[q][v], hs);
+            }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int i = i0 + q * WL;
-            if (i < N) { fg[i] = gv[q]; fh[i] = hv[q]; }
+            const int i = b0 + V * (lane_id() + q * WL);
+            if (i >= N) continue;
+            stv<V, S>(fg, i, gv[q]);
+            stv<V, S>(fh, i, hv[q]);
         }
     }
 }
@@ -684,13 +822,13 @@ __device__ __forceinline__ void cell_target_wave(const LevelDesc& L, const CellS
     if (!ph.compat) return;
     if constexpr (CM == 8) {
         double A[64];
-        compat_sums8<S, U>(L, eq_cast<S>(e), cs.u, cs.v, cs.T, ph, A);
+        compat_sums8<S, U>(L, step_eq<S>(e), cs.u, cs.v, cs.T, ph, A);
         compat_from_sums8(A, cs.rho, cs.u, cs.v, cs.T, (1.0 - ph.Pr) * cs.qx, (1.0 - ph.Pr) * cs.qy, ph, a);
     } else if (L.axes) {
         compat_axes<S>(L, e, cs.rho, cs.u, cs.v, cs.T, ph, lane_id() & (AXG - 1), a);
     } else {
         double sm[13];
-        compat_sums<S, U>(L, eq_cast<S>(e), sm);
+        compat_sums<S, U>(L, step_eq<S>(e), sm);
         compat_from_sums(sm, cs.rho, cs.u, cs.v, cs.T, ph, a);
     }
     e = make_eq(cs.rho, cs.u, cs.v, cs.T, cs.qx, cs.qy, a, ph);
@@ -708,7 +846,8 @@ __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __rest
                                                          const int* __restrict__ cell_slot,
                                                          const int* __restrict__ order, int n_cells, Phys ph,
                                                          double* __restrict__ params,
-                                                         const double* __restrict__ cmom, int CH) {
+                                                         const double* __restrict__ cmom, int CH,
+                                                         double* __restrict__ cpar) {
     constexpr int NS = CM == 8 ? 64 : 13;      // compatibility sums per item
     __shared__ CellState sh_c[GW];
     __shared__ Eq<double> sh_e[GW];
@@ -735,9 +874,9 @@ __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __rest
                 double sm[NS];
                 if constexpr (CM == 8) {
                     const CellState& cs = sh_c[j];
-                    compat_sums8<S, U>(L, eq_cast<S>(sh_e[j]), cs.u, cs.v, cs.T, ph, sm);
+                    compat_sums8<S, U>(L, step_eq<S>(sh_e[j]), cs.u, cs.v, cs.T, ph, sm);
                 } else {
-                    compat_sums<S, U>(L, eq_cast<S>(sh_e[j]), sm);
+                    compat_sums<S, U>(L, step_eq<S>(sh_e[j]), sm);
                 }
                 if (lane_id() < NS) {
 #pragma unroll
@@ -768,35 +907,12 @@ __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __rest
             const int c = g0 + j < n_cells ? order[g0 + j] : n_cells;
             if (c >= n_cells) break;
             const LevelDesc& L = lvs[cell_lev[c]];
-            phibar_points<S, U>(L, (size_t)cell_slot[c] * L.stride, sh_e[j], sh_c[j].alpha, sh_c[j].beta);
+            const StepEq<S> e = step_eq<S>(sh_e[j], sh_c[j].alpha, sh_c[j].beta);
+            if (UPDATE_RE<S> && lane_id() == 0) write_eq_record<S>(cpar + (size_t)c * NFP, e);
+            phibar_points<S, U, true>(L, (size_t)cell_slot[c] * L.stride, e);
         }
         __syncthreads();
     }
-}
-
-// The record of an equation and two weights (layout FP_*): a face's target, or
-// a cell's.
-__device__ __forceinline__ void write_eq_record(double* o, double c1, double c2, const Eq<double>& e) {
-    o[FP_C1] = c1; o[FP_C2] = c2;
-    o[FP_RN] = e.rn; o[FP_UX] = e.ux; o[FP_UY] = e.uy; o[FP_I2RT] = e.i2RT; o[FP_RT] = e.RT;
-    o[FP_IRT] = e.iRT; o[FP_XQX] = e.Xqx; o[FP_XQY] = e.Xqy;
-    o[FP_B0] = e.b0; o[FP_B1] = e.b1; o[FP_B2] = e.b2; o[FP_B3] = e.b3;
-    o[FP_CORR] = e.corr ? 1.0 : 0.0;
-    o[FP_E4] = e.e4; o[FP_E5] = e.e5; o[FP_E6] = e.e6; o[FP_E7] = e.e7; o[FP_CKRT] = e.cKRT;
-    o[FP_C8] = e.c8 ? 1.0 : 0.0;
-}
-
-template <typename T>
-__device__ __forceinline__ Eq<double> read_eq_record(const T* fp, const Phys& ph) {
-    Eq<double> d;
-    d.rn = fp[FP_RN]; d.ux = fp[FP_UX]; d.uy = fp[FP_UY]; d.i2RT = fp[FP_I2RT]; d.RT = fp[FP_RT];
-    d.iRT = fp[FP_IRT]; d.Xqx = fp[FP_XQX]; d.Xqy = fp[FP_XQY];
-    d.b0 = fp[FP_B0]; d.b1 = fp[FP_B1]; d.b2 = fp[FP_B2]; d.b3 = fp[FP_B3];
-    d.cK = ph.K + 3.0 - ph.D; d.Dp2 = ph.D + 2.0; d.Dd = ph.D; d.K2 = 2.0 * ph.K;
-    d.corr = fp[FP_CORR] != 0.0;
-    d.e4 = fp[FP_E4]; d.e5 = fp[FP_E5]; d.e6 = fp[FP_E6]; d.e7 = fp[FP_E7]; d.cKRT = fp[FP_CKRT];
-    d.c8 = fp[FP_C8] != 0.0;
-    return d;
 }
 
 // Cell stage on the tensor base grid, where the correction costs axis sums
@@ -823,7 +939,7 @@ __global__ __launch_bounds__(BS) void k_cell_target_axes(const LevelDesc* __rest
         }
         if (lg == 0) {
             write_params(params + (size_t)c * NPARAM, cs, a);
-            write_eq_record(cpar + (size_t)c * NFP, cs.alpha, cs.beta, e);
+            write_eq_record<S>(cpar + (size_t)c * NFP, step_eq_lane<S>(e, cs.alpha, cs.beta, 0));
         }
     }
 }
@@ -831,12 +947,11 @@ __global__ __launch_bounds__(BS) void k_cell_target_axes(const LevelDesc* __rest
 template <typename S, int U, int MINW>
 __global__ __launch_bounds__(BS, MINW) void k_phibar(const LevelDesc* __restrict__ lvs, const int* __restrict__ cell_lev,
                                                      const int* __restrict__ cell_slot, const int* __restrict__ order,
-                                                     int n_cells, Phys ph, const double* __restrict__ cpar) {
+                                                     int n_cells, const double* __restrict__ cpar) {
     for (int it = item0(); it < n_cells; it += istride()) {
         const int c = order[it];
         const LevelDesc& L = lvs[cell_lev[c]];
-        const double* fp = cpar + (size_t)c * NFP;
-        phibar_points<S, U>(L, (size_t)cell_slot[c] * L.stride, read_eq_record(fp, ph), fp[FP_C1], fp[FP_C2]);
+        phibar_points<S, U, true>(L, (size_t)cell_slot[c] * L.stride, read_eq_record<S>(cpar + (size_t)c * NFP));
     }
 }
 
@@ -863,18 +978,26 @@ __global__ __launch_bounds__(BS) void k_raw_moments(const LevelDesc* __restrict_
         double m[11];
 #pragma unroll
         for (int j = 0; j < 11; ++j) m[j] = 0.0;
-        for (int i0 = beg + lane_id(); i0 < end; i0 += WL * U) {
-            S gv[U], hv[U];
-            double xv[U], yv[U], wv[U];
+        constexpr int V = VW<S>;           // in the order of the update's sums
+        const int last = L.stride - V;
+        for (int b0 = beg; b0 < end; b0 += WL * V * U) {
+            vec<S, V> gv[U], hv[U];
+            vec<double, V> xv[U], yv[U], wv[U];
 #pragma unroll
             for (int q = 0; q < U; ++q) {
-                const int i = i0 + q * WL, ic = clampi(i, end);
-                gv[q] = g[ic]; hv[q] = h[ic];
-                xv[q] = gp(L.xi_x)[ic]; yv[q] = gp(L.xi_y)[ic];
-                wv[q] = i < end ? gp(L.w)[ic] : 0.0;
+                const int ic = min(b0 + V * (lane_id() + q * WL), last);
+                gv[q] = ldv<V, S>(g, ic); hv[q] = ldv<V, S>(h, ic);
+                xv[q] = ldv<V, double>(gp(L.xi_x), ic);
+                yv[q] = ldv<V, double>(gp(L.xi_y), ic);
+                wv[q] = ldv<V, double>(gp(L.w), ic);
             }
 #pragma unroll
-            for (int q = 0; q < U; ++q) acc_raw<S>(m, wv[q], xv[q] - u0, yv[q] - v0, gv[q], hv[q]);
+            for (int q = 0; q < U; ++q)
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const bool in = b0 + V * (lane_id() + q * WL) + v < end;
+                    acc_raw<S>(m, wv[q][v], xv[q][v] - u0, yv[q][v] - v0, in ? gv[q][v] : S(0), in ? hv[q][v] : S(0));
+                }
         }
         wave_sum<11>(m);
         if (lane_id() == 0) {
@@ -1378,24 +1501,6 @@ __device__ __forceinline__ void stencil_slope(const USide<S>& a, const S (&v)[5]
     venkat_slope<S>(a.lx, a.ly, a.fx, a.fy, a.eps2, v, sx, sy);
 }
 
-// Values a lane holds of one row: consecutive points, one 8-byte access.
-template <typename S>
-constexpr int VW = 8 / (int)sizeof(S);
-template <typename T, int N>
-using vec = T __attribute__((ext_vector_type(N)));
-
-// N consecutive values at element i (a multiple of N) of a row whose address
-// is uniform: scalar base and one 32-bit byte offset per lane, shared by all
-// rows read at that index.
-template <int N, typename T>
-__device__ __forceinline__ vec<T, N> ldv(gptr<const T> row, int i) {
-    return *(gptr<const vec<T, N>>)((gptr<const char>)row + (unsigned)i * (unsigned)sizeof(T));
-}
-template <int N, typename T>
-__device__ __forceinline__ void stv(gptr<T> row, int i, vec<T, N> x) {
-    __builtin_nontemporal_store(x, (gptr<vec<T, N>>)((gptr<char>)row + (unsigned)i * (unsigned)sizeof(T)));
-}
-
 // Face stage, part 1 (reconstruction): the interface values phi_bar_f =
 // phi_bar+_up + (x_f - x_up - xi s) . sigma_up of the same-level and boundary
 // faces (both sides averaged where xi . n = 0), and the eleven raw moments of
@@ -1593,8 +1698,8 @@ __device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const
                 // one slot, left by all points of the batch
                 const int k = PER * n + s1 * (PER - 1);
                 reach(sl, e[n]);
-                stv<V>(sl.rg, i, e[n][0]);
-                stv<V>(sl.rh, i, e[n][1]);
+                stv_nt<V>(sl.rg, i, e[n][0]);
+                stv_nt<V>(sl.rh, i, e[n][1]);
                 if (stores >= 0) stores += 2;
                 act[n] = true;
                 if (own[n] != k) {
@@ -1831,11 +1936,13 @@ __device__ __forceinline__ double wall_inflow(const LevelDesc& L, const FaceItem
     return m1[0];
 }
 
-// The record the update reads for one face (layout FP_*).
-__device__ __forceinline__ void write_face_record(double* o, double kind, const FaceItem& F, double c1, double c2,
+// The record the update reads for one face (layout FP_*); c1, c2: the weights
+// of the row value and of the target.
+template <typename S>
+__device__ __forceinline__ void write_face_record(double* o, int kind, const FaceItem& F, double c1, double c2,
                                                   const Eq<double>& e) {
-    o[FP_KIND] = kind; o[FP_ROW] = (double)F.row; o[FP_NX] = F.nx; o[FP_NY] = F.ny;
-    write_eq_record(o, c1, c2, e);
+    o[FP_NX] = F.nx; o[FP_NY] = F.ny;
+    write_eq_record<S>(o, step_eq_lane<S>(e, c1, c2, kind));
 }
 
 template <typename S, int U, int MINW, int CM>
@@ -1884,9 +1991,9 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
                     double sm[NS];
                     if constexpr (CM == 8) {
                         const FaceState& fs = sh_f[j];
-                        compat_sums8<S, U>(L, eq_cast<S>(sh_e[j]), fs.u, fs.v, fs.T, ph, sm);
+                        compat_sums8<S, U>(L, step_eq<S>(sh_e[j]), fs.u, fs.v, fs.T, ph, sm);
                     } else {
-                        compat_sums<S, U>(L, eq_cast<S>(sh_e[j]), sm);
+                        compat_sums<S, U>(L, step_eq<S>(sh_e[j]), sm);
                     }
                     if (lane_id() < NS) {
 #pragma unroll
@@ -1905,7 +2012,8 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
             const FaceItem F = items[g0 + t];
             FaceState fs = sh_f[t];
             Eq<double> e = sh_e[t];
-            double kind = 0.0, c1 = fs.c1, c2 = fs.c2;
+            int kind = 0;
+            double c1 = fs.c1, c2 = fs.c2;
             if (F.R >= 0) {
                 if (ph.compat && ph.face_compat) {
                     double a[8];
@@ -1920,10 +2028,10 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
                 c2 *= F.area;
             } else {
                 const BCDev bc = bcs[-1 - F.R];
-                kind = (double)bc.kind;
+                kind = bc.kind;
                 if (bc.kind == 1) c2 = F.area * (-sh_m[t][0] / sh_m[t][1]);
             }
-            write_face_record(fpar + (size_t)(g0 + t) * NFP, kind, F, c1, c2, e);
+            write_face_record<S>(fpar + (size_t)(g0 + t) * NFP, kind, F, c1, c2, e);
         }
         __syncthreads();
     }
@@ -1943,7 +2051,8 @@ __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ 
         const LevelDesc& L = lvs[F.lev];
         double m[NFMOM];
         face_moments(fmom, f, nF, F, L.N, CH, m);
-        double kind = 0.0, c1, c2;
+        int kind = 0;
+        double c1, c2;
         Eq<double> e;
         if (F.R >= 0) {
             const FaceState fs = face_state(m, m[M_U0], m[M_V0], ph);
@@ -1952,14 +2061,14 @@ __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ 
                 double a[8];
                 if constexpr (CM == 8) {
                     double A[64];
-                    compat_sums8<S, U>(L, eq_cast<S>(e), fs.u, fs.v, fs.T, ph, A);
+                    compat_sums8<S, U>(L, step_eq<S>(e), fs.u, fs.v, fs.T, ph, A);
                     compat_from_sums8(A, fs.rho, fs.u, fs.v, fs.T, (1.0 - ph.Pr) * fs.qx, (1.0 - ph.Pr) * fs.qy,
                                       ph, a);
                 } else if (L.axes) {
                     compat_axes<S>(L, e, fs.rho, fs.u, fs.v, fs.T, ph, lane_id() & (AXG - 1), a);
                 } else {
                     double sm[13];
-                    compat_sums<S, U>(L, eq_cast<S>(e), sm);
+                    compat_sums<S, U>(L, step_eq<S>(e), sm);
                     compat_from_sums(sm, fs.rho, fs.u, fs.v, fs.T, ph, a);
                 }
                 e = make_eq(fs.rho, fs.u, fs.v, fs.T, fs.qx, fs.qy, a, ph);
@@ -1968,14 +2077,14 @@ __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ 
             c2 = fs.c2 * F.area;
         } else {
             const BCDev bc = bcs[-1 - F.R];
-            kind = (double)bc.kind;
+            kind = bc.kind;
             e = bc.kind == 2 ? make_eq(bc.rho, bc.u, bc.v, bc.T, 0.0, 0.0, nullptr, ph)
                              : make_eq(1.0, bc.u, bc.v, bc.T, 0.0, 0.0, nullptr, ph);
             c1 = F.area;
             c2 = F.area;
             if (bc.kind == 1) c2 = F.area * (-m[0] / wall_inflow<S, U>(L, F, eq_cast<S>(e)));
         }
-        if (lane_id() == 0) write_face_record(fpar + (size_t)f * NFP, kind, F, c1, c2, e);
+        if (lane_id() == 0) write_face_record<S>(fpar + (size_t)f * NFP, kind, F, c1, c2, e);
     }
 }
 
@@ -2007,13 +2116,8 @@ __global__ __launch_bounds__(BS) void k_face_target_axes(const LevelDesc* __rest
             compat_axes<S>(L, e, fs.rho, fs.u, fs.v, fs.T, ph, lg, a);
             e = make_eq(fs.rho, fs.u, fs.v, fs.T, fs.qx, fs.qy, a, ph);
         }
-        if (lg == 0) write_face_record(fpar + (size_t)f * NFP, 0.0, F, fs.c1 * F.area, fs.c2 * F.area, e);
+        if (lg == 0) write_face_record<S>(fpar + (size_t)f * NFP, 0, F, fs.c1 * F.area, fs.c2 * F.area, e);
     }
-}
-
-template <typename S>
-__device__ __forceinline__ Eq<S> load_face_eq(const double* fp, const Phys& ph) {
-    return eq_cast<S>(read_eq_record(fp, ph));
 }
 
 // ---------------------------------------------------------------------------
@@ -2029,11 +2133,20 @@ __device__ __forceinline__ Eq<S> load_face_eq(const double* fp, const Phys& ph) 
 // ---------------------------------------------------------------------------
 // One cell over points [beg, N) of its level; m: the raw moments of the new
 // state about the step's cell velocity (u0, v0).
-template <typename S, int U>
+// ST: the staged step, whose rows are too large for the caches: the cell's own
+// rows stream past them and leave them to the face rows, which two cells read.
+// Bound by memory traffic (16 of 40 bytes a point are the face rows' in FP32),
+// at three quarters of the vector issue slots before the target's constants
+// were folded and the records kept in storage precision.  Lanes take the points
+// in pairs in FP32 (8-byte accesses).  Cylinder 256 x 128, 101^2, FP32: 3.39
+// -> 2.90 ms; with merged levels .535 -> .437; two-cavity .859 -> .761 ms.
+template <typename S, int U, bool ST>
 __device__ __forceinline__ void update_points(const LevelDesc& L, int c, const int* cell_slot, const CellGeom* geom,
                                               const int* cell_frow, const FaceItem* items, const double* fpar,
-                                              const double* params, const Phys& ph, int beg, int N,
+                                              const double* cpar, const double* params, const Phys& ph, int beg, int N,
                                               double (&m)[11], double& u0, double& v0) {
+    constexpr int V = VW<S>;
+    constexpr bool RE = ST && UPDATE_RE<S>;
     const S c43 = (S)(4.0 / 3.0), c13 = (S)(1.0 / 3.0);
     const size_t row = (size_t)cell_slot[c] * L.stride;
     auto g = rowp<S>(L.g, row);
@@ -2046,93 +2159,126 @@ __device__ __forceinline__ void update_points(const LevelDesc& L, int c, const i
     const S kv = uni((S)(ph.dt / geom[c].vol));
     u0 = params[(size_t)c * NPARAM + P_U];
     v0 = params[(size_t)c * NPARAM + P_V];
+    StepEq<S> ec;
+    if constexpr (RE) ec = read_eq_record<S>(cpar + (size_t)c * NFP);
+    const int last = L.stride - V;
 #pragma unroll
     for (int k = 0; k < 11; ++k) m[k] = 0.0;
-    for (int i0 = beg + lane_id(); i0 < N; i0 += WL * U) {
-        double xv[U], yv[U], wv[U];
-        S bg[U], bh[U], go[U], ho[U], ag[U], ah[U];
+    for (int b0 = beg; b0 < N; b0 += WL * V * U) {
+        vec<double, V> xv[U], yv[U], wv[U];
+        vec<S, V> bg[U], bh[U], go[U], ho[U], ag[U], ah[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int i = i0 + q * WL, ic = clampi(i, N);
-            xv[q] = gp(L.xi_x)[ic]; yv[q] = gp(L.xi_y)[ic];
-            wv[q] = i < N ? gp(L.w)[ic] : 0.0;
-            bg[q] = fg[ic]; bh[q] = fh[ic];
-            go[q] = g[ic]; ho[q] = h[ic];
+            const int ic = min(b0 + V * (lane_id() + q * WL), last);
+            go[q] = ST ? ldv_nt<V, S>(g, ic) : ldv<V, S>(g, ic);
+            ho[q] = ST ? ldv_nt<V, S>(h, ic) : ldv<V, S>(h, ic);
+            if constexpr (!RE) {
+                bg[q] = ST ? ldv_nt<V, S>(fg, ic) : ldv<V, S>(fg, ic);
+                bh[q] = ST ? ldv_nt<V, S>(fh, ic) : ldv<V, S>(fh, ic);
+            }
+            xv[q] = ldv<V, double>(gp(L.xi_x), ic);
+            yv[q] = ldv<V, double>(gp(L.xi_y), ic);
+            wv[q] = ldv<V, double>(gp(L.w), ic);
             ag[q] = S(0); ah[q] = S(0);
+        }
+        vec<S, V> xs[U], ys[U], x2[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                xs[q][v] = (S)xv[q][v];
+                ys[q][v] = (S)yv[q][v];
+                x2[q][v] = fma_(xs[q][v], xs[q][v], ys[q][v] * ys[q][v]);
+            }
+        if constexpr (RE) {
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    S gs, hs;
+                    step_eval<S>(ec, xs[q][v], ys[q][v], x2[q][v], gs, hs);
+                    bg[q][v] = fma_(ec.c1, go[q][v], gs);
+                    bh[q][v] = fma_(ec.c1, ho[q][v], hs);
+                }
         }
 #pragma unroll
         for (int f = 0; f < 4; ++f) {
             const int cd = code[f];
             if (cd < 0) continue;
-            const S sgn = (cd & 1) ? S(-1) : S(1);
-            if (cd & 2) {
-                const size_t r = (size_t)(cd >> 2) * L.stride;
-                auto Fg = rowp<S>(L.Fg, r);
-                auto Fh = rowp<S>(L.Fh, r);
-                S vg[U], vh[U];
+            const bool final = cd & 2;
+            const size_t r = (size_t)(final ? cd >> 2 : items[cd >> 2].row) * L.stride;
+            auto Fg = rowp<S>(L.Fg, r);
+            auto Fh = rowp<S>(L.Fh, r);
+            vec<S, V> vg[U], vh[U];
 #pragma unroll
-                for (int q = 0; q < U; ++q) {
-                    const int ic = clampi(i0 + q * WL, N);
-                    vg[q] = Fg[ic]; vh[q] = Fh[ic];
-                }
+            for (int q = 0; q < U; ++q) {
+                const int ic = min(b0 + V * (lane_id() + q * WL), last);
+                vg[q] = ldv<V, S>(Fg, ic);
+                vh[q] = ldv<V, S>(Fh, ic);
+            }
+            if (final) {
+                const S sgn = (cd & 1) ? S(-1) : S(1);
 #pragma unroll
                 for (int q = 0; q < U; ++q) { ag[q] += sgn * vg[q]; ah[q] += sgn * vh[q]; }
                 continue;
             }
             const double* fp = fpar + (size_t)(cd >> 2) * NFP;
-            const int kind = __builtin_amdgcn_readfirstlane((int)fp[FP_KIND]);
-            const size_t r = (size_t)items[cd >> 2].row * L.stride;
-            auto Fg = rowp<S>(L.Fg, r);
-            auto Fh = rowp<S>(L.Fh, r);
-            const double nx = fp[FP_NX], ny = fp[FP_NY];
-            const S k1 = uni((S)fp[FP_C1]), k2 = uni((S)fp[FP_C2]);
-            S vg[U], vh[U];
+            const double sg = (cd & 1) ? -1.0 : 1.0;
+            const double nx = sg * fp[FP_NX], ny = sg * fp[FP_NY];     // exact
+            const StepEq<S> e = read_eq_record<S>(fp);
+            if (e.kind == 0) {
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const int ic = clampi(i0 + q * WL, N);
-                vg[q] = Fg[ic]; vh[q] = Fh[ic];
-            }
-            if (kind == 3) {            // outflow: incoming = the cell's phi_bar+
+                for (int q = 0; q < U; ++q)
 #pragma unroll
-                for (int q = 0; q < U; ++q) {
-                    const double dnd = xv[q] * nx + yv[q] * ny;
-                    const S dn = (S)dnd;
-                    const S pg = dnd > 0 ? vg[q] : bg[q], ph_ = dnd > 0 ? vh[q] : bh[q];
-                    ag[q] += sgn * (k1 * dn * pg);
-                    ah[q] += sgn * (k1 * dn * ph_);
-                }
+                    for (int v = 0; v < V; ++v) {
+                        const S dn = (S)(xv[q][v] * nx + yv[q][v] * ny);
+                        S gs, hs;
+                        step_eval<S>(e, xs[q][v], ys[q][v], x2[q][v], gs, hs);
+                        ag[q][v] = fma_(dn, fma_(e.c1, vg[q][v], gs), ag[q][v]);
+                        ah[q][v] = fma_(dn, fma_(e.c1, vh[q][v], hs), ah[q][v]);
+                    }
                 continue;
             }
-            const Eq<S> e = load_face_eq<S>(fp, ph);
+            // boundary: the row where the face is left, else the target, or at
+            // an outflow (kind 3) the cell's phi_bar+
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const double dnd = xv[q] * nx + yv[q] * ny;
-                const S dn = (S)dnd;
-                S gs, hs;
-                eq_eval<S>(e, (S)xv[q], (S)yv[q], gs, hs);
-                S pg, ph_;
-                if (kind == 0) {
-                    pg = k1 * vg[q] + k2 * gs;
-                    ph_ = k1 * vh[q] + k2 * hs;
-                } else {
-                    pg = dnd > 0 ? k1 * vg[q] : k2 * gs;
-                    ph_ = dnd > 0 ? k1 * vh[q] : k2 * hs;
+            for (int q = 0; q < U; ++q)
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const double dnd = xv[q][v] * nx + yv[q][v] * ny;
+                    const S dn = (S)dnd;
+                    const bool out = (cd & 1) ? dnd < 0.0 : dnd > 0.0;
+                    S pg = e.c1 * (out ? vg[q][v] : bg[q][v]), qh = e.c1 * (out ? vh[q][v] : bh[q][v]);
+                    if (e.kind != 3) {
+                        S gs, hs;
+                        step_eval<S>(e, xs[q][v], ys[q][v], x2[q][v], gs, hs);
+                        pg = out ? pg : gs;
+                        qh = out ? qh : hs;
+                    }
+                    ag[q][v] = fma_(dn, pg, ag[q][v]);
+                    ah[q][v] = fma_(dn, qh, ah[q][v]);
                 }
-                ag[q] += sgn * (dn * pg);
-                ah[q] += sgn * (dn * ph_);
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int i = b0 + V * (lane_id() + q * WL);
+            vec<S, V> gn, hn;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                gn[v] = fma_(-kv, ag[q][v], fma_(c43, bg[q][v], -c13 * go[q][v]));
+                hn[v] = fma_(-kv, ah[q][v], fma_(c43, bh[q][v], -c13 * ho[q][v]));
             }
-        }
-        S gn[U], hn[U];
+            if (i < N) {
+                if (ST) { stv_nt<V, S>(g, i, gn); stv_nt<V, S>(h, i, hn); }
+                else { stv<V, S>(g, i, gn); stv<V, S>(h, i, hn); }
+            }
+            // past the end: rows hold anything there, and the weight may be a
+            // next chunk's
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-            gn[q] = c43 * bg[q] - c13 * go[q] - kv * ag[q];
-            hn[q] = c43 * bh[q] - c13 * ho[q] - kv * ah[q];
-        }
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int i = i0 + q * WL;
-            if (i < N) { g[i] = gn[q]; h[i] = hn[q]; }
-            acc_raw<S>(m, wv[q], xv[q] - u0, yv[q] - v0, gn[q], hn[q]);
+            for (int v = 0; v < V; ++v) {
+                const bool in = i + v < N;
+                acc_raw<S>(m, wv[q][v], xv[q][v] - u0, yv[q][v] - v0, in ? gn[v] : S(0), in ? hn[v] : S(0));
+            }
         }
     }
 }
@@ -2146,6 +2292,7 @@ __global__ __launch_bounds__(BS, MINW) void k_update(const LevelDesc* __restrict
                                                      const int* __restrict__ cell_frow,
                                                      const FaceItem* __restrict__ items,
                                                      const double* __restrict__ fpar,
+                                                     const double* __restrict__ cpar,
                                                      const double* __restrict__ params, Phys ph,
                                                      double* __restrict__ cmom, int CH, int nch) {
     const int n = n_cells * nch;
@@ -2156,7 +2303,7 @@ __global__ __launch_bounds__(BS, MINW) void k_update(const LevelDesc* __restrict
         if (beg >= L.N) continue;
         const int N = min(L.N, beg + CH);      // end of this chunk
         double m[11], u0, v0;
-        update_points<S, U>(L, c, cell_slot, geom, cell_frow, items, fpar, params, ph, beg, N, m, u0, v0);
+        update_points<S, U, true>(L, c, cell_slot, geom, cell_frow, items, fpar, cpar, params, ph, beg, N, m, u0, v0);
         wave_sum<11>(m);
         if (lane_id() == 0) {
             double* o = cmom + ((size_t)kc * n_cells + c) * NMOM;
@@ -2187,7 +2334,8 @@ __device__ __forceinline__ void update_cell_items(const LevelDesc* __restrict__ 
         const LevelDesc& L = lvs[cell_lev[c]];
         double cm[NMOM], u0, v0;
         double m[11];
-        update_points<S, U>(L, c, cell_slot, geom, cell_frow, items, fpar, params, ph, 0, L.N, m, u0, v0);
+        update_points<S, U, false>(L, c, cell_slot, geom, cell_frow, items, fpar, nullptr, params, ph, 0, L.N, m, u0,
+                                   v0);
         wave_sum<11>(m);
 #pragma unroll
         for (int k = 0; k < 11; ++k) cm[k] = m[k];
@@ -2204,7 +2352,7 @@ __device__ __forceinline__ void update_cell_items(const LevelDesc* __restrict__ 
         double a[8];
         cell_target_wave<S, U, CM>(L, cs, ph, e, a);
         if (lane_id() == 0) write_params(params + (size_t)c * NPARAM, cs, a);
-        phibar_points<S, U>(L, (size_t)cell_slot[c] * L.stride, e, cs.alpha, cs.beta);
+        phibar_points<S, U, false>(L, (size_t)cell_slot[c] * L.stride, step_eq<S>(e, cs.alpha, cs.beta));
     }
 }
 
@@ -2469,6 +2617,21 @@ constexpr int N_VARIANTS = 5;
         else MLVS_DISPATCH_VU1(prec, var, 4, KERNEL, __VA_ARGS__);                               \
     } while (0)
 
+// ... the update: its rows in flight take more than the 128 registers of four
+// waves per SIMD, and one batch of two points too few bytes in flight (cylinder
+// 256 x 128, 101^2, FP32: 3.08 ms in (1, 4) and (1, 3), 2.90 in (2, 3), 2.91 in
+// (2, 2), 2.88 in (4, 2); with merged levels .461, .437, .437 and .450).
+#define MLVS_DISPATCH_U(prec, var, KERNEL, ...)                                                  \
+    do {                                                                                        \
+        switch (var) {                                                                          \
+        case 0: MLVS_LAUNCH_UW(prec, KERNEL, 1, 4, __VA_ARGS__); break;                          \
+        case 2: MLVS_LAUNCH_UW(prec, KERNEL, 4, 2, __VA_ARGS__); break;                          \
+        case 3: MLVS_LAUNCH_UW(prec, KERNEL, 2, 2, __VA_ARGS__); break;                          \
+        case 4: MLVS_LAUNCH_UW(prec, KERNEL, 1, 3, __VA_ARGS__); break;                          \
+        default: MLVS_LAUNCH_UW(prec, KERNEL, 2, 3, __VA_ARGS__); break;                         \
+        }                                                                                       \
+    } while (0)
+
 // The cross-level faces are few, long items beside the same-level face stages:
 // FP64 takes two waves per SIMD (at four, 450 registers spill: cylinder 95 x 45,
 // 236 faces, 0.212 ms, 0.126 at two); FP32 is no slower at four (cylinder 256 x
@@ -2522,17 +2685,17 @@ static inline int axes_grid(int n) {
 
 hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev, const int* cell_slot,
                             const int* order, int n_cells, Phys ph, double* params, const double* cmom, int CH,
-                            double* cpar, int var) {
+                            double* cpar, bool tensor, int var) {
     if (n_cells <= 0) return hipSuccess;
-    if (cpar && ph.compat != 8) {
+    if (tensor && ph.compat != 8) {
         MLVS_DISPATCH(prec, k_cell_target_axes, dim3(axes_grid(n_cells)), dim3(BS), 0, st, lv, cell_lev, n_cells, ph,
                       params, cmom, CH, cpar);
         MLVS_DISPATCH_V(prec, var, k_phibar, dim3(grid_for(n_cells)), dim3(BS), 0, st, lv, cell_lev, cell_slot, order,
-                        n_cells, ph, cpar);
+                        n_cells, cpar);
         return hipGetLastError();
     }
     MLVS_DISPATCH_VC(prec, var, ph.compat, k_cell_prep, dim3(grid_for(n_cells, GW)), dim3(GBS), 0, st, lv, cell_lev,
-                     cell_slot, order, n_cells, ph, params, cmom, CH);
+                     cell_slot, order, n_cells, ph, params, cmom, CH, cpar);
     return hipGetLastError();
 }
 
@@ -2600,11 +2763,11 @@ hipError_t launch_update_cell(int prec, hipStream_t st, const LevelDesc* lv, con
 
 hipError_t launch_update(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev, const int* cell_slot,
                          const int* order, int n_cells, const CellGeom* geom, const int* cell_frow,
-                         const FaceItem* items, const double* fpar, const double* params, Phys ph, double* cmom,
+                         const FaceItem* items, const double* fpar, const double* cpar, const double* params, Phys ph, double* cmom,
                          int CH, int nch, int var) {
     if (n_cells <= 0) return hipSuccess;
-    MLVS_DISPATCH_V(prec, var, k_update, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st, lv, cell_lev, cell_slot,
-                    order, n_cells, geom, cell_frow, items, fpar, params, ph, cmom, CH, nch);
+    MLVS_DISPATCH_U(prec, var, k_update, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st, lv, cell_lev, cell_slot,
+                    order, n_cells, geom, cell_frow, items, fpar, cpar, params, ph, cmom, CH, nch);
     return hipGetLastError();
 }
 

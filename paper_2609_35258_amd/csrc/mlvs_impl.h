@@ -27,16 +27,13 @@ enum { M_U0 = 11, M_V0 = 12, NMOM = 16 };
 // moments, so NFMOM = NMOM.
 enum { NFMOM = NMOM };
 
-// Per-face record written by the face-target stage and read by the update
-// (double).  KIND: 0 interior, else the boundary kind; C1, C2: the weights of
-// phi_bar_f and of the target (area included); RN..B3, E4..CKRT: the target in
-// the evaluation form of the kernels; CORR: 1 if the compatibility factor
-// applies; C8: 1 if it has the eight-moment terms.
+// Record of a face, written by the face-target stage and read by the update, or
+// of a cell: the face normal (double), then the target with its weights in the
+// storage precision (StepEq of kernels.hip, 24 doubles long in FP64): kind 0
+// interior (and cells), else the boundary kind; c1: the weight of phi_bar_f
+// (area included), or of a cell's phi~.
 enum {
-    FP_KIND = 0, FP_ROW, FP_NX, FP_NY, FP_C1, FP_C2,
-    FP_RN, FP_UX, FP_UY, FP_I2RT, FP_RT, FP_IRT, FP_XQX, FP_XQY,
-    FP_B0, FP_B1, FP_B2, FP_B3, FP_CORR,
-    FP_E4, FP_E5, FP_E6, FP_E7, FP_CKRT, FP_C8,   // eight-moment terms (see Eq in kernels.hip)
+    FP_NX = 0, FP_NY, FP_EQ,
     NFP = 26
 };
 
@@ -149,10 +146,10 @@ struct StepArgs {
 // Launch wrappers (kernels.hip).  `S` selects float (32) or double (64) storage.
 int variant_count();
 // order: the cells in traversal order (a permutation of 0..n_cells-1).  cpar:
-// room for n_cells records (NFP) when every level is the tensor base grid, else null.
+// n_cells records (NFP).  tensor: every level is the tensor base grid.
 hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                             const int* cell_slot, const int* order, int n_cells, Phys ph, double* params,
-                            const double* cmom, int CH, double* cpar, int var = 1);
+                            const double* cmom, int CH, double* cpar, bool tensor, int var = 1);
 hipError_t launch_raw_moments(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                               const int* cell_slot, int n_cells, const double* params, double* cmom, int CH,
                               int nch);
@@ -185,7 +182,7 @@ hipError_t launch_update_cell(int prec, hipStream_t st, const LevelDesc* lv, con
                               Phys ph, double* cmom, int var = 1);
 hipError_t launch_update(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                          const int* cell_slot, const int* order, int n_cells, const CellGeom* geom,
-                         const int* cell_frow, const FaceItem* items, const double* fpar, const double* params,
+                         const int* cell_frow, const FaceItem* items, const double* fpar, const double* cpar, const double* params,
                          Phys ph, double* cmom, int CH, int nch, int var = 1);
 hipError_t launch_init_eq(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                           const int* cell_slot, int n_cells, const double* rho_u_v_T, Phys ph,
