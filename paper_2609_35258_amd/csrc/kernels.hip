@@ -747,8 +747,9 @@ __device__ __forceinline__ CellState cell_state(const double* cm, const Phys& ph
     return c;
 }
 
+// Whether the staged update forms the cell's phi_bar+ again (see update_points).
 template <typename S>
-constexpr bool UPDATE_RE = false;
+constexpr bool UPDATE_RE = sizeof(S) == 4;
 
 // Cell stage: W, q, tau, compatibility coefficients (written to params) and
 // the rows phi_bar+ = alpha phi~ + beta phi_S* (Eq. g_h_eq_Pr with the
@@ -2140,6 +2141,11 @@ __global__ __launch_bounds__(BS) void k_face_target_axes(const LevelDesc* __rest
 // were folded and the records kept in storage precision.  Lanes take the points
 // in pairs in FP32 (8-byte accesses).  Cylinder 256 x 128, 101^2, FP32: 3.39
 // -> 2.90 ms; with merged levels .535 -> .437; two-cavity .859 -> .761 ms.
+// UPDATE_RE: forming phi_bar+ again from phi~ and the cell's record (24
+// instructions) instead of reading its rows saves 8 of those 40 bytes: 2.90 ->
+// 2.61, .437 -> .417 and .761 -> .667 ms.  In FP64 the fifth exponential costs
+// more than the 16 bytes (cylinder 128 x 64, 101^2: 1.53 ms reading, 1.56 so;
+// cavity 48 x 48, 65^2: .186 and .201); a fused step finds its rows in the caches.
 template <typename S, int U, bool ST>
 __device__ __forceinline__ void update_points(const LevelDesc& L, int c, const int* cell_slot, const CellGeom* geom,
                                               const int* cell_frow, const FaceItem* items, const double* fpar,
