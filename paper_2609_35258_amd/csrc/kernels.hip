@@ -100,26 +100,46 @@ __device__ __forceinline__ void swap16(double& a, double& b) {
     b = __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
 }
 
-// Eleven sums over the wavefront (all lanes active) added to tot[0..10] in LDS,
-// in about 65 instructions instead of wave_sum<11>'s 250: two exchanges that
-// each halve the values a lane holds (sums 2t, 2t + 1 go to the lower and upper
-// 32 lanes, then to even and odd rows of 16), and the four DPP steps inside a
-// row for the three registers that are left.  Row r of register t then holds
-// sum 4t + (0, 2, 1, 3)[r].  The wave alone touches tot.
+// Four sums over the wavefront (all lanes active) in about 21 instructions: two
+// exchanges that each halve the values a lane holds (a, b go to the lower and
+// upper 32 lanes, then to even and odd rows of 16), and the four DPP steps
+// inside a row for the one register that is left.  Rows 0..3 then hold the sums
+// of a, c, b, d.
+__device__ __forceinline__ double row_sums(double a, double b, double c, double d) {
+    swap32(a, b);
+    swap32(c, d);
+    double p = a + b, q = c + d;
+    swap16(p, q);
+    double x = p + q;
+    x += dpp_mov<0xB1>(x);
+    x += dpp_mov<0x4E>(x);
+    x += dpp_mov<0x141>(x);
+    x += dpp_mov<0x140>(x);
+    return x;
+}
+
+// wave_sum by row_sums: 110 instructions for thirteen sums instead of 300.  The
+// order differs, so a quantity keeps to one of the two: the step's sums to
+// this, those of initial states, mappings and the criterion to wave_sum.
+template <int NV>
+__device__ __forceinline__ void step_sum(double (&v)[NV]) {
+    auto at = [&](int k) { return k < NV ? v[k] : 0.0; };
+#pragma unroll
+    for (int t = 0; t < NV; t += 4) {
+        const double x = row_sums(at(t), at(t + 1), at(t + 2), at(t + 3));
+        v[t] = read_lane(x, 0);
+        if (t + 1 < NV) v[t + 1] = read_lane(x, 32);
+        if (t + 2 < NV) v[t + 2] = read_lane(x, 16);
+        if (t + 3 < NV) v[t + 3] = read_lane(x, 48);
+    }
+}
+
+// Eleven sums added to tot[0..10] in LDS, which the wave alone touches.
 __device__ __forceinline__ void add_sums11(double (&v)[11], double* tot) {
     const int r = (threadIdx.x >> 4) & 3, idx = ((r & 1) << 1) | (r >> 1);
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-        double a0 = v[4 * t], b0 = v[4 * t + 1], a1 = v[4 * t + 2], b1 = t < 2 ? v[4 * t + 3] : 0.0;
-        swap32(a0, b0);
-        swap32(a1, b1);
-        double a = a0 + b0, b = a1 + b1;
-        swap16(a, b);
-        double x = a + b;
-        x += dpp_mov<0xB1>(x);
-        x += dpp_mov<0x4E>(x);
-        x += dpp_mov<0x141>(x);
-        x += dpp_mov<0x140>(x);
+        const double x = row_sums(v[4 * t], v[4 * t + 1], v[4 * t + 2], t < 2 ? v[4 * t + 3] : 0.0);
         if ((threadIdx.x & 15) == 0 && 4 * t + idx < 11) tot[4 * t + idx] += x;
     }
 }
@@ -400,14 +420,14 @@ __device__ __forceinline__ double kexp(double x) { return exp(x); }
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// g and h of the target at (x, y); x2 = x^2 + y^2.
-template <typename C>
+// g and h of the target at (x, y); x2 = x^2 + y^2.  CORR = false: uncorrected.
+template <typename C, bool CORR = true>
 __device__ __forceinline__ void step_eval(const StepEq<C>& e, C x, C y, C x2, C& g, C& h) {
     const C cx = x - e.ux, cy = y - e.uy;
     const C c2 = fma_(cx, cx, cy * cy);
     C ge = e.rn * kexp(c2 * e.k);
     const C Xc = fma_(cx, e.Xqx, cy * e.Xqy);
-    if (e.corr) {
+    if (CORR && e.corr) {
         C f = fma_(e.b1, x, fma_(e.b2, y, fma_(e.b3, x2, e.b0)));
         if (e.c8) {
             f = fma_(fma_(e.e4, cx, e.e5 * cy), e.cKRT + c2, f);
@@ -420,13 +440,13 @@ __device__ __forceinline__ void step_eval(const StepEq<C>& e, C x, C y, C x2, C&
     h = ge * e.RT * fma_(Xc, fma_(c2, e.hiRT, -e.hD), e.cK);
 }
 
-// Either form by name of its parameters: the velocity sums of a correction use
+// The uncorrected target in either form: the velocity sums of a correction use
 // the evaluation that the corrected target will be evaluated with.
 template <typename C>
 __device__ __forceinline__ void target_eval(const Eq<C>& e, C x, C y, C& g, C& h) { eq_eval<C>(e, x, y, g, h); }
 template <typename C>
 __device__ __forceinline__ void target_eval(const StepEq<C>& e, C x, C y, C& g, C& h) {
-    step_eval<C>(e, x, y, fma_(x, x, y * y), g, h);
+    step_eval<C, false>(e, x, y, C(0), g, h);
 }
 
 // Velocity points of one item are visited in chunks of U points per lane:
@@ -438,8 +458,8 @@ __device__ __forceinline__ int clampi(int i, int N) { return i < N ? i : N - 1; 
 // Compatibility correction (Sec. 3.3.1), part 1: the thirteen velocity sums of
 // the uncorrected target over the level that the 4x4 system needs (wave per
 // item; every lane receives the totals).
-template <typename S, int U, typename E>
-__device__ __forceinline__ void compat_sums(const LevelDesc& L, const E& eu, double (&s)[13]) {
+template <typename S, int U>
+__device__ __forceinline__ void compat_sums(const LevelDesc& L, const Eq<S>& eu, double (&s)[13]) {
 #pragma unroll
     for (int k = 0; k < 13; ++k) s[k] = 0.0;
     const int N = L.N;
@@ -464,6 +484,43 @@ __device__ __forceinline__ void compat_sums(const LevelDesc& L, const E& eu, dou
         }
     }
     wave_sum<13>(s);
+}
+
+// ... of a step's target: points in pairs, weights zero past the last point up
+// to a whole row of 64, no branch in the loop, the products shared: bound by
+// vector issue, 50 instructions a point where compat_sums takes 90.  Cylinder
+// 256 x 128 with merged levels (1200 points a cell), FP32, with four items a
+// wave: face targets .309 -> .177 ms, cell stage .304 -> .222.
+template <typename S, int U>
+__device__ __forceinline__ void target_sums(const LevelDesc& L, const StepEq<S>& eu, double (&s)[13]) {
+#pragma unroll
+    for (int k = 0; k < 13; ++k) s[k] = 0.0;
+    const int N = L.N, last = L.stride - 2;
+    for (int b0 = 0; b0 < N; b0 += WL * 2 * U) {
+        vec<double, 2> xv[U], yv[U], wv[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int i = b0 + 2 * (lane_id() + q * WL), ic = min(i, last);
+            xv[q] = ldv<2, double>(gp(L.xi_x), ic);
+            yv[q] = ldv<2, double>(gp(L.xi_y), ic);
+            wv[q] = ldv<2, double>(gp(L.w), ic);
+            if (i > last) wv[q] = 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const double x = xv[q][v], y = yv[q][v];
+                S g, h;
+                target_eval<S>(eu, (S)x, (S)y, g, h);
+                const double wg = wv[q][v] * (double)g, wh = wv[q][v] * (double)h;
+                const double x2 = x * x + y * y, wgx = wg * x, wgy = wg * y, wg2 = wg * x2;
+                s[0] += wg; s[1] += wgx; s[2] += wgy; s[3] += wgx * x; s[4] += wgx * y;
+                s[5] += wgy * y; s[6] += wgx * x2; s[7] += wgy * x2; s[8] += wg2 * x2;
+                s[9] += wh; s[10] += wh * x; s[11] += wh * y; s[12] += wh * x2;
+            }
+    }
+    step_sum<13>(s);
 }
 
 // Part 2 (one lane per item): assemble A and the moment defect from the sums,
@@ -648,7 +705,8 @@ __device__ __forceinline__ void compat_sums8(const LevelDesc& L, const E& eu, do
                 for (int mm = 0; mm < 8; ++mm) A[k * 8 + mm] += kern[k] * phi[mm];
         }
     }
-    wave_sum<64>(A);
+    if constexpr (std::is_same<E, Eq<S>>::value) wave_sum<64>(A);
+    else step_sum<64>(A);
 }
 
 // Part 2 (one lane): solve A a = target - A[:, 0] with target [rho, rho u, rho v,
@@ -700,14 +758,9 @@ __device__ __forceinline__ void acc_raw(double* m, double w, double x, double y,
 // kinds of step hand their results over through LDS.  The scalar work is not
 // repeated on 64 lanes.
 // ---------------------------------------------------------------------------
-#ifndef MLVS_STAGED_IPW
-#define MLVS_STAGED_IPW 1
-#endif
 constexpr int GWV = 8;
-constexpr int IPW = MLVS_STAGED_IPW;
-constexpr int GW = GWV * IPW;
+constexpr int IPW_MIN = 8192;      // see MLVS_DISPATCH_VC
 constexpr int GBS = GWV * WL;
-static_assert(GW <= WL, "the scalar steps of a workgroup run on the lanes of one wave");
 
 // Velocity chunks.  Streaming stages that reuse neighbours' rows (face
 // reconstruction, update) split each item's points into chunks of CH points
@@ -829,7 +882,7 @@ __device__ __forceinline__ void cell_target_wave(const LevelDesc& L, const CellS
         compat_axes<S>(L, e, cs.rho, cs.u, cs.v, cs.T, ph, lane_id() & (AXG - 1), a);
     } else {
         double sm[13];
-        compat_sums<S, U>(L, step_eq<S>(e), sm);
+        target_sums<S, U>(L, step_eq<S>(e), sm);
         compat_from_sums(sm, cs.rho, cs.u, cs.v, cs.T, ph, a);
     }
     e = make_eq(cs.rho, cs.u, cs.v, cs.T, cs.qx, cs.qy, a, ph);
@@ -841,7 +894,7 @@ __device__ __forceinline__ void write_params(double* pr, const CellState& cs, co
     pr[P_A3] = a[3]; pr[P_ALPHA] = cs.alpha; pr[P_BETA] = cs.beta;
 }
 
-template <typename S, int U, int MINW, int CM>
+template <typename S, int U, int MINW, int CM, int IPW>
 __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __restrict__ lvs,
                                                          const int* __restrict__ cell_lev,
                                                          const int* __restrict__ cell_slot,
@@ -849,6 +902,8 @@ __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __rest
                                                          double* __restrict__ params,
                                                          const double* __restrict__ cmom, int CH,
                                                          double* __restrict__ cpar) {
+    constexpr int GW = GWV * IPW;
+    static_assert(GW <= WL, "the scalar steps run on the lanes of one wave");
     constexpr int NS = CM == 8 ? 64 : 13;      // compatibility sums per item
     __shared__ CellState sh_c[GW];
     __shared__ Eq<double> sh_e[GW];
@@ -877,7 +932,7 @@ __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __rest
                     const CellState& cs = sh_c[j];
                     compat_sums8<S, U>(L, step_eq<S>(sh_e[j]), cs.u, cs.v, cs.T, ph, sm);
                 } else {
-                    compat_sums<S, U>(L, step_eq<S>(sh_e[j]), sm);
+                    target_sums<S, U>(L, step_eq<S>(sh_e[j]), sm);
                 }
                 if (lane_id() < NS) {
 #pragma unroll
@@ -1000,7 +1055,7 @@ __global__ __launch_bounds__(BS) void k_raw_moments(const LevelDesc* __restrict_
                     acc_raw<S>(m, wv[q][v], xv[q][v] - u0, yv[q][v] - v0, in ? gv[q][v] : S(0), in ? hv[q][v] : S(0));
                 }
         }
-        wave_sum<11>(m);
+        step_sum<11>(m);
         if (lane_id() == 0) {
             double* o = cmom + (size_t)it * NMOM;
             for (int j = 0; j < 11; ++j) o[j] = m[j];
@@ -1946,12 +2001,14 @@ __device__ __forceinline__ void write_face_record(double* o, int kind, const Fac
     write_eq_record<S>(o, step_eq_lane<S>(e, c1, c2, kind));
 }
 
-template <typename S, int U, int MINW, int CM>
+template <typename S, int U, int MINW, int CM, int IPW>
 __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __restrict__ lvs,
                                                            const FaceItem* __restrict__ items, int n,
                                                            const BCDev* __restrict__ bcs, Phys ph,
                                                            const double* __restrict__ fmom,
                                                            double* __restrict__ fpar, int CH) {
+    constexpr int GW = GWV * IPW;
+    static_assert(GW <= WL, "the scalar steps run on the lanes of one wave");
     constexpr int NS = CM == 8 ? 64 : 13;      // compatibility sums per face
     __shared__ double sh_m[GW][NS];
     __shared__ FaceState sh_f[GW];
@@ -1994,7 +2051,7 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
                         const FaceState& fs = sh_f[j];
                         compat_sums8<S, U>(L, step_eq<S>(sh_e[j]), fs.u, fs.v, fs.T, ph, sm);
                     } else {
-                        compat_sums<S, U>(L, step_eq<S>(sh_e[j]), sm);
+                        target_sums<S, U>(L, step_eq<S>(sh_e[j]), sm);
                     }
                     if (lane_id() < NS) {
 #pragma unroll
@@ -2069,7 +2126,7 @@ __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ 
                     compat_axes<S>(L, e, fs.rho, fs.u, fs.v, fs.T, ph, lane_id() & (AXG - 1), a);
                 } else {
                     double sm[13];
-                    compat_sums<S, U>(L, step_eq<S>(e), sm);
+                    target_sums<S, U>(L, step_eq<S>(e), sm);
                     compat_from_sums(sm, fs.rho, fs.u, fs.v, fs.T, ph, a);
                 }
                 e = make_eq(fs.rho, fs.u, fs.v, fs.T, fs.qx, fs.qy, a, ph);
@@ -2310,7 +2367,7 @@ __global__ __launch_bounds__(BS, MINW) void k_update(const LevelDesc* __restrict
         const int N = min(L.N, beg + CH);      // end of this chunk
         double m[11], u0, v0;
         update_points<S, U, true>(L, c, cell_slot, geom, cell_frow, items, fpar, cpar, params, ph, beg, N, m, u0, v0);
-        wave_sum<11>(m);
+        step_sum<11>(m);
         if (lane_id() == 0) {
             double* o = cmom + ((size_t)kc * n_cells + c) * NMOM;
             for (int k = 0; k < 11; ++k) o[k] = m[k];
@@ -2342,7 +2399,7 @@ __device__ __forceinline__ void update_cell_items(const LevelDesc* __restrict__ 
         double m[11];
         update_points<S, U, false>(L, c, cell_slot, geom, cell_frow, items, fpar, nullptr, params, ph, 0, L.N, m, u0,
                                    v0);
-        wave_sum<11>(m);
+        step_sum<11>(m);
 #pragma unroll
         for (int k = 0; k < 11; ++k) cm[k] = m[k];
         cm[M_U0] = u0;
@@ -2586,24 +2643,36 @@ constexpr int N_VARIANTS = 5;
         if ((prec) == 32) hipLaunchKernelGGL((KERNEL<float, U_, W_, C_>), __VA_ARGS__);          \
         else hipLaunchKernelGGL((KERNEL<double, U_, W_, C_>), __VA_ARGS__);                      \
     } while (0)
-#define MLVS_DISPATCH_VC1(prec, var, C_, KERNEL, ...)                                            \
+// ... and for the staged kernels, per compatibility order and items per wave.
+// The 64 sums of eight moments need 256 registers: at four waves per SIMD (128)
+// every variant spilled 480 to 690 of them (cylinder 95 x 45, 61^2, FP64:
+// update 0.68 ms, 0.15 ms at two waves).  From IPW_MIN items on a wave takes
+// four: the scalar chain, as long as the sums of 1200 points, then serves 32
+// items at once; fewer items would leave compute units without a workgroup.
+// Merged levels, FP32, one item per wave and four: face targets of 9.3e3 faces
+// .043 and .043 ms, 1.7e4 .067 and .060, 3.7e4 .130 and .089; cell stage of 4608
+// cells .046 and .050, 8192 .061 and .054, 32768 .304 and .249 ms.
+#define MLVS_LAUNCH_UWI(prec, KERNEL, U_, W_, C_, I_, n, ...)                                    \
+    do {                                                                                        \
+        const dim3 grid_(grid_for(n, GWV * I_));                                                 \
+        if ((prec) == 32) hipLaunchKernelGGL((KERNEL<float, U_, W_, C_, I_>), grid_, __VA_ARGS__); \
+        else hipLaunchKernelGGL((KERNEL<double, U_, W_, C_, I_>), grid_, __VA_ARGS__);           \
+    } while (0)
+#define MLVS_DISPATCH_VC1(prec, var, KERNEL, n, ...)                                             \
     do {                                                                                        \
         switch (var) {                                                                          \
-        case 0: MLVS_LAUNCH_UWC(prec, KERNEL, 1, 4, C_, __VA_ARGS__); break;                     \
-        case 2: MLVS_LAUNCH_UWC(prec, KERNEL, 4, 2, C_, __VA_ARGS__); break;                     \
-        case 3: MLVS_LAUNCH_UWC(prec, KERNEL, 4, 4, C_, __VA_ARGS__); break;                     \
-        case 4: MLVS_LAUNCH_UWC(prec, KERNEL, 1, 2, C_, __VA_ARGS__); break;                     \
-        default: MLVS_LAUNCH_UWC(prec, KERNEL, 2, 4, C_, __VA_ARGS__); break;                    \
+        case 0: MLVS_LAUNCH_UWI(prec, KERNEL, 1, 4, 4, 1, n, __VA_ARGS__); break;                \
+        case 2: MLVS_LAUNCH_UWI(prec, KERNEL, 4, 2, 4, 1, n, __VA_ARGS__); break;                \
+        case 3: MLVS_LAUNCH_UWI(prec, KERNEL, 4, 4, 4, 1, n, __VA_ARGS__); break;                \
+        case 4: MLVS_LAUNCH_UWI(prec, KERNEL, 1, 2, 4, 1, n, __VA_ARGS__); break;                \
+        default: MLVS_LAUNCH_UWI(prec, KERNEL, 2, 4, 4, 1, n, __VA_ARGS__); break;               \
         }                                                                                       \
     } while (0)
-// ... and for the kernels instantiated per compatibility order.  The 64 sums of
-// eight moments need 256 registers: at four waves per SIMD (128) every variant
-// spilled 480 to 690 of them (cylinder 95 x 45, 61^2, FP64: update 0.68 ms,
-// 0.15 ms at two waves).
-#define MLVS_DISPATCH_VC(prec, var, cm, KERNEL, ...)                                             \
+#define MLVS_DISPATCH_VC(prec, var, cm, KERNEL, n, ...)                                          \
     do {                                                                                        \
-        if ((cm) == 8) MLVS_LAUNCH_UWC(prec, KERNEL, 1, 2, 8, __VA_ARGS__);                      \
-        else MLVS_DISPATCH_VC1(prec, var, 4, KERNEL, __VA_ARGS__);                               \
+        if ((cm) == 8) MLVS_LAUNCH_UWI(prec, KERNEL, 1, 2, 8, 1, n, __VA_ARGS__);                \
+        else if ((n) >= IPW_MIN) MLVS_LAUNCH_UWI(prec, KERNEL, 2, 4, 4, 4, n, __VA_ARGS__);      \
+        else MLVS_DISPATCH_VC1(prec, var, KERNEL, n, __VA_ARGS__);                               \
     } while (0)
 // ... the update with the next cell stage: its scalar chain spills at four
 // waves per SIMD (cavity 64 x 64, 28^2, FP64: 0.116 ms, 0.105 ms at two)
@@ -2700,7 +2769,7 @@ hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const
                         n_cells, cpar);
         return hipGetLastError();
     }
-    MLVS_DISPATCH_VC(prec, var, ph.compat, k_cell_prep, dim3(grid_for(n_cells, GW)), dim3(GBS), 0, st, lv, cell_lev,
+    MLVS_DISPATCH_VC(prec, var, ph.compat, k_cell_prep, n_cells, dim3(GBS), 0, st, lv, cell_lev,
                      cell_slot, order, n_cells, ph, params, cmom, CH, cpar);
     return hipGetLastError();
 }
@@ -2752,7 +2821,7 @@ hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, con
                       fpar, CH, n_wg);
         return hipGetLastError();
     }
-    MLVS_DISPATCH_VC(prec, var, ph.compat, k_face_target, dim3(grid_for(n, GW)), dim3(GBS), 0, st, lv, items, n, bcs,
+    MLVS_DISPATCH_VC(prec, var, ph.compat, k_face_target, n, dim3(GBS), 0, st, lv, items, n, bcs,
                      ph, fmom, fpar, CH);
     return hipGetLastError();
 }
