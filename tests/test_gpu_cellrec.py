@@ -58,3 +58,28 @@ def test_cellwise_reconstruction(case, precision, chunk, monkeypatch):
         e = state_error(g.get_state(), o.g, o.h)
         assert max(e) < (1e-12 if precision == 64 else 2e-6), (k, e)
     g.close()
+
+
+@pytest.mark.parametrize("case", ["jump", "triangles", "two_triangles"])
+def test_limiter_faces_that_decide_fp64(case):
+    # Venkatakrishnan's limiter from the largest and the smallest d-: a 1000:1
+    # jump over triangles and quadrilaterals, cells of few faces, plateaus
+    # (every d- zero), against the oracle's minimum over all faces
+    import paper_2609_35258_amd as m
+    if case == "jump":
+        p = W.two_cavity(16, nv=9, vmax=6.0)
+    elif case == "triangles":
+        p = W.as_unstructured(W.perturb(W.cavity(5, nv=9, vel_kind="nc", vmax=4.5), seed=8, amp=0.4), split="random",
+                              seed=6)
+    else:
+        p = W.as_unstructured(W.perturb(W.cavity(1, nv=9, vel_kind="nc", vmax=4.5), seed=8, amp=0.4), split="random",
+                              seed=6)
+    print("case limiter", case, p.n_cells, flush=True)
+    o = Oracle(p, compat=4)
+    g = m.Solver.from_problem(p, precision=64, compat=4)
+    for k in range(3):
+        o.step()
+        g.step(1)
+        e = state_error(g.get_state(), o.g, o.h)
+        assert max(e) < 1e-12, (k, e)
+    g.close()
