@@ -393,15 +393,8 @@ def cell_areas(p):
     return out
 
 
-# launch variant index -> (velocity points per lane per load batch, minimum waves per SIMD)
-VARIANTS = {0: (1, 4), 1: (2, 4), 2: (4, 2), 3: (4, 4), 4: (1, 2)}
-# kernels instantiated per compatibility order carry it as a template argument,
-# and the face kernels the mesh kind (0 structured, 1 unstructured) after it
-STAGE_CM = ("cell", "face_target", "update_cell")
-STAGE_MK = ("face_rec", "xface")
-STAGE_KERNEL = {"update_cell": "k_update_cell",
-                "cell": "k_cell_prep", "face_rec": "k_face_rec", "face_target": "k_face_target",
-                "update": "k_update", "xface": "k_xface"}
+STAGE_KERNEL = {"update_cell": "k_update_cell", "cell": "k_cell_prep", "face_rec": "k_face_rec", "face": "k_face_rec",
+                "face_target": "k_face_target", "update": "k_update", "xface": "k_xface"}
 
 
 def measured_traffic(workload, stage, precision, variant, mk=0, crit=False):
@@ -413,19 +406,14 @@ def measured_traffic(workload, stage, precision, variant, mk=0, crit=False):
     if not os.path.exists(path) or (not crit and (stage not in STAGE_KERNEL or variant is None)):
         return None
     h = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-    if crit:
-        name = "mlvs::k_criterion<%s>" % ("double" if precision == 64 else "float")
-    else:
-        u, w = VARIANTS[variant]
-        if mk and stage in STAGE_MK:
-            u, w = VARIANTS[0]             # unstructured face kernels: the (1, 4) pair for every variant
-        name = "mlvs::%s<%s,%d,%d%s%s>" % (STAGE_KERNEL[stage], "double" if precision == 64 else "float", u, w,
-                                           ",4" if stage in STAGE_CM else "", ",%d" % mk if stage in STAGE_MK else "")
+    name = "mlvs::%s<%s" % ("k_criterion" if crit else STAGE_KERNEL[stage], "double" if precision == 64 else "float")
+    hits = []                              # one run launches one variant of a kernel
     for line in open(path):
         f = line.split()
-        if len(f) == 4 and not line.startswith("#") and f[0] == h and f[1] == workload and f[2] == name:
-            return float(f[3])
-    return None
+        if len(f) == 4 and not line.startswith("#") and f[0] == h and f[1] == workload and (f[2] + ",").replace(
+                ">", ",").startswith(name + ","):
+            hits.append(float(f[3]))
+    return hits[0] if len(hits) == 1 else None
 
 
 def cylinder_case(steps=200, warmup=100, precision=32, mode="both", Kn=0.1, adapt=None):

@@ -1151,8 +1151,8 @@ struct mlvs_ctx_s {
     unsigned int* d_sync = nullptr;    // [0] barrier arrivals, [1] sticky error flag
     int persistent_grid = 0;
     int64_t n_captures = 0, n_graph_launches = 0;
-    // Fused step (every level fits one velocity chunk): reconstruction and
-    // target in one launch, and the update carries the next step's cell stage.
+    // Fused step (every level fits one velocity chunk): the update carries the
+    // next step's cell stage.
     bool fuse_allowed = true;          // MLVS_FUSE=0 turns the fused step off
     bool fused = false;
     bool prep_valid = false;           // phi_bar+ rows and parameters match the stored state

@@ -4,8 +4,8 @@
 // remap); a 256-thread workgroup carries four independent items.  Lanes
 // stride over the item's velocity points (velocity index contiguous in
 // memory, so every row access is coalesced); velocity-space moments are
-// reduced in registers, then across the wave with a fixed butterfly of
-// shuffles (deterministic, no LDS and no barriers).  One launch per
+// reduced in registers, then across the wave in a fixed order (deterministic,
+// no barriers).  One launch per
 // stage covers every level: each item names its own level.  Storage type S is
 // float or double; per-velocity arithmetic runs in S; moment sums, the small
 // linear solves and the per-cell parameters are double.
