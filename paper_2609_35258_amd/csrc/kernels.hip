@@ -336,11 +336,12 @@ __device__ __forceinline__ Eq<C> eq_cast(const Eq<double>& d) {
     return e;
 }
 
-// FP32 storage evaluates its Maxwellians with the hardware base-2 exponential
-// (two instructions; relative error about 1e-7 |x| in the argument's rounding,
-// below the storage precision where the values matter).  The same function
-// serves the compatibility sums and every later evaluation of the target, so
-// the discrete moments the correction enforces are the ones the step uses.
+// The plain form, for initial states, mappings between levels and cross-level
+// faces: FP32 storage takes the hardware base-2 exponential (two instructions;
+// relative error about 1e-7 |x| in the argument's rounding, below the storage
+// precision where the values matter).  Their compatibility sums use the same
+// function, as the step's use its own (target_eval, compat_axes), so that the
+// discrete moments a correction enforces are those of the values it enters.
 __device__ __forceinline__ float dexp(float x) { return __expf(x); }
 __device__ __forceinline__ double dexp(double x) { return exp(x); }
 
@@ -571,43 +572,66 @@ __device__ __forceinline__ void compat_solve(const LevelDesc& L, const Eq<S>& eu
 // cylinder 256 x 128, 101^2, FP32 took 1.09 ms, so .128).  Sixteen lanes per item: lane lg of the group
 // takes every sixteenth node, a fixed tree adds the lanes, and every lane
 // holds the result, whatever the launch puts beside the group.  The sums are
-// of the rounded parameters the step evaluates the target with (S).  Solved in
-// the basis [1, c_x, c_y, c^2] (the same span and constraints, taken about the
+// of the rounded parameters and velocities the step evaluates the target with
+// (S); what is left out, the rounding of single points, averages out over them.
+// Error of a step's velocity in FP32 (rms over random states, 33^2 points):
+// 3.4e-8 without the velocities' rounding, 1.2e-8 so, 1.2e-8 by sums over all
+// points.  Solved in the basis [1, c_x, c_y, c^2] (the same span and constraints, taken about the
 // velocity), returned as coefficients of [1, xi_x, xi_y, E_xi].
 constexpr int AXG = 16;
 
-__device__ __forceinline__ void axis_sums(const double* x, const double* w, int n, double u, double i2RT, bool f32,
-                                          int lg, double (&A)[8]) {
+// Sums of one axis: A[k], and in FP32 (F32) D[m] = sum w e^{-c^2/2RT} c^m d, with
+// c the velocity as step_eval rounds it and d what the true one is further off:
+// the rounding of a column's c shifts its exponent and its moment at every one
+// of its points.  RSQ: the axis whose square step_eval rounds.
+template <bool F32, bool RSQ>
+__device__ __forceinline__ void axis_sums(const double* x, const double* w, int n, double u, double i2RT, int lg,
+                                          double (&A)[8], double (&D)[2]) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) A[k] = 0.0;
+    D[0] = D[1] = 0.0;
     constexpr int U = 4;               // nodes in flight: their loads and exponentials overlap
     for (int i0 = lg; i0 < n; i0 += AXG * U) {
-        double c[U], t[U];
+        double c[U], t[U], s[U], d[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             const int i = i0 + AXG * q, ic = clampi(i, n);
             const double xi = gp(x)[ic];
-            c[q] = (f32 ? (double)(float)xi : xi) - u;
+            if constexpr (F32) {
+                const float cf = (float)xi - (float)u;
+                c[q] = cf;
+                d[q] = (xi - u) - c[q];
+                s[q] = RSQ ? (double)(cf * cf) : c[q] * c[q];
+            } else {
+                c[q] = xi - u;
+                d[q] = 0.0;
+                s[q] = c[q] * c[q];
+            }
             t[q] = i < n ? gp(w)[ic] : 0.0;
         }
 #pragma unroll
-        for (int q = 0; q < U; ++q) t[q] *= exp(-(c[q] * c[q]) * i2RT);
+        for (int q = 0; q < U; ++q) t[q] *= exp(-s[q] * i2RT);
 #pragma unroll
         for (int q = 0; q < U; ++q)
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 A[k] += t[q];
+                if (F32 && k < 2) D[k] += t[q] * d[q];
                 t[q] *= c[q];
             }
     }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        double v = A[k];
+    auto join = [](double v) {
         v += dpp_mov<0xB1>(v);
         v += dpp_mov<0x4E>(v);
         v += dpp_mov<0x141>(v);
         v += dpp_mov<0x140>(v);
-        A[k] = v;
+        return v;
+    };
+#pragma unroll
+    for (int k = 0; k < 8; ++k) A[k] = join(A[k]);
+    if constexpr (F32) {
+        D[0] = join(D[0]);
+        D[1] = join(D[1]);
     }
 }
 
@@ -618,9 +642,9 @@ __device__ __forceinline__ void compat_axes(const LevelDesc& L, const Eq<double>
     auto r = [](double q) { return F32 ? (double)(float)q : q; };
     const double ue = r(e.ux), ve = r(e.uy), iRT = r(e.iRT);
     const double i2RT = F32 ? -r(-e.i2RT * LOG2E) / LOG2E : e.i2RT;     // as StepEq rounds it
-    double A[8], B[8];
-    axis_sums(L.axes, L.axes + L.nx, L.nx, ue, i2RT, F32, lg, A);
-    axis_sums(L.axes + 2 * L.nx, L.axes + 2 * L.nx + L.ny, L.ny, ve, i2RT, F32, lg, B);
+    double A[8], B[8], Ad[2], Bd[2];
+    axis_sums<F32, false>(L.axes, L.axes + L.nx, L.nx, ue, i2RT, lg, A, Ad);
+    axis_sums<F32, true>(L.axes + 2 * L.nx, L.axes + 2 * L.nx + L.ny, L.ny, ve, i2RT, lg, B, Bd);
     // sum w E c_x^a c_y^b (c^2)^m of the Gaussian E
     auto Q = [&](int a, int b, int m) {
         if (m == 0) return A[a] * B[b];
@@ -639,14 +663,15 @@ __device__ __forceinline__ void compat_axes(const LevelDesc& L, const Eq<double>
         const double q3 = qx * Q(a + 1, b, m + 1) + qy * Q(a, b + 1, m + 1);
         return rRT * (e.cK * Q(a, b, m) + (e.cK * iRT * q3 - (e.Dd * e.cK + e.K2) * q1));
     };
-    const double g0 = G(0, 0, 0), gx = G(1, 0, 0), gc = G(0, 0, 1), gxc = G(1, 0, 1);
+    const double g0 = G(0, 0, 0), gx = G(1, 0, 0) + rn * (Ad[0] * B[0]), gxc = G(1, 0, 1);
+    const double gc = G(0, 0, 1) + 2.0 * rn * (Ad[1] * B[0] + A[0] * Bd[1]);
     const double h0 = H(0, 0, 0), hx = H(1, 0, 0);
     const double du = u - ue, dv = v - ve;
     const double en = 0.5 * (3.0 + ph.K) * rho * ph.R * T + 0.5 * rho * (du * du + dv * dv);
     const double e3 = 0.5 * (gc + h0), e33 = 0.5 * (G(0, 0, 2) + H(0, 0, 1));
     double d[4];
     if (ph.D == 2) {
-        const double gy = G(0, 1, 0), gxy = G(1, 1, 0), gyc = G(0, 1, 1);
+        const double gy = G(0, 1, 0) + rn * (A[0] * Bd[0]), gxy = G(1, 1, 0), gyc = G(0, 1, 1);
         double M[4][4] = {{g0, gx, gy, gc},
                           {gx, G(2, 0, 0), gxy, gxc},
                           {gy, gxy, G(0, 2, 0), gyc},
