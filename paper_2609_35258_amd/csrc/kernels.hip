@@ -1721,17 +1721,14 @@ __device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const
             const int lb = b0 + WL * V * lane_id(), le = min(end, lb + WL * V);
             const bool on = lb < end;
             const int a0 = gp(L.ang)[on ? 2 * (lb / WL) : 0], a1 = gp(L.ang)[on ? 2 * ((le - 1) / WL) + 1 : 0];
-            const unsigned span = (unsigned)(a1 - a0);
-            constexpr unsigned W = 2u * (ANG_QUARTER - ANG_MARGIN);
 #pragma unroll
             for (int n = 0; n < NS; ++n) {
                 bool easy[2] = {false, false}, any[2] = {false, false};
 #pragma unroll
                 for (int m = 0; m < PER; ++m) {
                     const Slot<S>& sl = slot[PER * n + m];
-                    const unsigned t = (unsigned)(a0 - sl.ang) + W / 2;
-                    any[m] = on && sl.code >= 0 && !(span <= W && t + 0x80000000u <= W - span);
-                    easy[m] = any[m] && !sl.bnd && lb + WL * V <= end && span <= W && t <= W - span;
+                    any[m] = on && sl.code >= 0 && !ang_in(a0, a1, sl.ang);
+                    easy[m] = any[m] && !sl.bnd && lb + WL * V <= end && ang_out(a0, a1, sl.ang);
                 }
                 fast[n] = __ballot((easy[0] && !any[1]) || (easy[1] && !any[0]));
                 far[n] = __ballot(any[1]);

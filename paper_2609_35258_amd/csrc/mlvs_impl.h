@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "angles.h"
+
 namespace mlvs {
 
 // Per-cell parameter block (double).  Written by the cell stage of each step.
@@ -36,11 +38,6 @@ enum {
     FP_NX = 0, FP_NY, FP_EQ,
     NFP = 26
 };
-
-// Angles as 32-bit integers, a whole turn 2^32.  A quarter turn, and the margin
-// (2.4e-5 rad) by which a decision from angles must be clear of it: far above
-// the rounding of an angle or of a float velocity (about 1e-7).
-constexpr int ANG_QUARTER = 1 << 30, ANG_MARGIN = 1 << 14;
 
 // One velocity space (a representative level or an interface level).
 struct LevelDesc {
