@@ -282,11 +282,16 @@ mlvs_status mlvs_set_state(mlvs_ctx ctx, const double* g, const double* h);
 mlvs_status mlvs_info(mlvs_ctx ctx, double* dt, int64_t* n_cells, int32_t* n_blocks, int32_t* n_base);
 
 /* Launch variants of a stage (kernels instantiated for several pairs of
- * velocity points per lane per load batch and minimum occupancy): *count
- * variants exist for `stage` (numbering as in mlvs_time_stage);
- * mlvs_set_variant selects one for subsequent launches.  Used by the
- * autotuner; results do not depend on the variant. */
+ * velocity points per lane per load batch and minimum occupancy): indices 0
+ * to *count - 1 are accepted for `stage` (numbering as in mlvs_time_stage);
+ * mlvs_set_variant selects one for subsequent launches.  Where a stage has
+ * one launch only (some stages on unstructured meshes, with eight moments, on
+ * the base grid alone or for many items) the index has no effect:
+ * mlvs_variant_form gives what a variant launches on the present mesh and
+ * level set, and variants of equal *form launch the same kernels.  Used by
+ * the autotuner; results do not depend on the variant. */
 mlvs_status mlvs_variants(int stage, int* count);
+mlvs_status mlvs_variant_form(mlvs_ctx ctx, int stage, int variant, int* form);
 mlvs_status mlvs_set_variant(mlvs_ctx ctx, int stage, int variant);
 
 /* Replay each step as a HIP graph (on = 1): the launches of one step are

@@ -131,6 +131,7 @@ _PROTOS = {
                                        ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int),
                                        ctypes.POINTER(ctypes.c_int)]),
     "mlvs_variants": (ctypes.c_int, [ctypes.c_int, ctypes.POINTER(ctypes.c_int)]),
+    "mlvs_variant_form": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_int)]),
     "mlvs_set_variant": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int]),
     "mlvs_time_stage": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, _c_double_p]),
     "mlvs_stage_size": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.POINTER(ctypes.c_int64),
@@ -597,6 +598,12 @@ class Solver:
         n = ctypes.c_int()
         _check(lib().mlvs_variants(self.STAGES.get(stage, stage), ctypes.byref(n)))
         return n.value
+
+    def variant_form(self, stage, v: int):
+        """What variant v of a stage launches on the present level set: equal values, the same kernels."""
+        f = ctypes.c_int()
+        _check(lib().mlvs_variant_form(self.h, self.STAGES.get(stage, stage), int(v), ctypes.byref(f)))
+        return f.value
 
     def set_variant(self, stage, v: int):
         _check(lib().mlvs_set_variant(self.h, self.STAGES.get(stage, stage), int(v)))

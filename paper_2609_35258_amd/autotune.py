@@ -4,13 +4,16 @@ tiles of structured meshes.
 For each tunable stage the library holds several instantiations of the kernel
 (pairs of velocity points per lane per load batch and minimum waves per SIMD,
 i.e. memory-level parallelism against a register budget per lane).  The tuner
-times every variant on the solver's current
+times every variant that launches something of its own on the solver's current
 state with HIP events (``Solver.time_stage``), keeps the fastest, and caches
 the choice in a JSON file keyed by GPU architecture, storage precision, the
-stage's work shape (items, mean velocity points per item), the number of
-variants the stage has and a hash of the built library, so later runs of the
-same shape with the same kernels skip the sweep, and a rebuilt library or a
-new variant sweeps again.  Variants only change scheduling, never the
+stage's work shape (items, mean velocity points per item), the kernels its
+variants launch (``Solver.variant_form``: they differ between mesh kinds,
+compatibility orders, the base grid alone and merged levels, few items and
+many) and a hash of the built library, so later runs of the same shape with the
+same kernels skip the sweep, and a rebuilt library or a new variant sweeps
+again.  A stage with one launch has nothing to choose: its variant is left as
+it is and nothing is cached.  Variants only change scheduling, never the
 results.
 
 The traversal tiles (``Solver.set_tiling``: tw x th cells visited, and their
@@ -60,8 +63,13 @@ def shape_key(solver, stage: str, precision: int) -> Optional[str]:
     per = int(round(pts / items))
     # bucket the size so nearby shapes share an entry
     bucket = 1 << max(per - 1, 1).bit_length()
-    return "%s|fp%d|%s|items~%d|pts<=%d|variants%d|lib%s" % (
-        _arch(), precision, stage, 1 << max(items - 1, 1).bit_length(), bucket, solver.variants(stage), _lib_tag())
+    return "%s|fp%d|%s|items~%d|pts<=%d|forms%s|lib%s" % (
+        _arch(), precision, stage, 1 << max(items - 1, 1).bit_length(), bucket,
+        "+".join("%x" % f for f in _forms(solver, stage)), _lib_tag())
+
+
+def _forms(solver, stage: str) -> list:
+    return [solver.variant_form(stage, v) for v in range(solver.variants(stage))]
 
 
 def autotune(solver, precision: int, stages: Optional[Iterable[str]] = None, reps: int = 5,
@@ -77,18 +85,25 @@ def autotune(solver, precision: int, stages: Optional[Iterable[str]] = None, rep
         key = shape_key(solver, st, precision)
         if key is None:
             continue
+        forms = _forms(solver, st)
+        distinct = [v for v in range(len(forms)) if forms.index(forms[v]) == v]
+        if len(distinct) == 1:
+            solver.time_stage(st, 1)
+            ms = solver.time_stage(st, reps)
+            out[st] = {"variant": distinct[0], "ms": ms, "all_ms": [ms], "key": key, "from_cache": False}
+            continue
         if key in table and not force:
             solver.set_variant(st, table[key]["variant"])
             out[st] = dict(table[key], key=key, from_cache=True)
             continue
         times = []
-        for v in range(solver.variants(st)):
+        for v in distinct:
             solver.set_variant(st, v)
             solver.time_stage(st, 1)                      # warm the variant
             times.append(solver.time_stage(st, reps))
-        best = min(range(len(times)), key=lambda k: times[k])
+        best = distinct[min(range(len(times)), key=lambda k: times[k])]
         solver.set_variant(st, best)
-        table[key] = {"variant": best, "ms": times[best], "all_ms": times}
+        table[key] = {"variant": best, "ms": min(times), "all_ms": times}
         out[st] = dict(table[key], key=key, from_cache=False)
     _store(path, table)
     return out

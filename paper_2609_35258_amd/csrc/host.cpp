@@ -3124,6 +3124,16 @@ mlvs_status mlvs_set_variant(mlvs_ctx c, int stage, int v) {
     });
 }
 
+mlvs_status mlvs_variant_form(mlvs_ctx c, int stage, int v, int* form) {
+    return guarded([&] {
+        int cnt = 0;
+        if (!c || !form || mlvs_variants(stage, &cnt) != MLVS_OK || v < 0 || v >= cnt)
+            fail(MLVS_E_ARG, "bad arguments");
+        *form = variant_form(stage, v, c->ph.compat, c->ph.mesh_kind, c->tensor, c->mesh.n_cells,
+                             c->n_faces + c->n_bfaces);
+    });
+}
+
 mlvs_status mlvs_set_persistent(mlvs_ctx c, int on) {
     return guarded([&] {
         if (!c || (on != 0 && on != 1)) fail(MLVS_E_ARG, "bad arguments");

@@ -3699,6 +3699,28 @@ static hipError_t persistent_grid(KF kernel, int* grid) {
 
 int persistent_variant_count() { return 2; }
 
+// What variant `var` of a stage launches (the rules of the dispatches above):
+// the kernel family times sixteen plus the index, where the index chooses.
+int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, int n_cells, int nF) {
+    enum { F_C8 = 16, F_UMESH = 32, F_TENSOR = 64, F_LARGE = 128 };
+    const int c8 = compat == 8 ? F_C8 : 0, um = mesh_kind ? F_UMESH : 0, axes = tensor && !c8 ? F_TENSOR : 0;
+    const int rec = um ? um : var;
+    auto staged = [&](int n, int tensor_form) {
+        return axes ? tensor_form : c8 ? c8 : n >= IPW_MIN ? (int)F_LARGE : var;
+    };
+    switch (stage) {
+    case 0: return staged(n_cells, axes + var);
+    case 2: return rec;
+    case 3: return staged(nF, axes);
+    case 4: return um ? um : var == 2 ? 2 : 0;
+    case 5: return var;
+    case 7: return rec | staged(nF, axes);
+    case 8: return (c8 | axes) + var;
+    case 9: return (c8 | um | axes) + (um ? 0 : var);
+    default: return 0;
+    }
+}
+
 hipError_t launch_step_persistent(int prec, hipStream_t st, const StepArgs* A, unsigned int* sync, Phys ph, int var,
                                   int* grid_used) {
     hipError_t e = hipSuccess;

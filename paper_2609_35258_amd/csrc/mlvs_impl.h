@@ -142,6 +142,8 @@ struct StepArgs {
 
 // Launch wrappers (kernels.hip).  `S` selects float (32) or double (64) storage.
 int variant_count();
+// Equal values: these variants of a stage launch the same kernels.
+int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, int n_cells, int nF);
 // order: the cells in traversal order (a permutation of 0..n_cells-1).  cpar:
 // n_cells records (NFP).  tensor: every level is the tensor base grid.
 hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
