@@ -134,7 +134,15 @@ __device__ __forceinline__ void step_sum(double (&v)[NV]) {
     }
 }
 
-// Eleven sums added to tot[0..10] in LDS, which the wave alone touches.
+// Order between LDS accesses of the wave's own lanes (no instruction: a wave's
+// LDS accesses are carried out in order, the compiler must keep them so).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Eleven sums added to tot[0..10] in LDS, which the wave alone touches (each
+// entry always by the same lane).
 __device__ __forceinline__ void add_sums11(double (&v)[11], double* tot) {
     const int r = (threadIdx.x >> 4) & 3, idx = ((r & 1) << 1) | (r >> 1);
 #pragma unroll
@@ -1909,7 +1917,9 @@ __device__ __forceinline__ void cell_rec_items(const LevelDesc* __restrict__ lvs
         SideOf<S, MK> sd;
         load_side<S>(sd, L, c, cell_slot, cell_nbr, geom, 0.0, 0.0);
         if (j < 11) tot[r][j] = 0.0;
+        wave_lds_order();
         cell_rec_points<S, MK>(L, c, sd, cell_frow, items, geom[c], ph, beg, end, u0, v0, tot, sh_in[w]);
+        wave_lds_order();
         // lane 16 r + j writes moment j of slot r
         const int cd = cell_frow[4 * c + r];
         const double val = j == M_U0 ? u0 : j == M_V0 ? v0 : tot[r][j < 11 ? j : 0];
