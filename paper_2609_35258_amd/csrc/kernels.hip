@@ -671,15 +671,20 @@ __device__ __forceinline__ void compat_axes(const LevelDesc& L, const Eq<double>
         const double q3 = qx * Q(a + 1, b, m + 1) + qy * Q(a, b + 1, m + 1);
         return rRT * (e.cK * Q(a, b, m) + (e.cK * iRT * q3 - (e.Dd * e.cK + e.K2) * q1));
     };
-    const double g0 = G(0, 0, 0), gx = G(1, 0, 0) + rn * (Ad[0] * B[0]), gxc = G(1, 0, 1);
-    const double gc = G(0, 0, 1) + 2.0 * rn * (Ad[1] * B[0] + A[0] * Bd[1]);
+    double gx = G(1, 0, 0), gy = G(0, 1, 0), gc = G(0, 0, 1);
+    if constexpr (F32) {               // the moments' velocities are the true ones
+        gx += rn * (Ad[0] * B[0]);
+        gy += rn * (A[0] * Bd[0]);
+        gc += 2.0 * rn * (Ad[1] * B[0] + A[0] * Bd[1]);
+    }
+    const double g0 = G(0, 0, 0), gxc = G(1, 0, 1);
     const double h0 = H(0, 0, 0), hx = H(1, 0, 0);
     const double du = u - ue, dv = v - ve;
     const double en = 0.5 * (3.0 + ph.K) * rho * ph.R * T + 0.5 * rho * (du * du + dv * dv);
     const double e3 = 0.5 * (gc + h0), e33 = 0.5 * (G(0, 0, 2) + H(0, 0, 1));
     double d[4];
     if (ph.D == 2) {
-        const double gy = G(0, 1, 0) + rn * (A[0] * Bd[0]), gxy = G(1, 1, 0), gyc = G(0, 1, 1);
+        const double gxy = G(1, 1, 0), gyc = G(0, 1, 1);
         double M[4][4] = {{g0, gx, gy, gc},
                           {gx, G(2, 0, 0), gxy, gxc},
                           {gy, gxy, G(0, 2, 0), gyc},
