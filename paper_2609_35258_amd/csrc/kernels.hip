@@ -1913,6 +1913,8 @@ __device__ __forceinline__ void cell_rec_items(const LevelDesc* __restrict__ lvs
     const int r = lane_id() >> 4, j = lane_id() & 15;
     const int n = n_cells * nch;
     for (int it = first; it < n; it += stride) {
+        if (j < 11) tot[r][j] = 0.0;
+        wave_lds_order();                          // first: no load waits for it
         const int kc = it / n_cells, c = order[it - kc * n_cells];
         const LevelDesc& L = lvs[cell_lev[c]];
         const int beg = kc * CH;
@@ -1921,12 +1923,10 @@ __device__ __forceinline__ void cell_rec_items(const LevelDesc* __restrict__ lvs
         const double u0 = params[(size_t)c * NPARAM + P_U], v0 = params[(size_t)c * NPARAM + P_V];
         SideOf<S, MK> sd;
         load_side<S>(sd, L, c, cell_slot, cell_nbr, geom, 0.0, 0.0);
-        if (j < 11) tot[r][j] = 0.0;
-        wave_lds_order();
         cell_rec_points<S, MK>(L, c, sd, cell_frow, items, geom[c], ph, beg, end, u0, v0, tot, sh_in[w]);
-        wave_lds_order();
         // lane 16 r + j writes moment j of slot r
         const int cd = cell_frow[4 * c + r];
+        wave_lds_order();
         const double val = j == M_U0 ? u0 : j == M_V0 ? v0 : tot[r][j < 11 ? j : 0];
         if (cd >= 0 && !(cd & 2) && j <= M_V0) fmom[(((size_t)kc * nF + (cd >> 2)) * 2 + (cd & 1)) * NFMOM + j] = val;
     }
