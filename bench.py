@@ -393,27 +393,60 @@ def cell_areas(p):
     return out
 
 
-STAGE_KERNEL = {"update_cell": "k_update_cell", "cell": "k_cell_prep", "face_rec": "k_face_rec", "face": "k_face_rec",
-                "face_target": "k_face_target", "update": "k_update", "xface": "k_xface"}
+def stage_kernels(stage, form, precision):
+    """Names of the kernels that a stage launches in a given form (Solver.variant_form: the kernel family, and
+    below 16 the variant index where it chooses), as in profiles/traffic.txt."""
+    fam, v = form // 16 * 16, form % 16
+    S = "double" if precision == 64 else "float"
+    staged = ((1, 4), (2, 4), (4, 2), (4, 4), (1, 2))
+
+    def target(name, tensor):
+        if fam & 64:
+            return tensor
+        if fam & 16:
+            return ["%s<%s,1,2,8,1>" % (name, S)]
+        if fam & 128:
+            return ["%s<%s,2,4,4,4>" % (name, S)]
+        return ["%s<%s,%d,%d,4,1>" % ((name, S) + staged[v])]
+
+    rec = ["k_face_rec<%s,2,1>" % S if fam & 32 else "k_face_rec<%s,%d,0>" % (S, (2, 3, 4, 5, 1)[v])]
+    if stage == "cell":
+        return target("k_cell_prep", ["k_cell_target_axes<%s>" % S, "k_phibar<%s,%d,%d>" % ((S,) + staged[v])])
+    if stage == "face_rec":
+        return rec
+    if stage == "face_target":
+        return target("k_face_target", ["k_face_target_axes<%s>" % S])
+    if stage == "face":
+        return rec + target("k_face_target", ["k_face_target_axes<%s>" % S])
+    if stage == "xface":
+        return ["k_xface<%s,%d,%d>" % (S, (2 if precision == 32 else 1) if v == 2 else (4 if precision == 32 else 2),
+                                       1 if fam & 32 else 0)]
+    if stage == "update":
+        return ["k_update<%s,%d,%d>" % ((S,) + ((1, 4), (2, 3), (4, 2), (2, 2), (1, 3))[v])]
+    if stage == "update_cell":
+        return ["k_update_cell<%s,%d,%d,%d>" % ((S,) + ((1, 2), (2, 2), (4, 2), (2, 3), (4, 1))[v]
+                                                + (8 if fam & 16 else 4,))]
+    if stage == "criterion":
+        return ["k_criterion<%s>" % S]
+    return []
 
 
-def measured_traffic(workload, stage, precision, variant, mk=0, crit=False):
-    """HBM-side bytes per dispatch of the stage's kernel from profiles/traffic.txt
+def measured_traffic(workload, stage, precision, form):
+    """HBM-side bytes per launch of the stage's kernels from profiles/traffic.txt
     (FETCH_SIZE and WRITE_SIZE runs, copy-calibrated), or None when absent or
     when the kernel source has changed since the counters were taken."""
     path = os.path.join(ROOT, "profiles", "traffic.txt")
     src = os.path.join(ROOT, "paper_2609_35258_amd", "csrc", "kernels.hip")
-    if not os.path.exists(path) or (not crit and (stage not in STAGE_KERNEL or variant is None)):
+    if not os.path.exists(path) or form is None:
         return None
     h = hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
-    name = "mlvs::%s<%s" % ("k_criterion" if crit else STAGE_KERNEL[stage], "double" if precision == 64 else "float")
-    hits = []                              # one run launches one variant of a kernel
+    found = {}
     for line in open(path):
         f = line.split()
-        if len(f) == 4 and not line.startswith("#") and f[0] == h and f[1] == workload and (f[2] + ",").replace(
-                ">", ",").startswith(name + ","):
-            hits.append(float(f[3]))
-    return hits[0] if len(hits) == 1 else None
+        if len(f) == 4 and not line.startswith("#") and f[0] == h and f[1] == workload:
+            found[f[2].replace("mlvs::", "")] = float(f[3])
+    names = stage_kernels(stage, form, precision)
+    return sum(found[n] for n in names) if names and all(n in found for n in names) else None
 
 
 def cylinder_case(steps=200, warmup=100, precision=32, mode="both", Kn=0.1, adapt=None):
@@ -431,11 +464,11 @@ def cylinder_case(steps=200, warmup=100, precision=32, mode="both", Kn=0.1, adap
     if mode == "uvs":
         u, t_u, upd_u, _ = run_gpu(p, steps, warmup + 2, precision, None)
         prof_u = stage_profile(u, reps=5)
-        var_u = {k: v["variant"] for k, v in getattr(u, "tuned", {}).items()}
+        forms_u = _forms(getattr(u, "tuned", {}))
         u.close()
         return {"uvs": {"value": upd_u / t_u, "ms_per_step": 1e3 * t_u / steps,
                         "roofline": method_roofline(prof_u, precision, upd_u / steps, 1e3 * t_u / steps, uvs_wl,
-                                                    var_u)}}
+                                                    forms_u)}}
     ap = CYL_ADAPT if adapt is None else adapt
     s = m.Solver.from_problem(p, precision=precision, compat=4, adapt=ap, graph=True)
     s.step(warmup)
@@ -464,7 +497,7 @@ def cylinder_case(steps=200, warmup=100, precision=32, mode="both", Kn=0.1, adap
     f_u = u.moments()
     mem_u = u.memory()
     prof_u = stage_profile(u, reps=5)
-    var_u = {k: v["variant"] for k, v in getattr(u, "tuned", {}).items()}
+    forms_u = _forms(getattr(u, "tuned", {}))
     u.close()
     err = {name: float(np.sqrt(np.sum((f_m[:, k] - f_u[:, k]) ** 2) / np.sum(f_u[:, k] ** 2)))
            for k, name in ((0, "rho"), (1, "u"), (3, "T"))}
@@ -478,7 +511,7 @@ def cylinder_case(steps=200, warmup=100, precision=32, mode="both", Kn=0.1, adap
             "nbar": float(np.sum(npts * ncells) / np.sum(ncells)), "n_cross": int(ncross),
             "roofline": method_roofline(prof, precision, upd / steps, 1e3 * t_m / steps),
             "uvs": {"value": upd_u / t_u, "ms_per_step": 1e3 * t_u / steps,
-                    "roofline": method_roofline(prof_u, precision, upd_u / steps, 1e3 * t_u / steps, uvs_wl, var_u),
+                    "roofline": method_roofline(prof_u, precision, upd_u / steps, 1e3 * t_u / steps, uvs_wl, forms_u),
                     "time_to_solution_ratio": t_u / t_m, "memory_ratio": mem_u / mem_m,
                     "mlvs_vs_uvs_rel_l2": err, "meets_1e-3_gate_rho_T": _gate(err)}}
 
@@ -552,7 +585,11 @@ JET_WL = "jet512x256-nc161-fp32"
 METHOD_VALUES, FLOOR_VALUES = 4, 6
 
 
-def method_roofline(prof, precision, updates_per_step, step_ms, workload=None, variants=None, interval=0,
+def _forms(tuned):
+    return {k: v["form"] for k, v in tuned.items()}
+
+
+def method_roofline(prof, precision, updates_per_step, step_ms, workload=None, forms=None, interval=0,
                     crit_cells=0, crit_blocks=0):
     """Roofline of the timed window's dominant kernel (the largest share of a
     step: the criterion counts 1/interval of its launch time).  Algorithmic
@@ -589,8 +626,8 @@ def method_roofline(prof, precision, updates_per_step, step_ms, workload=None, v
     dom = max(per_step, key=per_step.get)
     alg = alg_of(dom)
     achieved = alg / (prof[dom]["ms"] * 1e-3) / 1e9
-    var = (variants or {}).get(dom)
-    t = measured_traffic(workload, dom, precision, var, crit=(dom == "criterion")) if workload else None
+    form = 0 if dom == "criterion" else (forms or {}).get(dom)
+    t = measured_traffic(workload, dom, precision, form) if workload else None
     step_alg = METHOD_VALUES * evsz * updates_per_step
     # every stage's launch time and share of a step; achieved and frac only
     # where the method gives the kernel a figure of its own (the step's
@@ -675,7 +712,7 @@ def jet_headline(steps, warmup, interval=5, precision=32, with_uvs=True, tune=Tr
            "nbar": float(np.sum(npts * ncells) / np.sum(ncells)), "n_cross": int(ncross), "device_bytes": int(mem_m),
            "variants": variants, "tiles": _tiles_summary(tiles),
            "roofline": method_roofline(prof, precision, ups, 1e3 * t_m / steps,
-                                       JET_WL + "-mlvs" if precision == 32 else None, variants, interval,
+                                       JET_WL + "-mlvs" if precision == 32 else None, _forms(tuned), interval,
                                        crit_cells=p.n_cells, crit_blocks=(p.nv // 2) ** 2)}
     if with_uvs:
         out["uvs"], f_u, mem_u, t_u = _jet_uvs(p, steps, warmup, precision, tune)
@@ -720,7 +757,7 @@ def _jet_uvs(p, steps, warmup, precision, tune):
     res = {"value": upd_u / t_u, "ms_per_step": 1e3 * t_u / steps, "device_bytes": int(mem_u), "variants": var_u,
            "tiles": _tiles_summary(tiles_u),
            "roofline": method_roofline(prof_u, precision, upd_u / steps, 1e3 * t_u / steps,
-                                       JET_WL + "-uvs" if precision == 32 else None, var_u)}
+                                       JET_WL + "-uvs" if precision == 32 else None, _forms(tuned_u))}
     return res, f_u, mem_u, t_u
 
 

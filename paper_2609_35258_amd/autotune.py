@@ -74,7 +74,8 @@ def _forms(solver, stage: str) -> list:
 
 def autotune(solver, precision: int, stages: Optional[Iterable[str]] = None, reps: int = 5,
              cache: Optional[str] = None, force: bool = False) -> Dict[str, dict]:
-    """Choose the fastest variant per stage; returns {stage: {variant, ms, key, from_cache}}.
+    """Choose the fastest variant per stage; returns {stage: {variant, form, ms, key, from_cache}}, form what
+    the variant launches (Solver.variant_form).
     stages: default, the tunable stages the solver's step launches."""
     if stages is None:
         stages = [st for st in solver.step_stages() if st in TUNABLE]
@@ -90,11 +91,11 @@ def autotune(solver, precision: int, stages: Optional[Iterable[str]] = None, rep
         if len(distinct) == 1:
             solver.time_stage(st, 1)
             ms = solver.time_stage(st, reps)
-            out[st] = {"variant": distinct[0], "ms": ms, "all_ms": [ms], "key": key, "from_cache": False}
+            out[st] = {"variant": distinct[0], "form": forms[0], "ms": ms, "all_ms": [ms], "key": key, "from_cache": False}
             continue
         if key in table and not force:
             solver.set_variant(st, table[key]["variant"])
-            out[st] = dict(table[key], key=key, from_cache=True)
+            out[st] = dict(table[key], form=forms[table[key]["variant"]], key=key, from_cache=True)
             continue
         times = []
         for v in distinct:
@@ -104,7 +105,7 @@ def autotune(solver, precision: int, stages: Optional[Iterable[str]] = None, rep
         best = distinct[min(range(len(times)), key=lambda k: times[k])]
         solver.set_variant(st, best)
         table[key] = {"variant": best, "ms": min(times), "all_ms": times}
-        out[st] = dict(table[key], key=key, from_cache=False)
+        out[st] = dict(table[key], form=forms[best], key=key, from_cache=False)
     _store(path, table)
     return out
 
