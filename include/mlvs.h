@@ -296,16 +296,19 @@ mlvs_status mlvs_set_variant(mlvs_ctx ctx, int stage, int variant);
 
 /* Replay each step as a HIP graph (on = 1): the launches of one step are
  * captured once per level set (again after every adaptation or level
- * change) and replayed with hipGraphLaunch.  Needs a non-default stream
+ * change) and replayed with hipGraphLaunch.  A level set whose levels have at
+ * most 1024 points (the fused step) gets a second graph after 64 replays, of
+ * eight steps, which takes the place of eight replays where a call has that many
+ * steps left and no adaptation is due among them.  Needs a non-default stream
  * (MLVS_E_STATE otherwise).  Results are identical to direct launches. */
 mlvs_status mlvs_set_graph(mlvs_ctx ctx, int on);
 
 /* Persistent step (the batched form of the step, north of Sec. 4.4's remark
  * on kernel organisation and synchronisation): on = 1 runs each time step as
  * ONE launch of a persistent kernel over the context's work lists (neighbour
- * rows, then cross-level and same-level faces, then update with the next
- * step's cell stage, stages separated by grid-wide barriers; velocity rows
- * whole), preceded by a one-thread kernel that clears its barrier counter.
+ * rows, then cross-level faces and the reconstruction, then face targets, then
+ * update with the next step's cell stage, stages separated by grid-wide
+ * barriers; velocity rows whole), preceded by a one-thread kernel that clears its barrier counter.
  * The kernel reads every work-list pointer and item count from a device
  * block the context rewrites in place at each level install, so with
  * mlvs_set_graph(ctx, 1) the captured step survives adaptations (captured
@@ -315,7 +318,8 @@ mlvs_status mlvs_set_graph(mlvs_ctx ctx, int on);
 mlvs_status mlvs_set_persistent(mlvs_ctx ctx, int on);
 
 /* Step launch statistics: *persistent the mode, *captures the number of step
- * graphs captured since creation, *launches the graph launches, *grid the
+ * graphs captured since creation, *launches the graph launches (each one step,
+ * or eight: see mlvs_set_graph), *grid the
  * persistent kernel's workgroup count (0 before its first launch), *error the
  * persistent kernel's sticky error flag (1: a grid barrier gave up waiting,
  * the step that set it is invalid).  Any pointer may be NULL; reading *error

@@ -1762,9 +1762,9 @@ void build_items(mlvs_ctx c) {
     }
     int nmax = 1;
     for (int l = 0; l < K; ++l) nmax = std::max(nmax, c->levels[l]->N);
-    // Velocity chunk of the streaming stages: whole rows (one item per face
-    // and per cell) unless there are too few faces to fill the GPU with
-    // waves, then the fewest chunks that do.  Levels of at most
+    // Velocity chunk of the streaming stages (reconstruction and update, a wave
+    // per cell and chunk): whole rows unless there are too few faces, about two
+    // per cell, to fill the GPU with waves, then the fewest chunks that do.  Levels of at most
     // FUSE_MAX_POINTS points always take whole rows and the fused step.
     constexpr int FUSE_MAX_POINTS = 1024, MIN_ITEMS = 16384;
     const int nf_all = std::max<int>(nF_all, 1);
@@ -3527,12 +3527,12 @@ void capture_steps(mlvs_ctx c, int steps, hipGraph_t& graph, hipGraphExec_t& exe
 }
 
 // One step of a call with `left` steps to go, or STEP_BATCH of them; returns how
-// many.  Between two graph launches the GPU idles for several microseconds, a
-// fifth of a small problem's step (1-D, 200 cells, FP64: 29.7 us a step
-// replayed singly, 23.4 by eights; cavity 64 x 64, 28^2: 264 and 255): level
-// sets of small levels (fused steps) replay STEP_BATCH steps as one graph,
-// captured after BATCH_AFTER single replays, so that a short run or a level set
-// that is soon replaced does not pay for the longer capture.
+// many.  Between two graph launches the GPU idles for about four microseconds, a
+// seventh of a small problem's step (FP64, replayed singly and by eights: 1-D with
+// 200 cells 31.2 and 26.9 us a step, cavity 16 x 16, 28^2 70.1 and 66.1, 64 x 64
+// 182 and 178): level sets of small levels (fused steps) replay STEP_BATCH steps
+// as one graph, captured after BATCH_AFTER single replays, so that a short run or
+// a level set that is soon replaced does not pay for the longer capture.
 constexpr int STEP_BATCH = 8, BATCH_AFTER = 64;
 int do_steps(mlvs_ctx c, int left) {
     const int64_t at = c->adaptive && c->ap.interval > 0 ? c->step_count % c->ap.interval : -1;

@@ -176,22 +176,6 @@ __device__ __forceinline__ gptr<T> gp(T* p) { return (gptr<T>)p; }
 template <typename S>
 __device__ __forceinline__ gptr<S> rowp(void* base, size_t off) { return gp(reinterpret_cast<S*>(base)) + off; }
 
-// The velocity of point i as the storage precision's kernels read it: FP64
-// storage reads the double coordinates, FP32 storage one (x, y) float pair
-// (half the bytes and one load instead of two; the rounding is that of the
-// stored values).
-template <typename S>
-__device__ __forceinline__ void load_xy(const LevelDesc& L, int i, double& x, double& y) {
-    if constexpr (sizeof(S) == 4) {
-        const unsigned long long b = gp(reinterpret_cast<const unsigned long long*>(L.xy32))[i];
-        x = __uint_as_float((unsigned)b);
-        y = __uint_as_float((unsigned)(b >> 32));
-    } else {
-        x = gp(L.xi_x)[i];
-        y = gp(L.xi_y)[i];
-    }
-}
-
 // Values a lane holds of one row: consecutive points, one 8-byte access.
 template <typename S>
 constexpr int VW = 8 / (int)sizeof(S);
@@ -844,13 +828,6 @@ __device__ __forceinline__ CellState cell_state(const double* cm, const Phys& ph
 template <typename S>
 constexpr bool UPDATE_RE = sizeof(S) == 4;
 
-// Cell stage: W, q, tau, compatibility coefficients (written to params) and
-// the rows phi_bar+ = alpha phi~ + beta phi_S* (Eq. g_h_eq_Pr with the
-// correction of Sec. 3.3.1).  The raw moments of g~, h~ come from cmom (the
-// previous update, or k_raw_moments after the state was set from outside).
-// The phi_bar+ row of one cell (Eq. bar_phi_transport): phi_bar+ = alpha
-// phi~ + beta phi_S* at every point of its level, phi_S* the (corrected)
-// target e.
 // The target in a face's or cell's record (layout FP_*).
 template <typename S>
 __device__ __forceinline__ void write_eq_record(double* o, const StepEq<S>& e) {
@@ -861,7 +838,10 @@ __device__ __forceinline__ StepEq<S> read_eq_record(const double* o) {
     return uni_eq(*reinterpret_cast<const StepEq<S>*>(o + FP_EQ));
 }
 
-// ST: rows too large for the caches, streamed past them.
+// The phi_bar+ row of one cell (Eq. bar_phi_transport): phi_bar+ = alpha
+// phi~ + beta phi_S* at every point of its level, e the (corrected) target with
+// beta folded and alpha as its c1.  ST: rows too large for the caches, streamed
+// past them.
 template <typename S, int U, bool ST>
 __device__ __forceinline__ void phibar_points(const LevelDesc& L, size_t row, const StepEq<S>& e) {
     constexpr int V = VW<S>;
@@ -934,6 +914,10 @@ __device__ __forceinline__ void write_params(double* pr, const CellState& cs, co
     pr[P_A3] = a[3]; pr[P_ALPHA] = cs.alpha; pr[P_BETA] = cs.beta;
 }
 
+// Cell stage: W, q, tau, compatibility coefficients (written to params) and
+// the rows phi_bar+ = alpha phi~ + beta phi_S* (Eq. g_h_eq_Pr with the
+// correction of Sec. 3.3.1).  The raw moments of g~, h~ come from cmom (the
+// previous update, or k_raw_moments after the state was set from outside).
 template <typename S, int U, int MINW, int CM, int IPW>
 __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __restrict__ lvs,
                                                          const int* __restrict__ cell_lev,
@@ -1015,7 +999,7 @@ __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __rest
 // only: state, correction and parameters by sixteen lanes per cell (records to
 // cpar), then the rows as a plain stream, at the rate of a copy.  Cylinder
 // 256 x 128, 101^2, FP32: 1.85 ms with sums over all points in the row pass,
-// 1.15 so; 1-D with 200 cells 28.0 -> 27.5 us a step.
+// 1.2 so; 1-D with 200 cells 28.0 -> 27.5 us a step.
 template <typename S>
 __global__ __launch_bounds__(BS) void k_cell_target_axes(const LevelDesc* __restrict__ lvs,
                                                          const int* __restrict__ cell_lev, int n_cells, Phys ph,
@@ -1437,17 +1421,6 @@ __device__ __forceinline__ void side_slope(const Side<S>& sd, int i, S (&f)[2], 
     }
 }
 
-// phi_bar+ of the side's cell extrapolated to the face at velocity index i:
-// phi_bar+ + (x_f - x_c - xi s) . sigma.
-template <typename S, typename SD>
-__device__ __forceinline__ void side_ext(const SD& sd, int i, S x, S y, S s, S& eg, S& eh) {
-    S f[2], sx[2], sy[2];
-    side_slope<S>(sd, i, f, sx, sy);
-    const S ax = sd.dx - x * s, ay = sd.dy - y * s;
-    eg = f[0] + ax * sx[0] + ay * sy[0];
-    eh = f[1] + ax * sx[1] + ay * sy[1];
-}
-
 // Face state from the reduced raw moments of phi_bar_f (Eq. W_from_bar,
 // q_f = 2 tau_f q_bar / (2 tau_f + s Pr)), the compatibility coefficients of
 // the face target, and the recovery weights c1 = 2 tau_f/(2 tau_f + s),
@@ -1627,19 +1600,20 @@ __device__ __forceinline__ void stencil_slope(const USide<S>& a, const S (&v)[5]
 // value to its sums.  Points are stored by velocity angle, so a wave's points
 // nearly always all leave or all enter through a face and the face is skipped
 // whole.  Boundary faces: outgoing rows and moments, with double velocities as
-// in the update, so that a diffuse wall's zero net mass flux holds there for
-// either storage precision.
+// in the update, so that a diffuse wall's zero net mass flux holds there to the
+// roundings of its target (see wall_inflow) for either storage precision.
 //
 // The batch after the one in work is on its way to LDS (loads that pass by the
 // registers): a wave's ten stencil rows, velocities and weights take 7 KB, and
 // no register is held for them (loads two batches ahead into registers: 2.85 ms
 // on the cylinder below).
 //
-// Bound by memory traffic with half of the vector issue slots taken.  Time with
-// one wave per face, and so: cylinder 256 x 128, 101^2, FP32 4.02 -> 2.53 ms
-// (4 TB/s); the same with merged levels .64 -> .48; jet 512 x 256 with merged
-// levels, FP32 1.11 -> .73; two-cavity triangles (9504 cells, 101^2) 1.25 ->
-// .97 ms.
+// Bound by memory traffic with half of the vector issue slots taken.  Time of
+// the stage alone with one wave per face, and so, FP32: cylinder 256 x 128, 101^2
+// 4.02 -> 2.56 ms (9.9 GB, 3.8 TB/s); the same with merged levels .64 -> .49; jet
+// 256 x 128, 161^2, with merged levels 1.11 -> .75; two-cavity triangles (9504
+// cells, 101^2) 1.25 -> .83 ms with the limiter above.  In a step with merged
+// levels the cross-level faces run beside it: .59 (cylinder) and 1.07 ms (jet).
 constexpr int REC_ROWS = 14;           // 512-byte pieces of a batch: stencil rows, velocities, weights
 
 // Batch b0 (64 V points) to the wave's LDS area `to`: lanes 0..31 fetch one
@@ -1748,7 +1722,12 @@ __device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const
                 slow[n] = __ballot(any[0] || any[1]) & ~fast[n];
             }
         }
-        // the fetch is done when only the stores after it are left
+        // the fetch is done when only the four stores after it can be left: loads
+        // and stores count in issue order, and anything else issued since (spills,
+        // the angles) only makes the wait longer.  It would be too short if fewer
+        // than four were issued after the fetch: the memory clobbers keep stores of
+        // one batch between its fetch and this wait, and two stores of different
+        // rows are never one instruction
         if (stores == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         vec<S, V> st[2][5];
@@ -2699,7 +2678,8 @@ constexpr int N_VARIANTS = 5;
 // ... and for the staged kernels, per compatibility order and items per wave.
 // The 64 sums of eight moments need 256 registers: at four waves per SIMD (128)
 // every variant spilled 480 to 690 of them (cylinder 95 x 45, 61^2, FP64:
-// update 0.68 ms, 0.15 ms at two waves).  From IPW_MIN items on a wave takes
+// update 0.68 ms, 0.15 ms at two waves, where 12 to 36 still spill, and in the
+// staged kernels over 2000 scalar ones, on the 64 sums' way to LDS).  From IPW_MIN items on a wave takes
 // four: the scalar chain, as long as the sums of 1200 points, then serves 32
 // items at once; fewer items would leave compute units without a workgroup.
 // Merged levels, FP32, one item per wave and four: face targets of 9.3e3 faces
