@@ -9,18 +9,14 @@ namespace mlvs {
 // (about 1e-7).
 constexpr int ANG_QUARTER = 1 << 30, ANG_MARGIN = 1 << 14;
 
-// Whether every angle of the run from a0 on to a1 (counted upwards, across the
-// wrap as well) is within a quarter turn, less the margin, of the direction n
-// (of the opposite one for `in`).  Unsigned throughout: the differences wrap.
-constexpr bool ang_within(unsigned a0, unsigned a1, unsigned n) {
-    constexpr unsigned W = 2u * (unsigned)(ANG_QUARTER - ANG_MARGIN);
-    const unsigned span = a1 - a0;
-    return span <= W && a0 - n + W / 2 <= W - span;
-}
-// ... velocities that all leave through a face of outward normal n, or all enter.
-constexpr bool ang_out(int a0, int a1, int n) { return ang_within((unsigned)a0, (unsigned)a1, (unsigned)n); }
-constexpr bool ang_in(int a0, int a1, int n) {
-    return ang_within((unsigned)a0, (unsigned)a1, (unsigned)n + 0x80000000u);
-}
+// A run of angles from a0 on to a1 and a face of outward normal n: whether all of
+// the run is within a quarter turn, less the margin, of n (velocities that all
+// leave) or of the opposite direction (all enter), from span = ang_span(a0, a1) and
+// t = ang_turn(a0, n).  Unsigned: the differences wrap.
+constexpr unsigned ANG_HALF = 2u * (ANG_QUARTER - ANG_MARGIN);
+constexpr unsigned ang_span(int a0, int a1) { return (unsigned)a1 - (unsigned)a0; }
+constexpr unsigned ang_turn(int a0, int n) { return (unsigned)a0 - (unsigned)n + ANG_HALF / 2; }
+constexpr bool ang_out(unsigned span, unsigned t) { return span <= ANG_HALF && t <= ANG_HALF - span; }
+constexpr bool ang_in(unsigned span, unsigned t) { return span <= ANG_HALF && t + 0x80000000u <= ANG_HALF - span; }
 
 }  // namespace mlvs

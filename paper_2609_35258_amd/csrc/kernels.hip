@@ -1708,14 +1708,16 @@ __device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const
             const int lb = b0 + WL * V * lane_id(), le = min(end, lb + WL * V);
             const bool on = lb < end;
             const int a0 = gp(L.ang)[on ? 2 * (lb / WL) : 0], a1 = gp(L.ang)[on ? 2 * ((le - 1) / WL) + 1 : 0];
+            const unsigned span = ang_span(a0, a1);
 #pragma unroll
             for (int n = 0; n < NS; ++n) {
                 bool easy[2] = {false, false}, any[2] = {false, false};
 #pragma unroll
                 for (int m = 0; m < PER; ++m) {
                     const Slot<S>& sl = slot[PER * n + m];
-                    any[m] = on && sl.code >= 0 && !ang_in(a0, a1, sl.ang);
-                    easy[m] = any[m] && !sl.bnd && lb + WL * V <= end && ang_out(a0, a1, sl.ang);
+                    const unsigned t = ang_turn(a0, sl.ang);
+                    any[m] = on && sl.code >= 0 && !ang_in(span, t);
+                    easy[m] = any[m] && !sl.bnd && lb + WL * V <= end && ang_out(span, t);
                 }
                 fast[n] = __ballot((easy[0] && !any[1]) || (easy[1] && !any[0]));
                 far[n] = __ballot(any[1]);

@@ -15,27 +15,29 @@ PROGRAM = r"""
 #include <cstdio>
 #include <random>
 using namespace mlvs;
+constexpr bool out(int a0, int a1, int n) { return ang_out(ang_span(a0, a1), ang_turn(a0, n)); }
+constexpr bool in(int a0, int a1, int n) { return ang_in(ang_span(a0, a1), ang_turn(a0, n)); }
 // the point at rest: the whole turn is within no quarter of any normal
-static_assert(!ang_out(INT_MIN, INT_MAX, 0) && !ang_in(INT_MIN, INT_MAX, 0), "");
-static_assert(!ang_out(INT_MIN, INT_MAX, INT_MIN) && !ang_in(INT_MIN, INT_MAX, INT_MAX), "");
+static_assert(!out(INT_MIN, INT_MAX, 0) && !in(INT_MIN, INT_MAX, 0), "");
+static_assert(!out(INT_MIN, INT_MAX, INT_MIN) && !in(INT_MIN, INT_MAX, INT_MAX), "");
 // normals and runs at the two ends of the range
-static_assert(ang_out(INT_MIN, INT_MIN + 9, INT_MAX) && !ang_in(INT_MIN, INT_MIN + 9, INT_MAX), "");
-static_assert(ang_out(INT_MAX - 9, INT_MAX, INT_MIN) && ang_in(INT_MAX - 9, INT_MAX, 0), "");
-static_assert(ang_in(INT_MIN, INT_MIN, 0) && ang_out(-5, 5, 0) && ang_in(-5, 5, INT_MIN), "");
+static_assert(out(INT_MIN, INT_MIN + 9, INT_MAX) && !in(INT_MIN, INT_MIN + 9, INT_MAX), "");
+static_assert(out(INT_MAX - 9, INT_MAX, INT_MIN) && in(INT_MAX - 9, INT_MAX, 0), "");
+static_assert(in(INT_MIN, INT_MIN, 0) && out(-5, 5, 0) && in(-5, 5, INT_MIN), "");
 // a right angle is neither, and the margin counts on both sides
-static_assert(!ang_out(ANG_QUARTER, ANG_QUARTER, 0) && !ang_in(ANG_QUARTER, ANG_QUARTER, 0), "");
-static_assert(!ang_out(0, ANG_QUARTER - ANG_MARGIN + 1, 0) && ang_out(0, ANG_QUARTER - ANG_MARGIN - 1, 0), "");
+static_assert(!out(ANG_QUARTER, ANG_QUARTER, 0) && !in(ANG_QUARTER, ANG_QUARTER, 0), "");
+static_assert(!out(0, ANG_QUARTER - ANG_MARGIN + 1, 0) && out(0, ANG_QUARTER - ANG_MARGIN - 1, 0), "");
 
 int main() {
     std::mt19937_64 rng(7);
     const double unit = 3.14159265358979323846 / 2147483648.0;
-    long bad = 0, out = 0, in = 0;
+    long bad = 0, n_out = 0, n_in = 0;
     for (int k = 0; k < 200000; ++k) {
         const int n = (int)(unsigned)rng(), a = (int)(unsigned)rng();
         const long long room = (long long)INT_MAX - a;
         const int b = a + (int)std::llround(room * std::pow(std::uniform_real_distribution<>()(rng), 8));
-        const bool o = ang_out(a, b, n), i = ang_in(a, b, n);
-        out += o; in += i;
+        const bool o = out(a, b, n), i = in(a, b, n);
+        n_out += o; n_in += i;
         if (o && i) ++bad;
         for (int t = 0; t <= 16; ++t) {       // xi . n over the run, ends included
             const double ang = unit * (a + (double)((long long)b - a) * t / 16);
@@ -43,8 +45,8 @@ int main() {
             if ((o && !(dn > 0)) || (i && !(dn < 0))) ++bad;
         }
     }
-    std::printf("%ld wrong, %ld out, %ld in\n", bad, out, in);
-    return bad != 0 || out < 10000 || in < 10000;
+    std::printf("%ld wrong, %ld out, %ld in\n", bad, n_out, n_in);
+    return bad != 0 || n_out < 10000 || n_in < 10000;
 }
 """
 
