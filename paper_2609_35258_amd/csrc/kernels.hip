@@ -373,15 +373,21 @@ struct StepEq {
 
 constexpr double LOG2E = 1.4426950408889634074;
 
-// k: FP32 storage uses the hardware base-2 exponential, FP64 exp().  rn: the
-// weight is folded into the value that the velocity sums of a correction or of a
-// wall's inflow were formed with, so that it adds its own rounding only.  One
-// item per lane.
+// The factor of c^2 in the exponent: FP32 storage uses the hardware base-2
+// exponential, FP64 exp().
+template <typename C>
+__device__ __forceinline__ C step_k(const Eq<double>& d) {
+    return (C)(sizeof(C) == 4 ? -d.i2RT * LOG2E : -d.i2RT);
+}
+
+// rn: the weight is folded into the value that the velocity sums of a correction
+// or of a wall's inflow were formed with, so that it adds its own rounding only.
+// One item per lane.
 template <typename C>
 __device__ __forceinline__ StepEq<C> step_eq_lane(const Eq<double>& d, double c1, double scale, int kind) {
     StepEq<C> e;
     e.rn = (C)(scale * (double)(C)d.rn); e.ux = (C)d.ux; e.uy = (C)d.uy;
-    e.k = (C)(sizeof(C) == 4 ? -d.i2RT * LOG2E : -d.i2RT);
+    e.k = step_k<C>(d);
     e.iRT = (C)d.iRT; e.RT = (C)d.RT; e.Xqx = (C)d.Xqx; e.Xqy = (C)d.Xqy;
     e.hiRT = (C)(d.cK * d.iRT); e.hD = (C)(d.Dd * d.cK + d.K2); e.cK = (C)d.cK; e.Dp2 = (C)d.Dp2;
     e.b0 = (C)d.b0; e.b1 = (C)d.b1; e.b2 = (C)d.b2; e.b3 = (C)d.b3;
@@ -1994,15 +2000,16 @@ __device__ __forceinline__ void face_moments(const double* fmom, int f, int nF, 
 //     flux, far-field Maxwellian, or the cell's phi_bar+ (zero-gradient
 //     outflow).
 // Incoming mass flux sum w (xi . n) g_w over xi . n < 0 of a diffuse wall's
-// Maxwellian es (unit density), in one wave (every lane holds the result).  es
-// is evaluated as the update will: in FP32 the exponent's factor is rounded
-// once, the same way for all points, and a sum of another form would leave that
-// rounding in the wall's mass balance, with one sign at every step.  Net flux
-// through four walls over the outgoing one, 40 wall temperatures, 28^2 and
-// 101^2, FP32: at most 1.3e-7 with eq_eval's form here, 5.4e-8 so.
+// Maxwellian d (unit density), in one wave (every lane holds the result).  It is
+// evaluated as step_eval does without heat flux and correction: in FP32 the
+// exponent's factor is rounded once, the same way for all points, and a sum of
+// another form would leave that rounding in the wall's mass balance, with one
+// sign at every step.  Net flux through four walls over the outgoing one, 40 wall
+// temperatures, 28^2 to 101^2, FP32: at most 1.5e-7 with eq_eval here, 5.8e-8 so.
 template <typename S, int U>
-__device__ __forceinline__ double wall_inflow(const LevelDesc& L, const FaceItem& F, const StepEq<S>& es) {
+__device__ __forceinline__ double wall_inflow(const LevelDesc& L, const FaceItem& F, const Eq<double>& d) {
     const int N = L.N;
+    const S rn = uni((S)d.rn), ux = uni((S)d.ux), uy = uni((S)d.uy), k = uni(step_k<S>(d));
     double m1[1] = {0.0};
     for (int i0 = lane_id(); i0 < N; i0 += WL * U) {
         double xv[U], yv[U], wv[U];
@@ -2016,8 +2023,8 @@ __device__ __forceinline__ double wall_inflow(const LevelDesc& L, const FaceItem
         for (int q = 0; q < U; ++q) {
             const double dn = xv[q] * F.nx + yv[q] * F.ny;
             if (dn < 0) {
-                S gs, hs;
-                target_eval<S>(es, (S)xv[q], (S)yv[q], gs, hs);
+                const S cx = (S)xv[q] - ux, cy = (S)yv[q] - uy;
+                const S gs = rn * kexp(fma_(cx, cx, cy * cy) * k);
                 m1[0] += wv[q] * dn * (double)gs;
             }
         }
@@ -2094,7 +2101,7 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
                     }
                 }
             } else if (bcs[-1 - F.R].kind == 1) {
-                const double m1 = wall_inflow<S, U>(L, F, step_eq<S>(sh_e[j]));
+                const double m1 = wall_inflow<S, U>(L, F, sh_e[j]);
                 if (lane_id() == 0) sh_m[j][1] = m1;      // [0] keeps the outgoing flux
             }
         }
@@ -2174,7 +2181,7 @@ __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ 
                              : make_eq(1.0, bc.u, bc.v, bc.T, 0.0, 0.0, nullptr, ph);
             c1 = F.area;
             c2 = F.area;
-            if (bc.kind == 1) c2 = F.area * (-m[0] / wall_inflow<S, U>(L, F, step_eq<S>(e)));
+            if (bc.kind == 1) c2 = F.area * (-m[0] / wall_inflow<S, U>(L, F, e));
         }
         if (lane_id() == 0) write_face_record<S>(fpar + (size_t)f * NFP, kind, F, c1, c2, e);
     }
