@@ -417,7 +417,8 @@ def stage_kernels(stage, form, precision):
     if stage == "face_target":
         return target("k_face_target", ["k_face_target_axes<%s>" % S])
     if stage == "face":
-        return rec + target("k_face_target", ["k_face_target_axes<%s>" % S])
+        return rec + (["k_face_target_wave<%s,1,2,%d>" % (S, 8 if fam & 16 else 4)] if fam & 256
+                      else target("k_face_target", ["k_face_target_axes<%s>" % S]))
     if stage == "xface":
         return ["k_xface<%s,%d,%d>" % (S, (2 if precision == 32 else 1) if v == 2 else (4 if precision == 32 else 2),
                                        1 if fam & 32 else 0)]

@@ -1099,7 +1099,7 @@ struct mlvs_ctx_s {
     int chunk = 1024;                  // velocity points per chunk (multiple of 64), set per level set
     int chunk_env = 0;                 // MLVS_CHUNK: a fixed chunk instead of the chosen one
     int nch = 1;                       // chunks of the largest level
-    bool tensor = false;               // the level set is the base grid alone (see LevelDesc::axes)
+    bool tensor = false;               // the level set is the base grid alone and takes axis sums (LevelDesc::axes)
     double* d_cpar = nullptr;          // [n_cells][NFP] cell records
     double* d_fpar = nullptr;          // [faces + boundary faces][NFP] face records
     bool mom_valid = false;            // d_cmom matches the stored state
@@ -1387,6 +1387,20 @@ void update_step_args(mlvs_ctx c) {
     A.n_cells = c->mesh.n_cells;
     hip_check(hipMemcpyAsync(c->d_args, &A, sizeof A, hipMemcpyHostToDevice, c->st), "step args upload");
     hip_check(hipStreamSynchronize(c->st), "stream synchronize");
+}
+
+// Whether the correction on the tensor base grid is formed from axis sums rather
+// than from sums over all points.  Axis sums spread a target over sixteen lanes:
+// fewer operations, a longer chain with double exponentials in either storage
+// precision.  One dimension has nothing to factor: only FP64 with several faces
+// per SIMD gains (us a step, over points and so, 101 points: 200 cells 27.2 and
+// 31.1, 3000 45.3 and 46.1, 4000 58.2 and 57.1, 8000 104 and 99.6; FP32 200 25.9
+// and 31.8, 8000 90.8 and 93.0).  Two dimensions, a few cells on small grids: 12 x
+// 12, 8^2 FP32 30.0 and 33.4, 16^2 32.7 and 35.6, 20^2 43.4 and 45.2, 28^2 59.1 and
+// 59.2, FP64 72.5 and 70.2; 24 x 24, 20^2 FP64 56.6 and 53.4.
+bool axis_sums_pay(mlvs_ctx c) {
+    if (c->phys.dim == 1) return c->prec == 64 && c->mesh.n_cells >= 3500;
+    return c->mesh.n_cells >= 512 || c->base.N > 512;
 }
 
 // Build face/ghost/cross-face work lists, flux rows and per-cell codes for the
@@ -1722,7 +1736,7 @@ void build_items(mlvs_ctx c) {
         xitems[i].BfromI = (a_first ? T[3] : T[2]).at(base);
     }
     // one level that merges nothing: the tensor base grid itself
-    c->tensor = K == 1 && c->levels[0]->N == c->base.N;
+    c->tensor = K == 1 && c->levels[0]->N == c->base.N && axis_sums_pay(c);
     // level descriptors: representative levels then interface levels
     std::vector<LevelDesc> descs;
     for (int i = 0; i < K + (int)c->ifaces.size(); ++i) {
@@ -3129,7 +3143,7 @@ mlvs_status mlvs_variant_form(mlvs_ctx c, int stage, int v, int* form) {
         int cnt = 0;
         if (!c || !form || mlvs_variants(stage, &cnt) != MLVS_OK || v < 0 || v >= cnt)
             fail(MLVS_E_ARG, "bad arguments");
-        *form = variant_form(stage, v, c->ph.compat, c->ph.mesh_kind, c->tensor, c->mesh.n_cells,
+        *form = variant_form(stage, v, c->ph.compat, c->ph.mesh_kind, c->tensor, c->fused, c->mesh.n_cells,
                              c->n_faces + c->n_bfaces);
     });
 }
@@ -3614,10 +3628,10 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
                                              c->ph, c->d_fmom, c->chunk, c->nch, c->variant[stage]);
         if (stage == 2 || e != hipSuccess) return e;
         return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->n_faces, c->d_bcs, c->ph, c->d_fmom,
-                                  c->d_fpar, c->chunk, c->tensor, c->variant[7]);
+                                  c->d_fpar, c->chunk, c->tensor, c->fused, c->variant[7]);
     }
     case 3: return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->n_faces, c->d_bcs, c->ph, c->d_fmom,
-                                      c->d_fpar, c->chunk, c->tensor, c->variant[3]);
+                                      c->d_fpar, c->chunk, c->tensor, false, c->variant[3]);
     case 4: return launch_xface(c->prec, on ? on : c->st, c->d_lv, c->d_xfaces, c->n_xfaces, c->d_cell_slot, c->d_cell_nbr,
                                 c->d_geom, c->d_params, c->ph, c->d_neg, c->variant[4]);
     case 5: return launch_update(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->d_geom,

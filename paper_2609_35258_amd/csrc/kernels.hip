@@ -2137,8 +2137,8 @@ __global__ __launch_bounds__(GBS, MINW) void k_face_target(const LevelDesc* __re
 }
 
 // The target of one face in one wave (every lane holds the sums; lane 0
-// writes the record): a stage of the persistent step, and the boundary faces
-// of k_face_target_axes.  Same arithmetic as k_face_target.
+// writes the record): the fused step's, a stage of the persistent step, and the
+// boundary faces of k_face_target_axes.  Same arithmetic as k_face_target.
 template <typename S, int U, int CM>
 __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ lvs,
                                                   const FaceItem* __restrict__ items, int nF,
@@ -2185,6 +2185,21 @@ __device__ __forceinline__ void face_target_items(const LevelDesc* __restrict__ 
         }
         if (lane_id() == 0) write_face_record<S>(fpar + (size_t)f * NFP, kind, F, c1, c2, e);
     }
+}
+
+// A wave per face, for the small levels of the fused step: bound by latency, and
+// a workgroup's three hand-overs (k_face_target) are longer than the chain that
+// they save lanes on.  Steps, staged targets and so: 1-D, 200 cells, 101 points,
+// FP64 31.1 and 27.2 us (with sums over points, see axis_sums_pay); cavity 64 x
+// 64, 28^2, merged 417 and 400; eight moments, whose 64 sums need no way to LDS
+// here, 558 and 283 us.
+template <typename S, int U, int MINW, int CM>
+__global__ __launch_bounds__(BS, MINW) void k_face_target_wave(const LevelDesc* __restrict__ lvs,
+                                                               const FaceItem* __restrict__ items, int nF,
+                                                               const BCDev* __restrict__ bcs, Phys ph,
+                                                               const double* __restrict__ fmom,
+                                                               double* __restrict__ fpar, int CH) {
+    face_target_items<S, U, CM>(lvs, items, nF, bcs, ph, fmom, fpar, CH, item0(), istride());
 }
 
 // Face targets on the tensor base grid: sixteen lanes per interior face (faces
@@ -2855,12 +2870,25 @@ hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const 
 
 hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n, int n_in,
                               const BCDev* bcs, Phys ph, const double* fmom, double* fpar, int CH, bool axes,
-                              int var) {
+                              bool fused, int var) {
     if (n <= 0) return hipSuccess;
     if (axes && ph.compat != 8) {
         const int n_wg = n_in > 0 ? axes_grid(n_in) : 0, n_b = (n - n_in + MAXW - 1) / MAXW;
         MLVS_DISPATCH(prec, k_face_target_axes, dim3(n_wg + n_b), dim3(BS), 0, st, lv, items, n_in, n, bcs, ph, fmom,
                       fpar, CH, n_wg);
+        return hipGetLastError();
+    }
+    // From IPW_MIN faces on four staged items a wave are faster, except with eight
+    // moments (cavity 96 x 96, 28^2, merged, FP32: a step of 616 us, 625 by waves).
+    // One point pair a lane and two waves per SIMD: no spills (four waves: 1-D with
+    // 2000 cells, FP32, 41.8 us, 31.6 so).
+    if (fused && (ph.compat == 8 || n < IPW_MIN)) {
+        if (ph.compat == 8)
+            MLVS_LAUNCH_UWC(prec, k_face_target_wave, 1, 2, 8, dim3(grid_for(n)), dim3(BS), 0, st, lv, items, n, bcs,
+                            ph, fmom, fpar, CH);
+        else
+            MLVS_LAUNCH_UWC(prec, k_face_target_wave, 1, 2, 4, dim3(grid_for(n)), dim3(BS), 0, st, lv, items, n, bcs,
+                            ph, fmom, fpar, CH);
         return hipGetLastError();
     }
     MLVS_DISPATCH_VC(prec, var, ph.compat, k_face_target, n, dim3(GBS), 0, st, lv, items, n, bcs,
@@ -3705,8 +3733,8 @@ int persistent_variant_count() { return 2; }
 
 // What variant `var` of a stage launches (the rules of the dispatches above):
 // the kernel family times sixteen plus the index, where the index chooses.
-int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, int n_cells, int nF) {
-    enum { F_C8 = 16, F_UMESH = 32, F_TENSOR = 64, F_LARGE = 128 };
+int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, bool fused, int n_cells, int nF) {
+    enum { F_C8 = 16, F_UMESH = 32, F_TENSOR = 64, F_LARGE = 128, F_WAVE = 256 };
     const int c8 = compat == 8 ? F_C8 : 0, um = mesh_kind ? F_UMESH : 0, axes = tensor && !c8 ? F_TENSOR : 0;
     const int rec = um ? um : var;
     auto staged = [&](int n, int tensor_form) {
@@ -3718,7 +3746,7 @@ int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, int
     case 3: return staged(nF, axes);
     case 4: return um ? um : var == 2 ? 2 : 0;
     case 5: return var;
-    case 7: return rec | staged(nF, axes);
+    case 7: return rec | (fused && !axes && (c8 || nF < IPW_MIN) ? F_WAVE | c8 : staged(nF, axes));
     case 8: return (c8 | axes) + var;
     case 9: return (c8 | um | axes) + (um ? 0 : var);
     default: return 0;

@@ -45,7 +45,8 @@ struct LevelDesc {
     int stride;        // row stride in elements (multiple of 64)
     int n_rows_state;  // cells on this level
     int nx, ny;        // axes' nodes
-    const double* axes;     // the tensor base grid's x [nx], wx [nx], y [ny], wy [ny]; null on coarser levels
+    const double* axes;     // the tensor base grid's x [nx], wx [nx], y [ny], wy [ny], where the
+                            // correction is formed from axis sums; null elsewhere
     const double* xi_x;
     const double* xi_y;
     const double* w;
@@ -143,9 +144,10 @@ struct StepArgs {
 // Launch wrappers (kernels.hip).  `S` selects float (32) or double (64) storage.
 int variant_count();
 // Equal values: these variants of a stage launch the same kernels.
-int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, int n_cells, int nF);
+int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, bool fused, int n_cells, int nF);
 // order: the cells in traversal order (a permutation of 0..n_cells-1).  cpar:
-// n_cells records (NFP).  tensor: every level is the tensor base grid.
+// n_cells records (NFP).  tensor: every level is the tensor base grid and takes
+// axis sums.
 hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                             const int* cell_slot, const int* order, int n_cells, Phys ph, double* params,
                             const double* cmom, int CH, double* cpar, bool tensor, int var = 1);
@@ -159,10 +161,11 @@ hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const 
                            const int* cell_slot, const int* cell_nbr, const int* cell_frow, const int* order,
                            int n_cells, const FaceItem* items, int nF, const CellGeom* geom, const double* params,
                            Phys ph, double* fmom, int CH, int nch, int var = 1);
-// items: n_in interior faces, then boundary faces, n in all; axes: every level is the tensor base grid
+// items: n_in interior faces, then boundary faces, n in all; axes: every level is
+// the tensor base grid and takes axis sums; fused: a stage of the fused step
 hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n, int n_in,
                               const BCDev* bcs, Phys ph, const double* fmom, double* fpar, int CH, bool axes,
-                              int var = 1);
+                              bool fused, int var = 1);
 hipError_t launch_xface(int prec, hipStream_t st, const LevelDesc* lv, const XFaceItem* items, int n,
                         const int* cell_slot, const int* cell_nbr, const CellGeom* geom,
                         const double* params, Phys ph, unsigned long long* neg, int var = 1);

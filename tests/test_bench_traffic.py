@@ -12,7 +12,7 @@ import paper_2609_35258_amd as m
 
 STAGED = [0, 1, 2, 3, 4, 16, 128]
 FORMS = {"cell": STAGED + [64, 65, 66, 67, 68], "face_rec": [0, 1, 2, 3, 4, 32], "face_target": STAGED + [64],
-         "face": [0, 1, 2, 3, 4, 64, 65, 66, 67, 68], "xface": [0, 2, 32], "update": [0, 1, 2, 3, 4],
+         "face": [0, 1, 2, 3, 4, 64, 65, 66, 67, 68, 256, 257, 258, 259, 260, 272, 288, 304], "xface": [0, 2, 32], "update": [0, 1, 2, 3, 4],
          "update_cell": [0, 1, 2, 3, 4, 16, 17, 18, 19, 20], "criterion": [0]}
 
 
