@@ -9,14 +9,15 @@ namespace mlvs {
 // (about 1e-7).
 constexpr int ANG_QUARTER = 1 << 30, ANG_MARGIN = 1 << 14;
 
-// A run of angles from a0 on to a1 and a face of outward normal n: whether all of
-// the run is within a quarter turn, less the margin, of n (velocities that all
-// leave) or of the opposite direction (all enter), from span = ang_span(a0, a1) and
-// t = ang_turn(a0, n).  Unsigned: the differences wrap.
+// A run of angles from a0 on to a1 and a face of outward normal n.  With span =
+// ang_span(a0, a1) and t = ang_turn(a0, n), all of the run is within a quarter
+// turn, less the margin, of n (velocities that all leave) where span <= ANG_HALF
+// and t <= ANG_HALF - span, and of the opposite direction (all enter) where this
+// holds with t + 2^31.  Unsigned: the differences wrap.
 constexpr unsigned ANG_HALF = 2u * (ANG_QUARTER - ANG_MARGIN);
-constexpr unsigned ang_span(int a0, int a1) { return (unsigned)a1 - (unsigned)a0; }
-constexpr unsigned ang_turn(int a0, int n) { return (unsigned)a0 - (unsigned)n + ANG_HALF / 2; }
-constexpr bool ang_out(unsigned span, unsigned t) { return span <= ANG_HALF && t <= ANG_HALF - span; }
-constexpr bool ang_in(unsigned span, unsigned t) { return span <= ANG_HALF && t + 0x80000000u <= ANG_HALF - span; }
+__attribute__((always_inline)) constexpr unsigned ang_span(int a0, int a1) { return (unsigned)a1 - (unsigned)a0; }
+__attribute__((always_inline)) constexpr unsigned ang_turn(int a0, int n) {
+    return (unsigned)a0 - (unsigned)n + ANG_HALF / 2;
+}
 
 }  // namespace mlvs

@@ -1722,8 +1722,8 @@ __device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const
                 for (int m = 0; m < PER; ++m) {
                     const Slot<S>& sl = slot[PER * n + m];
                     const unsigned t = ang_turn(a0, sl.ang);
-                    any[m] = on && sl.code >= 0 && !ang_in(span, t);
-                    easy[m] = any[m] && !sl.bnd && lb + WL * V <= end && ang_out(span, t);
+                    any[m] = on && sl.code >= 0 && !(span <= ANG_HALF && t + 0x80000000u <= ANG_HALF - span);
+                    easy[m] = any[m] && !sl.bnd && lb + WL * V <= end && span <= ANG_HALF && t <= ANG_HALF - span;
                 }
                 fast[n] = __ballot((easy[0] && !any[1]) || (easy[1] && !any[0]));
                 far[n] = __ballot(any[1]);

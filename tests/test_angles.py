@@ -15,8 +15,9 @@ PROGRAM = r"""
 #include <cstdio>
 #include <random>
 using namespace mlvs;
-constexpr bool out(int a0, int a1, int n) { return ang_out(ang_span(a0, a1), ang_turn(a0, n)); }
-constexpr bool in(int a0, int a1, int n) { return ang_in(ang_span(a0, a1), ang_turn(a0, n)); }
+constexpr bool within(unsigned span, unsigned t) { return span <= ANG_HALF && t <= ANG_HALF - span; }
+constexpr bool out(int a0, int a1, int n) { return within(ang_span(a0, a1), ang_turn(a0, n)); }
+constexpr bool in(int a0, int a1, int n) { return within(ang_span(a0, a1), ang_turn(a0, n) + 0x80000000u); }
 // the point at rest: the whole turn is within no quarter of any normal
 static_assert(!out(INT_MIN, INT_MAX, 0) && !in(INT_MIN, INT_MAX, 0), "");
 static_assert(!out(INT_MIN, INT_MAX, INT_MIN) && !in(INT_MIN, INT_MAX, INT_MAX), "");
