@@ -3637,7 +3637,8 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
     case 5: return launch_update(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->d_geom,
                                  c->d_cell_frow, c->d_faces, c->d_fpar, c->d_cpar, c->d_params, c->ph, c->d_cmom,
                                  c->chunk, c->nch, c->variant[5]);
-    case 9: return launch_step_persistent(c->prec, c->st, c->d_args, c->d_sync, c->ph, c->variant[9],
+    case 9: return launch_step_persistent(c->prec, c->st, c->d_args, c->d_sync, c->ph,
+                                          (int)(c->mesh.faces.size() + c->mesh.bfaces.size()), c->variant[9],
                                           &c->persistent_grid);
     case 8: return launch_update_cell(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n,
                                       c->d_geom, c->d_cell_frow, c->d_faces, c->d_fpar, c->d_params, c->ph,

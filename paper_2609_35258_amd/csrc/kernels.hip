@@ -2005,7 +2005,7 @@ __device__ __forceinline__ void face_moments(const double* fmom, int f, int nF, 
 // exponent's factor is rounded once, the same way for all points, and a sum of
 // another form would leave that rounding in the wall's mass balance, with one
 // sign at every step.  Net flux through four walls over the outgoing one, 40 wall
-// temperatures, 28^2 to 101^2, FP32: at most 1.5e-7 with eq_eval here, 5.8e-8 so.
+// temperatures, 28^2 to 101^2, FP32: at most 1.5e-7 with eq_eval here, 6.6e-8 so.
 template <typename S, int U>
 __device__ __forceinline__ double wall_inflow(const LevelDesc& L, const FaceItem& F, const Eq<double>& d) {
     const int N = L.N;
@@ -3677,7 +3677,7 @@ __global__ __launch_bounds__(BS, MINW) void k_step_persistent(const StepArgs* __
     const int first = item0(), stride = istride();
     unsigned int phase = 0;
     ghost_items<S>(A->lvs, A->ghosts, A->n_ghosts, A->cell_lev, A->cell_slot, A->params, ph, A->neg, first, stride);
-    grid_barrier(A->sync, phase);
+    if (A->n_ghosts > 0) grid_barrier(A->sync, phase);      // the same count in every workgroup
     const int nx = A->n_xfaces;
     xface_items<S, MK>(A->lvs, A->xfaces, nx, A->cell_slot, A->cell_nbr, A->geom, A->params, ph, A->neg, first,
                           stride);
@@ -3698,8 +3698,13 @@ __global__ void k_sync_reset(unsigned int* sync) {
     if (threadIdx.x == 0) sync[0] = 0u;
 }
 
+// All workgroups that are resident at once, or as many as the longest stage of a
+// mesh has waves for (items; the loops stride, so any level set is served): a
+// barrier takes longer the more workgroups meet, each with a write-back of its
+// L2.  1-D with 200 cells: 157 us a step with 512 workgroups and a barrier behind
+// no neighbour rows, 42 with 56 and without.
 template <typename KF>
-static hipError_t persistent_grid(KF kernel, int* grid) {
+static hipError_t persistent_grid(KF kernel, int items, int* grid) {
     int dev = 0, ncu = 0, nb = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -3707,14 +3712,14 @@ static hipError_t persistent_grid(KF kernel, int* grid) {
     if (e != hipSuccess) return e;
     const int g = ncu * nb / NXCD * NXCD;
     if (g < NXCD) return hipErrorInvalidConfiguration;
-    *grid = g;
+    *grid = min(g, grid_for(items));
     return hipSuccess;
 }
 
 #define MLVS_PERSISTENT(S_, U_, C_, MK_)                                                         \
     do {                                                                                        \
         auto kf = k_step_persistent<S_, U_, 2, C_, MK_>;                                         \
-        if ((e = persistent_grid(kf, &g)) != hipSuccess) return e;                               \
+        if ((e = persistent_grid(kf, items, &g)) != hipSuccess) return e;                               \
         hipLaunchKernelGGL(kf, dim3(g), dim3(BS), 0, st, A, ph);                                 \
     } while (0)
 #define MLVS_PERSISTENT_C(S_, U_, MK_)                                                           \
@@ -3753,8 +3758,8 @@ int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, boo
     }
 }
 
-hipError_t launch_step_persistent(int prec, hipStream_t st, const StepArgs* A, unsigned int* sync, Phys ph, int var,
-                                  int* grid_used) {
+hipError_t launch_step_persistent(int prec, hipStream_t st, const StepArgs* A, unsigned int* sync, Phys ph, int items,
+                                  int var, int* grid_used) {
     hipError_t e = hipSuccess;
     int g = 0;
     hipLaunchKernelGGL(k_sync_reset, dim3(1), dim3(64), 0, st, sync);

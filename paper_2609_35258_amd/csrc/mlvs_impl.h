@@ -174,8 +174,9 @@ hipError_t launch_xface(int prec, hipStream_t st, const LevelDesc* lv, const XFa
 // `var` 0 or 1 (one or two velocity points per lane and load batch).  The
 // grid is the kernel's occupancy times the number of compute units.
 int persistent_variant_count();
-hipError_t launch_step_persistent(int prec, hipStream_t st, const StepArgs* A, unsigned int* sync, Phys ph, int var,
-                                  int* grid_used);
+// items: the most items of a stage over all level sets of the mesh.
+hipError_t launch_step_persistent(int prec, hipStream_t st, const StepArgs* A, unsigned int* sync, Phys ph, int items,
+                                  int var, int* grid_used);
 // Update and the next step's cell stage in one wave per cell, for level sets
 // that fit one velocity chunk.
 hipError_t launch_update_cell(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,

@@ -70,3 +70,30 @@ def test_wave_targets_over_two_levels_fp64(mesh, compat):
         e = state_error(g.get_state(), o.g, o.h)
         assert max(e) < 1e-12, (k, e)
     g.close()
+
+
+@pytest.mark.parametrize("case", ["sod", "cavity", "two_levels"])
+def test_persistent_step_of_a_small_mesh(case):
+    # one workgroup per four faces, in eights, where fewer than fit the device;
+    # no neighbour rows and no barrier behind them except over two levels
+    import paper_2609_35258_amd as m
+    p = W.sod_1d(37, Kn=0.1, nv=33, vmax=6.0) if case == "sod" else W.cavity(6, nv=12, vel_kind="nc", vmax=4.5)
+    p = W.perturb(p, seed=4)
+    a, b = (m.Solver.from_problem(p, graph=True) for _ in range(2))
+    if case == "two_levels":
+        nb = p.nv // 2
+        far = np.abs(np.arange(nb) - (nb - 1) / 2) > 1.6
+        kap = np.stack([np.zeros(nb * nb, np.uint8), (far[:, None] | far[None, :]).astype(np.uint8).ravel()])
+        for s in (a, b):
+            s.set_levels(kap, (np.arange(p.n_cells) // 3 % 2).astype(np.int32))
+    b.set_persistent(True)
+    for k in range(4):
+        a.step(1)
+        b.step(1)
+        for x, y in zip(a.get_state(), b.get_state()):
+            assert np.array_equal(x[0], y[0]) and np.array_equal(x[1], y[1]), k
+    info = b.graph_info()
+    faces = 38 if case == "sod" else 84
+    assert info["error"] == 0 and info["grid"] == 8 * -(-faces // 32)
+    a.close()
+    b.close()
