@@ -397,6 +397,7 @@ def stage_kernels(stage, form, precision):
     """Names of the kernels that a stage launches in a given form (Solver.variant_form: the kernel family, and
     below 16 the variant index where it chooses), as in profiles/traffic.txt."""
     fam, v = form // 16 * 16, form % 16
+    rows = "_cached" if fam & 512 else ""          # rows kept in the caches, not streamed
     S = "double" if precision == 64 else "float"
     staged = ((1, 4), (2, 4), (4, 2), (4, 4), (1, 2))
 
@@ -409,9 +410,10 @@ def stage_kernels(stage, form, precision):
             return ["%s<%s,2,4,4,4>" % (name, S)]
         return ["%s<%s,%d,%d,4,1>" % ((name, S) + staged[v])]
 
-    rec = ["k_face_rec<%s,2,1>" % S if fam & 32 else "k_face_rec<%s,%d,0>" % (S, (2, 3, 4, 5, 1)[v])]
+    rec = ["k_face_rec%s<%s,%s>" % (rows, S, "2,1" if fam & 32 else "%d,0" % (2, 3, 4, 5, 1)[v])]
     if stage == "cell":
-        return target("k_cell_prep", ["k_cell_target_axes<%s>" % S, "k_phibar<%s,%d,%d>" % ((S,) + staged[v])])
+        return target("k_cell_prep" + rows,
+                      ["k_cell_target_axes<%s>" % S, "k_phibar%s<%s,%d,%d>" % ((rows, S) + staged[v])])
     if stage == "face_rec":
         return rec
     if stage == "face_target":
@@ -423,7 +425,7 @@ def stage_kernels(stage, form, precision):
         return ["k_xface<%s,%d,%d>" % (S, (2 if precision == 32 else 1) if v == 2 else (4 if precision == 32 else 2),
                                        1 if fam & 32 else 0)]
     if stage == "update":
-        return ["k_update<%s,%d,%d>" % ((S,) + ((1, 4), (2, 3), (4, 2), (2, 2), (1, 3))[v])]
+        return ["k_update%s<%s,%d,%d>" % ((rows, S) + ((1, 4), (2, 3), (4, 2), (2, 2), (1, 3))[v])]
     if stage == "update_cell":
         return ["k_update_cell<%s,%d,%d,%d>" % ((S,) + ((1, 2), (2, 2), (4, 2), (2, 3), (4, 1))[v]
                                                 + (8 if fam & 16 else 4,))]

@@ -1100,6 +1100,7 @@ struct mlvs_ctx_s {
     int chunk_env = 0;                 // MLVS_CHUNK: a fixed chunk instead of the chosen one
     int nch = 1;                       // chunks of the largest level
     bool tensor = false;               // the level set is the base grid alone and takes axis sums (LevelDesc::axes)
+    bool stream = false;               // its rows are larger than the caches (see build_items)
     double* d_cpar = nullptr;          // [n_cells][NFP] cell records
     double* d_fpar = nullptr;          // [faces + boundary faces][NFP] face records
     bool mom_valid = false;            // d_cmom matches the stored state
@@ -1737,6 +1738,16 @@ void build_items(mlvs_ctx c) {
     }
     // one level that merges nothing: the tensor base grid itself
     c->tensor = K == 1 && c->levels[0]->N == c->base.N && axis_sums_pay(c);
+    // Rows that the next stage does not find in the caches any more (256 MB behind
+    // the L2s) are streamed past them, in favour of those that two items read.  A
+    // step has six to eight arrays of such rows; by the bytes of one, us a step kept
+    // in the caches and streamed, cavity, 81^2 points: FP32 21 MB 194 and 207, 27 MB
+    // 231 and 246, 42 MB 317 and 293, 82 MB 567 and 493; FP64 30 MB 254 and 282, 41 MB
+    // 314 and 324, 54 MB 413 and 369.
+    constexpr double CACHED_ROWS = 40e6;
+    double row_bytes = 0.0;
+    for (int l = 0; l < K; ++l) row_bytes += (double)c->levels[l]->n_cells * c->levels[l]->stride * c->elt();
+    c->stream = row_bytes >= CACHED_ROWS;
     // level descriptors: representative levels then interface levels
     std::vector<LevelDesc> descs;
     for (int i = 0; i < K + (int)c->ifaces.size(); ++i) {
@@ -3143,8 +3154,8 @@ mlvs_status mlvs_variant_form(mlvs_ctx c, int stage, int v, int* form) {
         int cnt = 0;
         if (!c || !form || mlvs_variants(stage, &cnt) != MLVS_OK || v < 0 || v >= cnt)
             fail(MLVS_E_ARG, "bad arguments");
-        *form = variant_form(stage, v, c->ph.compat, c->ph.mesh_kind, c->tensor, c->fused, c->mesh.n_cells,
-                             c->n_faces + c->n_bfaces);
+        *form = variant_form(stage, v, c->ph.compat, c->ph.mesh_kind, c->tensor, c->fused, c->stream,
+                             c->mesh.n_cells, c->n_faces + c->n_bfaces);
     });
 }
 
@@ -3619,13 +3630,14 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
     const int nf = c->n_faces + c->n_bfaces;
     switch (stage) {
     case 0: return launch_cell_prep(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->ph,
-                                    c->d_params, c->d_cmom, c->chunk, c->d_cpar, c->tensor, c->variant[0]);
+                                    c->d_params, c->d_cmom, c->chunk, c->d_cpar, c->tensor, c->stream,
+                                    c->variant[0]);
     case 1: return launch_ghost(c->prec, c->st, c->d_lv, c->d_ghosts, c->n_ghosts, c->d_cell_lev, c->d_cell_slot,
                                 c->d_params, c->ph, c->d_neg);
     case 2: case 7: {
         const hipError_t e = launch_face_rec(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_cell_nbr,
                                              c->d_cell_frow, c->d_order, n, c->d_faces, nf, c->d_geom, c->d_params,
-                                             c->ph, c->d_fmom, c->chunk, c->nch, c->variant[stage]);
+                                             c->ph, c->d_fmom, c->chunk, c->nch, c->stream, c->variant[stage]);
         if (stage == 2 || e != hipSuccess) return e;
         return launch_face_target(c->prec, c->st, c->d_lv, c->d_faces, nf, c->n_faces, c->d_bcs, c->ph, c->d_fmom,
                                   c->d_fpar, c->chunk, c->tensor, c->fused, c->variant[7]);
@@ -3636,7 +3648,7 @@ hipError_t launch_stage(mlvs_ctx c, int stage, hipStream_t on) {
                                 c->d_geom, c->d_params, c->ph, c->d_neg, c->variant[4]);
     case 5: return launch_update(c->prec, c->st, c->d_lv, c->d_cell_lev, c->d_cell_slot, c->d_order, n, c->d_geom,
                                  c->d_cell_frow, c->d_faces, c->d_fpar, c->d_cpar, c->d_params, c->ph, c->d_cmom,
-                                 c->chunk, c->nch, c->variant[5]);
+                                 c->chunk, c->nch, c->stream, c->variant[5]);
     case 9: return launch_step_persistent(c->prec, c->st, c->d_args, c->d_sync, c->ph,
                                           (int)(c->mesh.faces.size() + c->mesh.bfaces.size()), c->variant[9],
                                           &c->persistent_grid);

@@ -924,14 +924,11 @@ __device__ __forceinline__ void write_params(double* pr, const CellState& cs, co
 // the rows phi_bar+ = alpha phi~ + beta phi_S* (Eq. g_h_eq_Pr with the
 // correction of Sec. 3.3.1).  The raw moments of g~, h~ come from cmom (the
 // previous update, or k_raw_moments after the state was set from outside).
-template <typename S, int U, int MINW, int CM, int IPW>
-__global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __restrict__ lvs,
-                                                         const int* __restrict__ cell_lev,
-                                                         const int* __restrict__ cell_slot,
-                                                         const int* __restrict__ order, int n_cells, Phys ph,
-                                                         double* __restrict__ params,
-                                                         const double* __restrict__ cmom, int CH,
-                                                         double* __restrict__ cpar) {
+template <typename S, int U, int CM, int IPW, bool ST>
+__device__ __forceinline__ void cell_prep_items(const LevelDesc* __restrict__ lvs, const int* __restrict__ cell_lev,
+                                                const int* __restrict__ cell_slot, const int* __restrict__ order,
+                                                int n_cells, Phys ph, double* __restrict__ params,
+                                                const double* __restrict__ cmom, int CH, double* __restrict__ cpar) {
     constexpr int GW = GWV * IPW;
     static_assert(GW <= WL, "the scalar steps run on the lanes of one wave");
     constexpr int NS = CM == 8 ? 64 : 13;      // compatibility sums per item
@@ -995,10 +992,32 @@ __global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __rest
             const LevelDesc& L = lvs[cell_lev[c]];
             const StepEq<S> e = step_eq<S>(sh_e[j], sh_c[j].alpha, sh_c[j].beta);
             if (UPDATE_RE<S> && lane_id() == 0) write_eq_record<S>(cpar + (size_t)c * NFP, e);
-            phibar_points<S, U, true>(L, (size_t)cell_slot[c] * L.stride, e);
+            phibar_points<S, U, ST>(L, (size_t)cell_slot[c] * L.stride, e);
         }
         __syncthreads();
     }
+}
+
+template <typename S, int U, int MINW, int CM, int IPW>
+__global__ __launch_bounds__(GBS, MINW) void k_cell_prep(const LevelDesc* __restrict__ lvs,
+                                                         const int* __restrict__ cell_lev,
+                                                         const int* __restrict__ cell_slot,
+                                                         const int* __restrict__ order, int n_cells, Phys ph,
+                                                         double* __restrict__ params,
+                                                         const double* __restrict__ cmom, int CH,
+                                                         double* __restrict__ cpar) {
+    cell_prep_items<S, U, CM, IPW, true>(lvs, cell_lev, cell_slot, order, n_cells, ph, params, cmom, CH, cpar);
+}
+
+template <typename S, int U, int MINW, int CM, int IPW>
+__global__ __launch_bounds__(GBS, MINW) void k_cell_prep_cached(const LevelDesc* __restrict__ lvs,
+                                                                const int* __restrict__ cell_lev,
+                                                                const int* __restrict__ cell_slot,
+                                                                const int* __restrict__ order, int n_cells, Phys ph,
+                                                                double* __restrict__ params,
+                                                                const double* __restrict__ cmom, int CH,
+                                                                double* __restrict__ cpar) {
+    cell_prep_items<S, U, CM, IPW, false>(lvs, cell_lev, cell_slot, order, n_cells, ph, params, cmom, CH, cpar);
 }
 
 // Cell stage on the tensor base grid, where the correction costs axis sums
@@ -1038,6 +1057,18 @@ __global__ __launch_bounds__(BS, MINW) void k_phibar(const LevelDesc* __restrict
         const int c = order[it];
         const LevelDesc& L = lvs[cell_lev[c]];
         phibar_points<S, U, true>(L, (size_t)cell_slot[c] * L.stride, read_eq_record<S>(cpar + (size_t)c * NFP));
+    }
+}
+template <typename S, int U, int MINW>
+__global__ __launch_bounds__(BS, MINW) void k_phibar_cached(const LevelDesc* __restrict__ lvs,
+                                                            const int* __restrict__ cell_lev,
+                                                            const int* __restrict__ cell_slot,
+                                                            const int* __restrict__ order,
+                                                            int n_cells, const double* __restrict__ cpar) {
+    for (int it = item0(); it < n_cells; it += istride()) {
+        const int c = order[it];
+        const LevelDesc& L = lvs[cell_lev[c]];
+        phibar_points<S, U, false>(L, (size_t)cell_slot[c] * L.stride, read_eq_record<S>(cpar + (size_t)c * NFP));
     }
 }
 
@@ -1655,7 +1686,7 @@ struct Slot {
     gptr<S> rg, rh;                    // face rows
 };
 
-template <typename S, int MK>
+template <typename S, int MK, bool ST>
 __device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const SideOf<S, MK>& sd,
                                                 const int* cell_frow, const FaceItem* items, const CellGeom& gm,
                                                 const Phys& ph, int beg, int end, double u0, double v0,
@@ -1787,8 +1818,8 @@ __device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const
                 // one slot, left by all points of the batch
                 const int k = PER * n + s1 * (PER - 1);
                 reach(sl, e[n]);
-                stv_nt<V>(sl.rg, i, e[n][0]);
-                stv_nt<V>(sl.rh, i, e[n][1]);
+                if (ST) { stv_nt<V>(sl.rg, i, e[n][0]); stv_nt<V>(sl.rh, i, e[n][1]); }
+                else { stv<V>(sl.rg, i, e[n][0]); stv<V>(sl.rh, i, e[n][1]); }
                 if (stores >= 0) stores += 2;
                 act[n] = true;
                 if (own[n] != k) {
@@ -1885,7 +1916,7 @@ __device__ __forceinline__ void cell_rec_points(const LevelDesc& L, int c, const
 
 // Pairs (velocity chunk, cell) [first, n) with stride `stride`: the loop of the
 // kernel below, and one stage of the persistent step.
-template <typename S, int MK>
+template <typename S, int MK, bool ST>
 __device__ __forceinline__ void cell_rec_items(const LevelDesc* __restrict__ lvs, const int* __restrict__ cell_lev,
                                                const int* __restrict__ cell_slot, const int* __restrict__ cell_nbr,
                                                const int* __restrict__ cell_frow, const int* __restrict__ order,
@@ -1910,7 +1941,7 @@ __device__ __forceinline__ void cell_rec_items(const LevelDesc* __restrict__ lvs
         const double u0 = params[(size_t)c * NPARAM + P_U], v0 = params[(size_t)c * NPARAM + P_V];
         SideOf<S, MK> sd;
         load_side<S>(sd, L, c, cell_slot, cell_nbr, geom, 0.0, 0.0);
-        cell_rec_points<S, MK>(L, c, sd, cell_frow, items, geom[c], ph, beg, end, u0, v0, tot, sh_in[w]);
+        cell_rec_points<S, MK, ST>(L, c, sd, cell_frow, items, geom[c], ph, beg, end, u0, v0, tot, sh_in[w]);
         // lane 16 r + j writes moment j of slot r
         const int cd = cell_frow[4 * c + r];
         wave_lds_order();
@@ -1930,8 +1961,22 @@ __global__ __launch_bounds__(BS, MINW) void k_face_rec(const LevelDesc* __restri
                                                        const CellGeom* __restrict__ geom,
                                                        const double* __restrict__ params, Phys ph,
                                                        double* __restrict__ fmom, int CH, int nch) {
-    cell_rec_items<S, MK>(lvs, cell_lev, cell_slot, cell_nbr, cell_frow, order, n_cells, items, nF, geom, params, ph,
-                          fmom, CH, nch, item0(), istride());
+    cell_rec_items<S, MK, true>(lvs, cell_lev, cell_slot, cell_nbr, cell_frow, order, n_cells, items, nF, geom,
+                                params, ph, fmom, CH, nch, item0(), istride());
+}
+template <typename S, int MINW, int MK>
+__global__ __launch_bounds__(BS, MINW) void k_face_rec_cached(const LevelDesc* __restrict__ lvs,
+                                                              const int* __restrict__ cell_lev,
+                                                              const int* __restrict__ cell_slot,
+                                                              const int* __restrict__ cell_nbr,
+                                                              const int* __restrict__ cell_frow,
+                                                              const int* __restrict__ order, int n_cells,
+                                                              const FaceItem* __restrict__ items, int nF,
+                                                              const CellGeom* __restrict__ geom,
+                                                              const double* __restrict__ params, Phys ph,
+                                                              double* __restrict__ fmom, int CH, int nch) {
+    cell_rec_items<S, MK, false>(lvs, cell_lev, cell_slot, cell_nbr, cell_frow, order, n_cells, items, nF, geom,
+                                params, ph, fmom, CH, nch, item0(), istride());
 }
 
 // Raw moments of phi_bar_f of one face from its two halves (chunk partials
@@ -2247,25 +2292,24 @@ __global__ __launch_bounds__(BS) void k_face_target_axes(const LevelDesc* __rest
 // ---------------------------------------------------------------------------
 // One cell over points [beg, N) of its level; m: the raw moments of the new
 // state about the step's cell velocity (u0, v0).
-// ST: the staged step, whose rows are too large for the caches: the cell's own
-// rows stream past them and leave them to the face rows, which two cells read.
+// ST: rows too large for the caches: the cell's own stream past them and leave
+// them to the face rows, which two cells read.
 // Bound by memory traffic (16 of 40 bytes a point are the face rows' in FP32),
 // at three quarters of the vector issue slots before the target's constants
 // were folded and the records kept in storage precision.  Lanes take the points
 // in pairs in FP32 (8-byte accesses).  Cylinder 256 x 128, 101^2, FP32: 3.39
 // -> 2.90 ms; with merged levels .535 -> .437; two-cavity .859 -> .761 ms.
-// UPDATE_RE: forming phi_bar+ again from phi~ and the cell's record (24
+// RE (UPDATE_RE, the staged step): forming phi_bar+ again from phi~ and the cell's record (24
 // instructions) instead of reading its rows saves 8 of those 40 bytes: 2.90 ->
 // 2.61, .437 -> .417 and .761 -> .667 ms.  In FP64 the fifth exponential costs
 // more than the 16 bytes (cylinder 128 x 64, 101^2: 1.53 ms reading, 1.56 so;
 // cavity 48 x 48, 65^2: .186 and .201); a fused step finds its rows in the caches.
-template <typename S, int U, bool ST>
+template <typename S, int U, bool RE, bool ST>
 __device__ __forceinline__ void update_points(const LevelDesc& L, int c, const int* cell_slot, const CellGeom* geom,
                                               const int* cell_frow, const FaceItem* items, const double* fpar,
                                               const double* cpar, const double* params, const Phys& ph, int beg, int N,
                                               double (&m)[11], double& u0, double& v0) {
     constexpr int V = VW<S>;
-    constexpr bool RE = ST && UPDATE_RE<S>;
     const S c43 = (S)(4.0 / 3.0), c13 = (S)(1.0 / 3.0);
     const size_t row = (size_t)cell_slot[c] * L.stride;
     auto g = rowp<S>(L.g, row);
@@ -2402,6 +2446,33 @@ __device__ __forceinline__ void update_points(const LevelDesc& L, int c, const i
     }
 }
 
+template <typename S, int U, bool ST>
+__device__ __forceinline__ void update_items(const LevelDesc* __restrict__ lvs, const int* __restrict__ cell_lev,
+                                             const int* __restrict__ cell_slot, const int* __restrict__ order,
+                                             int n_cells, const CellGeom* __restrict__ geom,
+                                             const int* __restrict__ cell_frow, const FaceItem* __restrict__ items,
+                                             const double* __restrict__ fpar, const double* __restrict__ cpar,
+                                             const double* __restrict__ params, Phys ph, double* __restrict__ cmom,
+                                             int CH, int nch) {
+    const int n = n_cells * nch;
+    for (int it = item0(); it < n; it += istride()) {
+        const int kc = it / n_cells, c = order[it - kc * n_cells];
+        const LevelDesc& L = lvs[cell_lev[c]];
+        const int beg = kc * CH;
+        if (beg >= L.N) continue;
+        const int N = min(L.N, beg + CH);      // end of this chunk
+        double m[11], u0, v0;
+        update_points<S, U, UPDATE_RE<S>, ST>(L, c, cell_slot, geom, cell_frow, items, fpar, cpar, params, ph, beg, N, m, u0, v0);
+        step_sum<11>(m);
+        if (lane_id() == 0) {
+            double* o = cmom + ((size_t)kc * n_cells + c) * NMOM;
+            for (int k = 0; k < 11; ++k) o[k] = m[k];
+            o[M_U0] = u0;
+            o[M_V0] = v0;
+        }
+    }
+}
+
 template <typename S, int U, int MINW>
 __global__ __launch_bounds__(BS, MINW) void k_update(const LevelDesc* __restrict__ lvs,
                                                      const int* __restrict__ cell_lev,
@@ -2414,23 +2485,24 @@ __global__ __launch_bounds__(BS, MINW) void k_update(const LevelDesc* __restrict
                                                      const double* __restrict__ cpar,
                                                      const double* __restrict__ params, Phys ph,
                                                      double* __restrict__ cmom, int CH, int nch) {
-    const int n = n_cells * nch;
-    for (int it = item0(); it < n; it += istride()) {
-        const int kc = it / n_cells, c = order[it - kc * n_cells];
-        const LevelDesc& L = lvs[cell_lev[c]];
-        const int beg = kc * CH;
-        if (beg >= L.N) continue;
-        const int N = min(L.N, beg + CH);      // end of this chunk
-        double m[11], u0, v0;
-        update_points<S, U, true>(L, c, cell_slot, geom, cell_frow, items, fpar, cpar, params, ph, beg, N, m, u0, v0);
-        step_sum<11>(m);
-        if (lane_id() == 0) {
-            double* o = cmom + ((size_t)kc * n_cells + c) * NMOM;
-            for (int k = 0; k < 11; ++k) o[k] = m[k];
-            o[M_U0] = u0;
-            o[M_V0] = v0;
-        }
-    }
+    update_items<S, U, true>(lvs, cell_lev, cell_slot, order, n_cells, geom, cell_frow, items, fpar, cpar, params, ph, cmom,
+                          CH, nch);
+}
+
+template <typename S, int U, int MINW>
+__global__ __launch_bounds__(BS, MINW) void k_update_cached(const LevelDesc* __restrict__ lvs,
+                                                            const int* __restrict__ cell_lev,
+                                                            const int* __restrict__ cell_slot,
+                                                            const int* __restrict__ order, int n_cells,
+                                                            const CellGeom* __restrict__ geom,
+                                                            const int* __restrict__ cell_frow,
+                                                            const FaceItem* __restrict__ items,
+                                                            const double* __restrict__ fpar,
+                                                            const double* __restrict__ cpar,
+                                                            const double* __restrict__ params, Phys ph,
+                                                            double* __restrict__ cmom, int CH, int nch) {
+    update_items<S, U, false>(lvs, cell_lev, cell_slot, order, n_cells, geom, cell_frow, items, fpar, cpar, params, ph, cmom,
+                          CH, nch);
 }
 
 // The update followed, in the same wave, by the next step's cell stage for
@@ -2453,7 +2525,7 @@ __device__ __forceinline__ void update_cell_items(const LevelDesc* __restrict__ 
         const LevelDesc& L = lvs[cell_lev[c]];
         double cm[NMOM], u0, v0;
         double m[11];
-        update_points<S, U, false>(L, c, cell_slot, geom, cell_frow, items, fpar, nullptr, params, ph, 0, L.N, m, u0,
+        update_points<S, U, false, false>(L, c, cell_slot, geom, cell_frow, items, fpar, nullptr, params, ph, 0, L.N, m, u0,
                                    v0);
         step_sum<11>(m);
 #pragma unroll
@@ -2781,22 +2853,22 @@ constexpr int N_VARIANTS = 5;
     } while (0)
 
 // ... the reconstruction, per occupancy and mesh kind
-#define MLVS_LAUNCH_REC(prec, W_, M_, ...)                                                       \
+#define MLVS_LAUNCH_REC(prec, KERNEL, W_, M_, ...)                                               \
     do {                                                                                        \
-        if ((prec) == 32) hipLaunchKernelGGL((k_face_rec<float, W_, M_>), __VA_ARGS__);          \
-        else hipLaunchKernelGGL((k_face_rec<double, W_, M_>), __VA_ARGS__);                      \
+        if ((prec) == 32) hipLaunchKernelGGL((KERNEL<float, W_, M_>), __VA_ARGS__);              \
+        else hipLaunchKernelGGL((KERNEL<double, W_, M_>), __VA_ARGS__);                          \
     } while (0)
-#define MLVS_DISPATCH_REC(prec, var, mk, ...)                                                    \
+#define MLVS_DISPATCH_REC(prec, var, mk, KERNEL, ...)                                            \
     do {                                                                                        \
         if (mk) {                                                                               \
-            MLVS_LAUNCH_REC(prec, 2, 1, __VA_ARGS__);                                            \
+            MLVS_LAUNCH_REC(prec, KERNEL, 2, 1, __VA_ARGS__);                                            \
         } else {                                                                                \
             switch (var) {                                                                      \
-            case 0: MLVS_LAUNCH_REC(prec, 2, 0, __VA_ARGS__); break;                             \
-            case 2: MLVS_LAUNCH_REC(prec, 4, 0, __VA_ARGS__); break;                             \
-            case 3: MLVS_LAUNCH_REC(prec, 5, 0, __VA_ARGS__); break;                             \
-            case 4: MLVS_LAUNCH_REC(prec, 1, 0, __VA_ARGS__); break;                             \
-            default: MLVS_LAUNCH_REC(prec, 3, 0, __VA_ARGS__); break;                            \
+            case 0: MLVS_LAUNCH_REC(prec, KERNEL, 2, 0, __VA_ARGS__); break;                     \
+            case 2: MLVS_LAUNCH_REC(prec, KERNEL, 4, 0, __VA_ARGS__); break;                     \
+            case 3: MLVS_LAUNCH_REC(prec, KERNEL, 5, 0, __VA_ARGS__); break;                     \
+            case 4: MLVS_LAUNCH_REC(prec, KERNEL, 1, 0, __VA_ARGS__); break;                     \
+            default: MLVS_LAUNCH_REC(prec, KERNEL, 3, 0, __VA_ARGS__); break;                     \
             }                                                                                   \
         }                                                                                       \
     } while (0)
@@ -2817,17 +2889,25 @@ static inline int axes_grid(int n) {
 
 hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev, const int* cell_slot,
                             const int* order, int n_cells, Phys ph, double* params, const double* cmom, int CH,
-                            double* cpar, bool tensor, int var) {
+                            double* cpar, bool tensor, bool stream, int var) {
     if (n_cells <= 0) return hipSuccess;
     if (tensor && ph.compat != 8) {
         MLVS_DISPATCH(prec, k_cell_target_axes, dim3(axes_grid(n_cells)), dim3(BS), 0, st, lv, cell_lev, n_cells, ph,
                       params, cmom, CH, cpar);
-        MLVS_DISPATCH_V(prec, var, k_phibar, dim3(grid_for(n_cells)), dim3(BS), 0, st, lv, cell_lev, cell_slot, order,
-                        n_cells, cpar);
+        if (stream)
+            MLVS_DISPATCH_V(prec, var, k_phibar, dim3(grid_for(n_cells)), dim3(BS), 0, st, lv, cell_lev, cell_slot,
+                            order, n_cells, cpar);
+        else
+            MLVS_DISPATCH_V(prec, var, k_phibar_cached, dim3(grid_for(n_cells)), dim3(BS), 0, st, lv, cell_lev,
+                            cell_slot, order, n_cells, cpar);
         return hipGetLastError();
     }
-    MLVS_DISPATCH_VC(prec, var, ph.compat, k_cell_prep, n_cells, dim3(GBS), 0, st, lv, cell_lev,
-                     cell_slot, order, n_cells, ph, params, cmom, CH, cpar);
+    if (stream)
+        MLVS_DISPATCH_VC(prec, var, ph.compat, k_cell_prep, n_cells, dim3(GBS), 0, st, lv, cell_lev, cell_slot, order,
+                         n_cells, ph, params, cmom, CH, cpar);
+    else
+        MLVS_DISPATCH_VC(prec, var, ph.compat, k_cell_prep_cached, n_cells, dim3(GBS), 0, st, lv, cell_lev, cell_slot,
+                         order, n_cells, ph, params, cmom, CH, cpar);
     return hipGetLastError();
 }
 
@@ -2860,11 +2940,16 @@ hipError_t launch_ghost(int prec, hipStream_t st, const LevelDesc* lv, const Gho
 hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev, const int* cell_slot,
                            const int* cell_nbr, const int* cell_frow, const int* order, int n_cells,
                            const FaceItem* items, int nF, const CellGeom* geom, const double* params, Phys ph,
-                           double* fmom, int CH, int nch, int var) {
+                           double* fmom, int CH, int nch, bool stream, int var) {
     if (n_cells <= 0 || nF <= 0) return hipSuccess;
-    MLVS_DISPATCH_REC(prec, var, ph.mesh_kind, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st, lv,
-                      cell_lev, cell_slot, cell_nbr, cell_frow, order, n_cells, items, nF, geom, params, ph, fmom, CH,
-                      nch);
+    if (stream)
+        MLVS_DISPATCH_REC(prec, var, ph.mesh_kind, k_face_rec, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st, lv,
+                          cell_lev, cell_slot, cell_nbr, cell_frow, order, n_cells, items, nF, geom, params, ph, fmom,
+                          CH, nch);
+    else
+        MLVS_DISPATCH_REC(prec, var, ph.mesh_kind, k_face_rec_cached, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st,
+                          lv, cell_lev, cell_slot, cell_nbr, cell_frow, order, n_cells, items, nF, geom, params, ph,
+                          fmom, CH, nch);
     return hipGetLastError();
 }
 
@@ -2909,10 +2994,14 @@ hipError_t launch_update_cell(int prec, hipStream_t st, const LevelDesc* lv, con
 hipError_t launch_update(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev, const int* cell_slot,
                          const int* order, int n_cells, const CellGeom* geom, const int* cell_frow,
                          const FaceItem* items, const double* fpar, const double* cpar, const double* params, Phys ph, double* cmom,
-                         int CH, int nch, int var) {
+                         int CH, int nch, bool stream, int var) {
     if (n_cells <= 0) return hipSuccess;
-    MLVS_DISPATCH_U(prec, var, k_update, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st, lv, cell_lev, cell_slot,
-                    order, n_cells, geom, cell_frow, items, fpar, cpar, params, ph, cmom, CH, nch);
+    if (stream)
+        MLVS_DISPATCH_U(prec, var, k_update, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st, lv, cell_lev, cell_slot,
+                        order, n_cells, geom, cell_frow, items, fpar, cpar, params, ph, cmom, CH, nch);
+    else
+        MLVS_DISPATCH_U(prec, var, k_update_cached, dim3(grid_for(n_cells * nch)), dim3(BS), 0, st, lv, cell_lev,
+                        cell_slot, order, n_cells, geom, cell_frow, items, fpar, cpar, params, ph, cmom, CH, nch);
     return hipGetLastError();
 }
 
@@ -3682,7 +3771,7 @@ __global__ __launch_bounds__(BS, MINW) void k_step_persistent(const StepArgs* __
     xface_items<S, MK>(A->lvs, A->xfaces, nx, A->cell_slot, A->cell_nbr, A->geom, A->params, ph, A->neg, first,
                           stride);
     const int fstart = ((first - nx) % stride + stride) % stride;
-    cell_rec_items<S, MK>(A->lvs, A->cell_lev, A->cell_slot, A->cell_nbr, A->cell_frow, A->order, A->n_cells, A->faces,
+    cell_rec_items<S, MK, true>(A->lvs, A->cell_lev, A->cell_slot, A->cell_nbr, A->cell_frow, A->order, A->n_cells, A->faces,
                           A->n_faces, A->geom, A->params, ph, A->fmom, 1 << 30, 1, fstart, stride);
     grid_barrier(A->sync, phase);
     face_target_items<S, U, CM>(A->lvs, A->faces, A->n_faces, A->bcs, ph, A->fmom, A->fpar, 1 << 30, first,
@@ -3738,20 +3827,21 @@ int persistent_variant_count() { return 2; }
 
 // What variant `var` of a stage launches (the rules of the dispatches above):
 // the kernel family times sixteen plus the index, where the index chooses.
-int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, bool fused, int n_cells, int nF) {
-    enum { F_C8 = 16, F_UMESH = 32, F_TENSOR = 64, F_LARGE = 128, F_WAVE = 256 };
+int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, bool fused, bool stream, int n_cells,
+                 int nF) {
+    enum { F_C8 = 16, F_UMESH = 32, F_TENSOR = 64, F_LARGE = 128, F_WAVE = 256, F_CACHED = 512 };
     const int c8 = compat == 8 ? F_C8 : 0, um = mesh_kind ? F_UMESH : 0, axes = tensor && !c8 ? F_TENSOR : 0;
-    const int rec = um ? um : var;
+    const int rows = stream ? 0 : F_CACHED, rec = um ? um : var;
     auto staged = [&](int n, int tensor_form) {
         return axes ? tensor_form : c8 ? c8 : n >= IPW_MIN ? (int)F_LARGE : var;
     };
     switch (stage) {
-    case 0: return staged(n_cells, axes + var);
-    case 2: return rec;
+    case 0: return rows | staged(n_cells, axes + var);
+    case 2: return rows | rec;
     case 3: return staged(nF, axes);
     case 4: return um ? um : var == 2 ? 2 : 0;
-    case 5: return var;
-    case 7: return rec | (fused && !axes && (c8 || nF < IPW_MIN) ? F_WAVE | c8 : staged(nF, axes));
+    case 5: return rows | var;
+    case 7: return rows | rec | (fused && !axes && (c8 || nF < IPW_MIN) ? F_WAVE | c8 : staged(nF, axes));
     case 8: return (c8 | axes) + var;
     case 9: return (c8 | um | axes) + (um ? 0 : var);
     default: return 0;

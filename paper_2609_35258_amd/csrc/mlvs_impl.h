@@ -144,13 +144,15 @@ struct StepArgs {
 // Launch wrappers (kernels.hip).  `S` selects float (32) or double (64) storage.
 int variant_count();
 // Equal values: these variants of a stage launch the same kernels.
-int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, bool fused, int n_cells, int nF);
+int variant_form(int stage, int var, int compat, int mesh_kind, bool tensor, bool fused, bool stream, int n_cells,
+                 int nF);
 // order: the cells in traversal order (a permutation of 0..n_cells-1).  cpar:
 // n_cells records (NFP).  tensor: every level is the tensor base grid and takes
-// axis sums.
+// axis sums.  stream (also below): the level set's rows are larger than the
+// caches and are streamed past them.
 hipError_t launch_cell_prep(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                             const int* cell_slot, const int* order, int n_cells, Phys ph, double* params,
-                            const double* cmom, int CH, double* cpar, bool tensor, int var = 1);
+                            const double* cmom, int CH, double* cpar, bool tensor, bool stream, int var = 1);
 hipError_t launch_raw_moments(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                               const int* cell_slot, int n_cells, const double* params, double* cmom, int CH,
                               int nch);
@@ -160,7 +162,7 @@ hipError_t launch_ghost(int prec, hipStream_t st, const LevelDesc* lv, const Gho
 hipError_t launch_face_rec(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                            const int* cell_slot, const int* cell_nbr, const int* cell_frow, const int* order,
                            int n_cells, const FaceItem* items, int nF, const CellGeom* geom, const double* params,
-                           Phys ph, double* fmom, int CH, int nch, int var = 1);
+                           Phys ph, double* fmom, int CH, int nch, bool stream, int var = 1);
 // items: n_in interior faces, then boundary faces, n in all; axes: every level is
 // the tensor base grid and takes axis sums; fused: a stage of the fused step
 hipError_t launch_face_target(int prec, hipStream_t st, const LevelDesc* lv, const FaceItem* items, int n, int n_in,
@@ -172,7 +174,7 @@ hipError_t launch_xface(int prec, hipStream_t st, const LevelDesc* lv, const XFa
 // The persistent step (one launch per time step over the work lists in A,
 // preceded by a one-thread kernel that clears the barrier counter in sync):
 // `var` 0 or 1 (one or two velocity points per lane and load batch).  The
-// grid is the kernel's occupancy times the number of compute units.
+// grid is the kernel's occupancy times the number of compute units, or less.
 int persistent_variant_count();
 // items: the most items of a stage over all level sets of the mesh.
 hipError_t launch_step_persistent(int prec, hipStream_t st, const StepArgs* A, unsigned int* sync, Phys ph, int items,
@@ -186,7 +188,7 @@ hipError_t launch_update_cell(int prec, hipStream_t st, const LevelDesc* lv, con
 hipError_t launch_update(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                          const int* cell_slot, const int* order, int n_cells, const CellGeom* geom,
                          const int* cell_frow, const FaceItem* items, const double* fpar, const double* cpar, const double* params,
-                         Phys ph, double* cmom, int CH, int nch, int var = 1);
+                         Phys ph, double* cmom, int CH, int nch, bool stream, int var = 1);
 hipError_t launch_init_eq(int prec, hipStream_t st, const LevelDesc* lv, const int* cell_lev,
                           const int* cell_slot, int n_cells, const double* rho_u_v_T, Phys ph,
                           double* params);
