@@ -1742,9 +1742,9 @@ void build_items(mlvs_ctx c) {
     // the L2s) are streamed past them, in favour of those that two items read.  A
     // step has six to eight arrays of such rows; by the bytes of one, us a step kept
     // in the caches and streamed, cavity, 81^2 points: FP32 21 MB 194 and 207, 27 MB
-    // 231 and 246, 42 MB 317 and 293, 82 MB 567 and 493; FP64 30 MB 254 and 282, 41 MB
-    // 314 and 324, 54 MB 413 and 369.
-    constexpr double CACHED_ROWS = 40e6;
+    // 231 and 246, 37 MB 270 and 260, 42 MB 317 and 293, 82 MB 567 and 493; FP64 30 MB
+    // 254 and 282, 41 MB 314 and 324, 54 MB 413 and 369.
+    constexpr double CACHED_ROWS = 32e6;
     double row_bytes = 0.0;
     for (int l = 0; l < K; ++l) row_bytes += (double)c->levels[l]->n_cells * c->levels[l]->stride * c->elt();
     c->stream = row_bytes >= CACHED_ROWS;
@@ -1787,18 +1787,27 @@ void build_items(mlvs_ctx c) {
     }
     int nmax = 1;
     for (int l = 0; l < K; ++l) nmax = std::max(nmax, c->levels[l]->N);
-    // Velocity chunk of the streaming stages (reconstruction and update, a wave
-    // per cell and chunk): whole rows unless there are too few faces, about two
-    // per cell, to fill the GPU with waves, then the fewest chunks that do.  Levels of at most
-    // FUSE_MAX_POINTS points always take whole rows and the fused step.
+    // Velocity chunk of the streaming stages (reconstruction and update, a wave per
+    // cell and chunk): whole rows unless there are too few faces, about two per
+    // cell, to fill the GPU with waves, then the fewest chunks that do, but none
+    // shorter than MIN_CHUNK points: a wave's way to its first row is as long as a
+    // few hundred points, and the next stage adds the chunks' sums.  From 2000 cells on
+    // one round of waves (3072) is nearly full, and halves of short rows only start a
+    // second one, up to the cells that need it anyway.  Step, chunks of the
+    // fewest faces alone and so, us: 1-D FP32 200 cells, 1201 points 77.6 and 54.3,
+    // 1000, 2001 142 and 94.1, 4000, 1201 176 and 133; 2-D FP32 8 x 8, 61^2 116 and
+    // 65.5, 32 x 32 158 and 146, 45 x 45, 41^2 143 and 122; FP64 132 and 95, 223 and
+    // 211, 189 and 172.  Levels of at most FUSE_MAX_POINTS points always take whole
+    // rows and the fused step.
     constexpr int FUSE_MAX_POINTS = 1024, MIN_ITEMS = 16384;
+    const int MIN_CHUNK = n < 512 ? 256 : n < 2000 ? 1024 : n < 3072 && nmax < 3328 ? nmax : 832;
     const int nf_all = std::max<int>(nF_all, 1);
     if (c->chunk_env > 0) {
         c->chunk = c->chunk_env;
     } else {
         int parts = 1;
         if (nmax > FUSE_MAX_POINTS && nf_all < MIN_ITEMS)
-            parts = std::min((MIN_ITEMS + nf_all - 1) / nf_all, (nmax + 63) / 64);
+            parts = std::min((MIN_ITEMS + nf_all - 1) / nf_all, std::max(nmax / MIN_CHUNK, 1));
         c->chunk = ((nmax + parts - 1) / parts + 63) / 64 * 64;
     }
     if (c->persistent) c->chunk = (nmax + 63) / 64 * 64;    // whole rows (the fused bodies)

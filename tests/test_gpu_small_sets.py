@@ -47,6 +47,24 @@ def test_base_grid_on_both_sides_of_the_rule(case, precision):
     g.close()
 
 
+@pytest.mark.parametrize("make", [lambda: W.cavity(2, nv=41, vel_kind="nc", vmax=5.0),
+                                  lambda: W.sod_1d(600, Kn=0.1, nv=1201, vmax=6.0)], ids=["cells_4", "sod_600"])
+def test_chosen_chunks_fp64(make):
+    # rows longer than the fused step's: chunks of 256 points and a remainder for
+    # four cells, one chunk of the whole row for 600
+    import paper_2609_35258_amd as m
+    p = W.perturb(make(), seed=7)
+    o = Oracle(p, compat=4)
+    g = m.Solver.from_problem(p, compat=4)
+    assert "face_rec" in g.step_stages()
+    for k in range(2):
+        o.step()
+        g.step(1)
+        e = state_error(g.get_state(), o.g, o.h)
+        assert max(e) < 1e-12, (k, e)
+    g.close()
+
+
 @pytest.mark.parametrize("compat", [0, 4, 8])
 @pytest.mark.parametrize("mesh", ["cavity", "triangles"])
 def test_wave_targets_over_two_levels_fp64(mesh, compat):
