@@ -896,15 +896,19 @@ int angle_units(double x, double y) {
     return (int)std::max(-2147483648.0, std::min(2147483647.0, std::nearbyint(a)));
 }
 
-// CellGeom::ang of every mesh: the outward normal of each slot's face.
+// CellGeom::ang of every mesh: the outward normal of each slot's face (one arc
+// tangent per face, the other side is half a turn on).
 void normal_angles(MeshH& M) {
+    std::vector<int> in(M.faces.size()), bnd(M.bfaces.size());
+    for (size_t f = 0; f < in.size(); ++f) in[f] = angle_units(M.faces[f].nx, M.faces[f].ny);
+    for (size_t b = 0; b < bnd.size(); ++b) bnd[b] = angle_units(M.bfaces[b].nx, M.bfaces[b].ny);
     for (int c = 0; c < M.n_cells; ++c)
         for (int k = 0; k < 4; ++k) {
             const int f = M.face_of_cell[4 * c + k], b = M.bface_of_cell[4 * c + k];
             if (f < 0 && b < 0) continue;
-            const FaceH& F = f >= 0 ? M.faces[f] : M.bfaces[b];
-            const double s = f >= 0 && !(F.L == c && (M.unstructured || k == 1 || k == 3)) ? -1.0 : 1.0;
-            M.geom[c].ang[k] = angle_units(s * F.nx, s * F.ny);
+            const bool left = f < 0 || (M.faces[f].L == c && (M.unstructured || k == 1 || k == 3));
+            const unsigned a = (unsigned)(f >= 0 ? in[f] : bnd[b]);
+            M.geom[c].ang[k] = (int)(left ? a : a + 0x80000000u);
         }
 }
 
